@@ -1678,49 +1678,72 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
     return rc;
 }
 
-// Row-major copy of an nC x nC matrix (given column-major when `transpose`)
-// with rows padded to an even length, and the r_C buffer of the dense product.
-int upload_dense_coarse(bddc_ctx *c, const std::vector<double> &h, bool transpose) {
+// The dense coarse operator from an nC x nC device matrix (column-major when
+// `transpose`, else row-major), its rows padded to an even length, and the
+// r_C buffer of the dense product.
+int set_dense_coarse(bddc_ctx *c, const double *d_src, bool transpose) {
     const int n = c->nC;
     c->ldm = (n + 1) & ~1;
-    std::vector<double> t((size_t)n * c->ldm, 0.0);
-    for (int r = 0; r < n; ++r)
-        for (int q = 0; q < n; ++q)
-            t[(size_t)r * c->ldm + q] = transpose ? h[(size_t)q * n + r] : h[(size_t)r * n + q];
     int rc;
-    if ((rc = dupload(c, &c->d_Mc, t)) || (rc = dalloc(c, &c->d_rC, (size_t)std::max(1, n)))) return rc;
+    if ((rc = dalloc(c, &c->d_Mc, (size_t)n * c->ldm)) || (rc = dalloc(c, &c->d_rC, (size_t)std::max(1, n)))) return rc;
+    launch_pad_rows(d_src, n, transpose, c->d_Mc, c->ldm, c->stream);
     return 0;
 }
 
 // The level-2 BDDC approximation of K_C^{-1} is a fixed linear operator: its
-// columns are the level-2/3 chain applied to the unit vectors e_q (rc reads
-// the coarse residual from one dense vector), stored row-major.
+// columns are the level-2/3 chain applied to the unit vectors e_q, EXPL_COLS
+// columns a launch (one grid row per column, as in the block products: one
+// column alone is a few dozen blocks of dependent loads, 40 us whatever its
+// size).  rc reads e_q from one vector of zeros around a single 1: column q
+// starts q entries before the 1, so consecutive columns are a stride of -1
+// apart.  (64^3, 1,932 columns: a training step with its setup 477 -> 383 ms;
+// 32^3, 216 columns: 118 -> 109 ms.)
+constexpr int EXPL_COLS = 256;
+
 int build_explicit_coarse(bddc_ctx *c) {
     const int n = c->nC;
     hipStream_t s = c->stream;
-    std::vector<int32_t> ptr(n + 1), idx(n);
-    for (int q = 0; q <= n; ++q) ptr[q] = q;
-    for (int q = 0; q < n; ++q) idx[q] = q;
-    int32_t *dp, *di;
-    double *de, *dcol;
+    std::vector<int32_t> ptr(n + 1);
+    std::iota(ptr.begin(), ptr.end(), 0);              // (the gather list too: entry q is value q)
+    const int nb = std::min(EXPL_COLS, n);
+    int64_t i2 = 0, b2 = 0, c3 = 0;
+    for (const SubregionHost &r : c->st.sr) { i2 += r.nI; b2 += r.nB; c3 += (int64_t)r.c3.size(); }
+    const int64_t n3 = std::max(1, c->n3);
+    i2 = std::max<int64_t>(1, i2); b2 = std::max<int64_t>(1, b2); c3 = std::max<int64_t>(1, c3);
+    int32_t *dp;
+    double *de, *dcol, *vI2, *t2, *rB2, *u2, *c3loc, *u3, *r3;
     int rc;
-    if ((rc = dupload(c, &dp, ptr)) || (rc = dupload(c, &di, idx)) || (rc = dalloc(c, &de, (size_t)n)) ||
-        (rc = dalloc(c, &dcol, (size_t)n * n)))
+    if ((rc = dupload(c, &dp, ptr)) || (rc = dalloc(c, &de, 2 * (size_t)n)) || (rc = dalloc(c, &dcol, (size_t)n * n)) ||
+        (rc = dalloc(c, &vI2, (size_t)i2 * nb)) || (rc = dalloc(c, &t2, (size_t)b2 * nb)) ||
+        (rc = dalloc(c, &rB2, (size_t)b2 * nb)) || (rc = dalloc(c, &u2, (size_t)b2 * nb)) ||
+        (rc = dalloc(c, &c3loc, (size_t)c3 * nb)) || (rc = dalloc(c, &u3, (size_t)n3 * nb)) ||
+        (rc = dalloc(c, &r3, (size_t)n3 * nb)))
         return rc;
-    launch_fill(n, 0.0, de, s);
+    launch_fill(2 * (int64_t)n, 0.0, de, s);
+    launch_fill(1, 1.0, de + n, s);
     launch_set_done(c->d_ctl, 0, s);
-    const L2Args l = l2_args(c, Gather{dp, di, de});
-    for (int q = 0; q < n; ++q) {
-        launch_fill(1, 1.0, de + q, s);
-        run_l2_chain(c, l, s);
-        launch_copy(n, c->d_uC, dcol + (int64_t)q * n, s);
-        launch_fill(1, 0.0, de + q, s);
+    L2Args l = l2_args(c, Gather{dp, dp, de});
+    l.vI2 = vI2; l.t2 = t2; l.rB2 = rB2; l.u2 = u2; l.c3loc = c3loc; l.u3 = u3;
+    l.cs_rc = -1; l.cs_vI2 = i2; l.cs_t2 = l.cs_rB2 = l.cs_u2 = b2; l.cs_c3loc = c3; l.cs_u3 = n3; l.cs_uC = n;
+    CoarseDenseArgs l3{};
+    l3.ctl = c->d_ctl; l3.n = c->n3; l3.rc = Gather{c->d_asm3_ptr, c->d_asm3_idx, c3loc}; l3.r = r3;
+    l3.M = c->d_K3inv; l3.ldm = c->ld3; l3.sign = -1.0; l3.u = u3;
+    l3.cs_rc = c3; l3.cs_r = n3; l3.cs_u = n3;
+    for (int q0 = 0; q0 < n; q0 += nb) {
+        const int nq = std::min(nb, n - q0);
+        l.rc.part = de + n - q0;
+        l.uC = dcol + (int64_t)q0 * n;
+        launch_l2_a(l, c->nsr, c->max_nL, s, nq);
+        launch_l2_b(l, c->nsr, c->max_nL, s, nq);
+        launch_coarse_dense(l3, s, nq);
+        launch_l2_d(l, c->nsr, c->smem_l2d, s, nq);
     }
+    if ((rc = set_dense_coarse(c, dcol, true))) return rc;
     HIPCHK(hipStreamSynchronize(s));
-    std::vector<double> h((size_t)n * n);
-    HIPCHK(hipMemcpy(h.data(), dcol, h.size() * sizeof(double), hipMemcpyDeviceToHost));
-    dfree(c, dp); dfree(c, di); dfree(c, de); dfree(c, dcol);
-    return upload_dense_coarse(c, h, true);
+    for (void *q : {(void *)dp, (void *)de, (void *)dcol, (void *)vI2, (void *)t2, (void *)rB2, (void *)u2, (void *)c3loc,
+                    (void *)u3, (void *)r3})
+        dfree(c, q);
+    return 0;
 }
 
 int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, const double *coef) {
@@ -1998,13 +2021,9 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_KCinv, n, n, 0, n, n}}))) {
             return rc;
         }
+        if (n > 0 && (rc = set_dense_coarse(c, c->d_KCinv, false))) return rc;
         HIPCHK(hipStreamSynchronize(s));
         dfree(c, dp); dfree(c, di);
-        if (n > 0) {
-            std::vector<double> h((size_t)n * n);
-            HIPCHK(hipMemcpy(h.data(), c->d_KCinv, h.size() * sizeof(double), hipMemcpyDeviceToHost));
-            if ((rc = upload_dense_coarse(c, h, false))) return rc;
-        }
         dfree(c, c->d_KCinv);
         c->d_KCinv = nullptr;
     } else {

@@ -210,6 +210,20 @@ __global__ void __launch_bounds__(256) k_dense_copy(const DenseCopyDesc *descs) 
     }
 }
 
+// setup: n x n matrix (column-major when `trans`, else row-major) into rows of
+// ldm >= n entries, zero past n; 32 x 32 tiles through LDS so that both sides
+// are read and written in whole lines
+__global__ void __launch_bounds__(256) k_pad_rows(const double *src, int n, int trans, double *dst, int64_t ldm) {
+    __shared__ double t[32][33];
+    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int a0 = trans ? c0 : r0, b0 = trans ? r0 : c0;      // source tile: lines a, entries b
+    for (int i = y; i < 32; i += 8)
+        t[i][x] = (a0 + i < n && b0 + x < n) ? src[(int64_t)(a0 + i) * n + b0 + x] : 0.0;
+    __syncthreads();
+    for (int i = y; i < 32; i += 8)
+        if (r0 + i < n && c0 + x < ldm) dst[(int64_t)(r0 + i) * ldm + c0 + x] = trans ? t[x][i] : t[i][x];
+}
+
 // out[t] = sum_{k in [ptr[t], ptr[t+1])} src[idx[k]]
 __global__ void __launch_bounds__(256) k_gather_sum(int64_t n, const int32_t *ptr, const int32_t *idx,
                                                     const double *src, double *out) {
@@ -644,6 +658,10 @@ void launch_ptsp(const PtspDesc *d, int n, hipStream_t s) {
 }
 void launch_dense_copy(const DenseCopyDesc *d, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_dense_copy, dim3(n), dim3(256), 0, s, d);
+}
+void launch_pad_rows(const double *src, int n, bool trans, double *dst, int64_t ldm, hipStream_t s) {
+    if (n > 0)
+        hipLaunchKernelGGL(k_pad_rows, dim3(nblk(ldm, 32), nblk(n, 32)), dim3(256), 0, s, src, n, trans ? 1 : 0, dst, ldm);
 }
 void launch_gather_sum(int64_t n, const int32_t *ptr, const int32_t *idx, const double *src, double *out, hipStream_t s) {
     if (n > 0) hipLaunchKernelGGL(k_gather_sum, dim3(nblk(n, 256)), dim3(256), 0, s, n, ptr, idx, src, out);
