@@ -1512,9 +1512,56 @@ int setup_operators(bddc_ctx *c) {
     return 0;
 }
 
-// Interior inverses K_II^{-1} packed like the other symmetric operators, and
-// the sparse couplings K_IB (interior rows) and K_BI (interface rows) from
-// the element matrices c_e h Kref (Section 2), for condensation and recovery.
+// The sparse couplings K_IB (interior rows) and K_BI (interface rows) from the
+// assembled local matrices (before their interiors are eliminated).
+int setup_couplings(bddc_ctx *c, const std::vector<int64_t> &k_off) {
+    const Structure &st = c->st;
+    const int nsub = st.n_sub;
+    hipStream_t s = c->stream;
+    int64_t ni = 0, nb = 0;
+    for (const SubHost &sh : st.sub) { ni += sh.nI; nb += sh.nB; }
+    int32_t *d_tot;
+    CoupDesc *dd;
+    int rc;
+    if ((rc = dalloc(c, &c->d_kib_ptr, (size_t)ni + 1)) || (rc = dalloc(c, &c->d_kbi_ptr, (size_t)nb + 1)) ||
+        (rc = dalloc(c, &d_tot, 2 * (size_t)nsub)) || (rc = dalloc(c, &dd, (size_t)nsub)))
+        return rc;
+    std::vector<CoupDesc> cd(nsub);
+    ni = nb = 0;
+    for (int i = 0; i < nsub; ++i) {
+        const SubHost &sh = st.sub[i];
+        cd[i] = CoupDesc{c->d_K + k_off[i], sh.nloc, sh.nI, c->d_kib_ptr + ni, c->d_kbi_ptr + nb, 0, 0};
+        ni += sh.nI;
+        nb += sh.nB;
+    }
+    HIPCHK(hipMemcpyAsync(dd, cd.data(), nsub * sizeof(CoupDesc), hipMemcpyHostToDevice, s));
+    launch_couple_count(dd, nsub, d_tot, s);
+    std::vector<int32_t> tot(2 * (size_t)nsub);
+    HIPCHK(hipMemcpyAsync(tot.data(), d_tot, tot.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    int64_t eib = 0, ebi = 0;
+    for (int i = 0; i < nsub; ++i) {
+        cd[i].ib0 = (int32_t)eib;
+        cd[i].bi0 = (int32_t)ebi;
+        eib += tot[i];
+        ebi += tot[(size_t)nsub + i];
+    }
+    if (std::max(eib, ebi) > INT32_MAX) return fail(BDDC_EINVAL, "interior-interface couplings exceed int32 indexing");
+    if ((rc = dalloc(c, &c->d_kib_col, (size_t)eib)) || (rc = dalloc(c, &c->d_kib_val, (size_t)eib)) ||
+        (rc = dalloc(c, &c->d_kbi_col, (size_t)ebi)) || (rc = dalloc(c, &c->d_kbi_val, (size_t)ebi)))
+        return rc;
+    const int32_t end_ib = (int32_t)eib, end_bi = (int32_t)ebi;
+    HIPCHK(hipMemcpyAsync(dd, cd.data(), nsub * sizeof(CoupDesc), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(c->d_kib_ptr + ni, &end_ib, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(c->d_kbi_ptr + nb, &end_bi, sizeof(int32_t), hipMemcpyHostToDevice, s));
+    launch_couple_fill(dd, nsub, c->d_kib_col, c->d_kib_val, c->d_kbi_col, c->d_kbi_val, s);
+    HIPCHK(hipStreamSynchronize(s));
+    dfree(c, d_tot); dfree(c, dd);
+    return 0;
+}
+
+// Interior inverses K_II^{-1} packed like the other symmetric operators, for
+// condensation and recovery.
 int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
     const int nsub = c->n_sub;
     const Structure &st = c->st;
@@ -1536,43 +1583,7 @@ int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
         HIPCHK(hipStreamSynchronize(c->stream));
         dfree(c, dpk);
     }
-    // K_IB from the element matrices; Kref: 1/3 on the diagonal, 0 between
-    // vertices differing in one coordinate, -1/12 otherwise
-    std::vector<int32_t> ib_ptr(1, 0), ib_col, bi_ptr(1, 0), bi_col;
-    std::vector<double> ib_val, bi_val;
-    for (int i = 0; i < nsub; ++i) {
-        const SubHost &sh = st.sub[i];
-        const int nI = sh.nI, nB = sh.nB;
-        std::vector<std::map<int, double>> rows(nI), cols(nB);
-        for (size_t t = 0; t < sh.elem.size(); ++t) {
-            for (int v = 0; v < 8; ++v) {
-                const int a = sh.elem_loc[t * 8 + v];
-                if (a < 0 || a >= nI) continue;
-                for (int w = 0; w < 8; ++w) {
-                    const int b = sh.elem_loc[t * 8 + w];
-                    if (b < nI) continue;
-                    const int nd = __builtin_popcount(v ^ w);
-                    if (nd == 1) continue;
-                    const double kv = sh.elem_c[t] * (nd == 0 ? 1.0 / 3.0 : -1.0 / 12.0);
-                    rows[a][b - nI] += kv;
-                    cols[b - nI][a] += kv;
-                }
-            }
-        }
-        for (int a = 0; a < nI; ++a) {
-            for (auto &e : rows[a]) { ib_col.push_back(e.first); ib_val.push_back(e.second); }
-            ib_ptr.push_back((int32_t)ib_col.size());
-        }
-        for (int k = 0; k < nB; ++k) {
-            for (auto &e : cols[k]) { bi_col.push_back(e.first); bi_val.push_back(e.second); }
-            bi_ptr.push_back((int32_t)bi_col.size());
-        }
-    }
-    if ((rc = dupload(c, &c->d_kib_ptr, ib_ptr)) || (rc = dupload(c, &c->d_kib_col, ib_col)) ||
-        (rc = dupload(c, &c->d_kib_val, ib_val)) || (rc = dupload(c, &c->d_kbi_ptr, bi_ptr)) ||
-        (rc = dupload(c, &c->d_kbi_col, bi_col)) || (rc = dupload(c, &c->d_kbi_val, bi_val)) ||
-        (rc = dalloc(c, &c->d_tmpN, (size_t)c->n_nodes)))
-        return rc;
+    if ((rc = dalloc(c, &c->d_tmpN, (size_t)c->n_nodes))) return rc;
     OpHost &op = c->opI;
     op.interior = true;
     op.prec = 64;
@@ -1824,6 +1835,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             AsmDesc *dd;
             if ((rc = dupload(c, &dd, ad))) return rc;
             launch_assemble(dd, nsub, s);
+            if ((rc = setup_couplings(c, k_off))) return rc;
             // interior elimination: sweep the interior pivots of every K_i
             std::vector<SweepDesc> sd(nsub);
             for (int i = 0; i < nsub; ++i)

@@ -25,6 +25,15 @@ struct AsmDesc {
     double *K;
 };
 
+// Couplings K_IB, K_BI of one subdomain from its assembled matrix (row-major,
+// interior rows first): CSR rows at ib_ptr (nI of them) and bi_ptr (nloc - nI).
+struct CoupDesc {
+    const double *K;
+    int nloc, nI;
+    int32_t *ib_ptr, *bi_ptr;
+    int32_t ib0, bi0;               // the subdomain's first entry in the CSR arrays
+};
+
 // ======================================================== operator products
 // One segment of a batched symmetric product: tiles [t0, t1) of the packed
 // tile sequence of one subdomain, whose tiles start at tile `tile` of the
@@ -323,6 +332,9 @@ struct GradArgs {
 };
 
 // setup (kernels.hip)
+void launch_couple_count(const CoupDesc *d, int n, int32_t *totals, hipStream_t s);
+void launch_couple_fill(const CoupDesc *d, int n, int32_t *ib_col, double *ib_val, int32_t *bi_col, double *bi_val,
+                        hipStream_t s);
 void launch_assemble(const AsmDesc *d, int n, hipStream_t s);
 void launch_rank1(double *A, int64_t ld, int n, const double *e, double coef, hipStream_t s);
 // batched symmetric sweeps in panels of 16 pivots (sweep.hip): the panel

@@ -43,6 +43,92 @@ __global__ void __launch_bounds__(256) k_assemble(const AsmDesc *descs) {
 }
 
 // ---------------------------------------------------------------------------
+// setup: the sparse couplings K_IB (interior rows) and K_BI (interface rows)
+// as CSR, for condensation and recovery, from the assembled dense K_i before
+// its interior is eliminated: a wave scans one row of the off-diagonal block
+// 64 columns at a time (one whole line per load; the block is read twice, at
+// 192^3 15 GB a pass) and a ballot gives each entry its place, so the columns
+// come out ascending.  An entry sums equal signs (-c_e h / 12, Section 2), so
+// it is nonzero exactly where the nodes share an element and differ in more
+// than one coordinate.  (The same lists by std::map on one host thread took
+// 79 ms of a 64^3 setup and 3.4 s of a 192^3 one; a 64^3 training step with its
+// setup went from 383 to 305 ms, a 32^3 one from 109 to 101 ms.)
+// k_couple_count: row counts into ptr[row]; k_couple_scan (one block per
+// subdomain and side): their exclusive prefix sums in place and the totals
+// (K_IB's, then K_BI's); k_couple_fill: offsets added, entries written.
+// ---------------------------------------------------------------------------
+constexpr int COUP_ROWS = 8;        // blocks that share a subdomain's rows
+
+template <typename F>
+__device__ __forceinline__ void couple_rows(const CoupDesc &d, F row) {
+    const int nw = blockDim.x >> 6, l = threadIdx.x & 63;
+    for (int r = blockIdx.y * nw + (threadIdx.x >> 6); r < d.nloc; r += COUP_ROWS * nw) {
+        const bool in = r < d.nI;
+        const int c0 = in ? d.nI : 0, m = in ? d.nloc - d.nI : d.nI;
+        row(r, in, d.K + (size_t)r * d.nloc + c0, m, l);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_couple_count(const CoupDesc *descs) {
+    const CoupDesc d = descs[blockIdx.x];
+    couple_rows(d, [&](int r, bool in, const double *K, int m, int l) {
+        int n = 0;
+#pragma unroll 4
+        for (int c = 0; c < m; c += 64) n += __popcll(__ballot(c + l < m && K[c + l] != 0.0));
+        if (l == 0) (in ? d.ib_ptr : d.bi_ptr - d.nI)[r] = n;
+    });
+}
+
+__global__ void __launch_bounds__(256) k_couple_scan(const CoupDesc *descs, int n, int32_t *totals) {
+    __shared__ int32_t wsum[4];
+    const CoupDesc d = descs[blockIdx.x];
+    const bool in = blockIdx.y == 0;
+    int32_t *p = in ? d.ib_ptr : d.bi_ptr;
+    const int m = in ? d.nI : d.nloc - d.nI, t = threadIdx.x, w = t >> 6, l = t & 63;
+    int32_t base = 0;
+    for (int r0 = 0; r0 < m; r0 += 256) {
+        const int32_t v = r0 + t < m ? p[r0 + t] : 0;
+        int32_t x = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(x, o);
+            if (l >= o) x += y;
+        }
+        if (l == 63) wsum[w] = x;
+        __syncthreads();
+        int32_t pre = base;
+        for (int q = 0; q < w; ++q) pre += wsum[q];
+        if (r0 + t < m) p[r0 + t] = pre + x - v;
+        base += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        __syncthreads();
+    }
+    if (t == 0) totals[blockIdx.y * n + blockIdx.x] = base;
+}
+
+__global__ void __launch_bounds__(256) k_couple_fill(const CoupDesc *descs, int32_t *ib_col, double *ib_val,
+                                                     int32_t *bi_col, double *bi_val) {
+    const CoupDesc d = descs[blockIdx.x];
+    couple_rows(d, [&](int r, bool in, const double *K, int m, int l) {
+        int32_t *ptr = (in ? d.ib_ptr : d.bi_ptr - d.nI) + r;
+        int32_t *col = in ? ib_col : bi_col;
+        double *val = in ? ib_val : bi_val;
+        int e = *ptr + (in ? d.ib0 : d.bi0);
+        if (l == 0) *ptr = e;
+#pragma unroll 4
+        for (int c = 0; c < m; c += 64) {
+            const double v = c + l < m ? K[c + l] : 0.0;
+            const uint64_t b = __ballot(v != 0.0);
+            if (v != 0.0) {
+                const int at = e + __popcll(b & ((1ull << l) - 1));
+                col[at] = c + l;
+                val[at] = v;
+            }
+            e += __popcll(b);
+        }
+    });
+}
+
+// ---------------------------------------------------------------------------
 // setup: Schur complement onto the last m = n - p entries of a permuted copy
 // of S (symmetric positive semi-definite, positive definite on the p leading
 // entries), for the adaptive face selection: k_face_gather copies S(perm,
@@ -624,6 +710,14 @@ void launch_rank1(double *A, int64_t ld, int n, const double *e, double coef, hi
 }
 void launch_assemble(const AsmDesc *d, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_assemble, dim3(n), dim3(256), 0, s, d);
+}
+void launch_couple_count(const CoupDesc *d, int n, int32_t *totals, hipStream_t s) {
+    hipLaunchKernelGGL(k_couple_count, dim3(n, COUP_ROWS), dim3(256), 0, s, d);
+    hipLaunchKernelGGL(k_couple_scan, dim3(n, 2), dim3(256), 0, s, d, n, totals);
+}
+void launch_couple_fill(const CoupDesc *d, int n, int32_t *ib_col, double *ib_val, int32_t *bi_col, double *bi_val,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(k_couple_fill, dim3(n, COUP_ROWS), dim3(256), 0, s, d, ib_col, ib_val, bi_col, bi_val);
 }
 void launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &h, SweepDesc *d_sw, int64_t *d_off,
                        double *panel, int *status, hipStream_t s) {

@@ -41,3 +41,35 @@ def test_explicit_coarse_operator_is_the_chain(name, cons):
         r = torch.randn(a.n_gamma, dtype=torch.float64, device="cuda", generator=g)
         za, zb = a.apply_precond(r), b.apply_precond(r)
         assert (za - zb).abs().max().item() <= 1e-12 * zb.abs().max().item()
+
+
+def _box(nx, cells):
+    cell = (np.arange(nx) * cells) // nx
+    return (cell[None, None, :] + cells * (cell[None, :, None] + cells * cell[:, None, None])).ravel().astype(np.int32)
+
+
+@pytest.mark.parametrize("nx,part", [
+    (4, _box(4, 2)),         # one interior node a subdomain, at most 19 interface nodes: rows within one wave
+    (15, _box(15, 2)),       # 7^3 / 6^3 interiors, interfaces past 64 and 128 columns
+    (24, _box(24, 2)),       # 12^3 subdomains: 1,331 interior nodes, 12 prefix rounds
+    (6, np.minimum(np.arange(216) % 6, 2).astype(np.int32)),   # the middle slab has no interior node
+])
+def test_condensation_couplings(nx, part):
+    """The condensed right-hand side and the recovered interiors use the
+    couplings K_IB, K_BI: against the oracle's substructuring (each an
+    O(1)-conditioned local solve: 1e-11 of the largest entry)."""
+    torch = _torch()
+    from oracle.sequence import OracleSolver
+    from paper_2412_17543_amd.solver import Solver
+    coef = workload.lognormal_coef(nx ** 3, 0.5)
+    print("[gpu] couplings %d^3, %d subdomains" % (nx, part.max() + 1), flush=True)
+    g = Solver(nx, part, coef, constraints=("corners", "faces"), autotune=False)
+    o = OracleSolver(nx, part, coef)
+    F = workload.rhs_sequence(nx, 1)
+    b = g.condense(torch.tensor(F[0], device="cuda")).cpu().numpy()
+    bo = o.ss.condense(F[0])
+    bo = bo[0] if isinstance(bo, tuple) else bo
+    assert np.abs(b - bo).max() <= 1e-11 * np.abs(bo).max()
+    U, its, rr = g.solve_sequence(torch.tensor(F, device="cuda"), 1e-12)
+    uo, _, _ = o.solve_sequence(F, 1e-12)
+    assert np.abs(U[0].cpu().numpy() - uo[0]).max() <= 1e-10 * np.abs(uo[0]).max()
