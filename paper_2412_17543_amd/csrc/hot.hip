@@ -176,18 +176,51 @@ __device__ __forceinline__ double to_d(double v) { return v; }
 __device__ __forceinline__ double to_d(float v) { return (double)v; }
 __device__ __forceinline__ double to_d(uint16_t v) { return (double)dev::bf16_to_f32(v); }
 
+// s plus, in list order, the partial products part[idx[e]], e in [e0, e1): the
+// first four together (most nodes have two to four entries: pointer, index
+// and value latencies once each), the rest L at a time.  A subdomain cut into
+// many segments gives lists of up to dozens of entries, which one by one cost
+// two latencies each (residual update: 16^3, 12 to 48 entries a node, 11.2 ->
+// 6.6 us; holed 64^3 16.1 -> 9.0 us).
+template <int L>
+__device__ __forceinline__ double gather_range(const int32_t *idx, const double *part, int e, int e1, double s) {
+    if constexpr (L > 4) {
+        while (e < e1) {                    // (past the list: its last entry again, not added)
+            int id[L];
+            double v[L];
+#pragma unroll
+            for (int u = 0; u < L; ++u) id[u] = idx[min(e + u, e1 - 1)];
+#pragma unroll
+            for (int u = 0; u < L; ++u) v[u] = part[id[u]];
+#pragma unroll
+            for (int u = 0; u < L; ++u)
+                if (e + u < e1) s += v[u];
+            e += L;
+        }
+    } else {
+        for (; e < e1; e += L) {
+            int id[L];
+            double v[L];
+#pragma unroll
+            for (int u = 0; u < L; ++u) id[u] = e + u < e1 ? idx[e + u] : -1;
+#pragma unroll
+            for (int u = 0; u < L; ++u) v[u] = id[u] >= 0 ? part[id[u]] : 0.0;
+#pragma unroll
+            for (int u = 0; u < L; ++u)
+                if (id[u] >= 0) s += v[u];
+        }
+    }
+    return s;
+}
+
 // Sum of the partial products listed for assembled entry t (fixed order).
+// LONG: lists of product segments, else lists of subdomains (at most 8 or so).
+template <bool LONG = false>
 __device__ __forceinline__ double gather_sum(const Gather &G, int64_t t) {
     const int e0 = G.ptr[t], e1 = G.ptr[t + 1];
-    double s = 0.0;
-    int e = e0;
-    for (; e + 3 < e1; e += 4) {
-        const double a0 = G.part[G.idx[e]], a1 = G.part[G.idx[e + 1]];
-        const double a2 = G.part[G.idx[e + 2]], a3 = G.part[G.idx[e + 3]];
-        s += a0; s += a1; s += a2; s += a3;
-    }
-    for (; e < e1; ++e) s += G.part[G.idx[e]];
-    return s;
+    if constexpr (!LONG) return gather_range<4>(G.idx, G.part, e0, e1, 0.0);
+    const double s = gather_range<4>(G.idx, G.part, e0, min(e0 + 4, e1), 0.0);
+    return gather_range<16>(G.idx, G.part, e0 + 4, e1, s);
 }
 
 // Stopping test of Section 5 (eq. stopping_rhs, or eq. stopping_residual with
@@ -629,8 +662,7 @@ __device__ __forceinline__ void upd_load(const UpdArgs &a, int64_t gb, int64_t s
 #pragma unroll
         for (int m = 0; m < UPD_SLOTS; ++m)
             if (id[u][m] >= 0) sum += v[m];
-        for (int e = e0[u] + UPD_SLOTS; e < e1[u]; ++e) sum += a.q.part[a.q.idx[e]];
-        q[u] = sum;
+        q[u] = gather_range<16>(a.q.idx, a.q.part, e0[u] + UPD_SLOTS, e1[u], sum);
     }
 }
 
@@ -813,7 +845,19 @@ __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
     // w = sum of the partials, then the basis terms, in column order
     auto row = [&](int k, const double (&u)[CF], const double (&r)[PF]) {
         double w = 0.0;
-        for (int cc = 0; cc < C; ++cc) w += cc < CF ? u[cc] : up[(int64_t)cc * n + k];
+#pragma unroll
+        for (int cc = 0; cc < CF; ++cc)
+            if (cc < C) w += u[cc];
+        // (a subdomain cut into many segments, four partials a round: holed
+        // 64^3 22.9 -> 16.7 us a launch)
+        for (int cc = CF; cc < C; cc += CF) {
+            double v[CF];
+#pragma unroll
+            for (int m = 0; m < CF; ++m) v[m] = ld_rc(ur, (cc + m) * n + k);
+#pragma unroll
+            for (int m = 0; m < CF; ++m)
+                if (cc + m < C) w += v[m];
+        }
 #pragma unroll
         for (int q = 0; q < PF; ++q)
             if (q < nci) w += r[q] * uCl[q];
@@ -981,7 +1025,7 @@ __global__ void __launch_bounds__(256) k_resid(ResidArgs a) {
     for (int q = 0; q <= KM; ++q) acc[q] = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < a.n; g += stride) {
-        const double q = gather_sum(a.q, g);
+        const double q = gather_sum<true>(a.q, g);
         const double r = a.b ? a.b[g] - q : q;
         a.out[g] = r;
         acc[0] += r * r;
