@@ -78,26 +78,22 @@ int adaptive_faces(const Structure &st, const double *d_K, const std::vector<int
     for (const auto &sh : st.sub) max_nB = std::max(max_nB, (size_t)sh.nB);
     const size_t per_job = max_nB * max_nB;
     const size_t batch = std::max<size_t>(1, std::min<size_t>(faces.size() * 2, (size_t(2) << 30) / (per_job * 8)));
-    double *d_work = nullptr, *d_out = nullptr, *d_panel = nullptr;
+    double *d_work = nullptr, *d_out = nullptr;
+    char *d_sweep = nullptr;
     int32_t *d_perm = nullptr;
     FaceSchurDesc *d_desc = nullptr;
-    SweepDesc *d_sw = nullptr;
-    int64_t *d_off = nullptr;
     auto cleanup = [&]() {
         if (d_work) (void)hipFree(d_work);
         if (d_out) (void)hipFree(d_out);
         if (d_perm) (void)hipFree(d_perm);
         if (d_desc) (void)hipFree(d_desc);
-        if (d_panel) (void)hipFree(d_panel);
-        if (d_sw) (void)hipFree(d_sw);
-        if (d_off) (void)hipFree(d_off);
+        if (d_sweep) (void)hipFree(d_sweep);
     };
     size_t max_m = 1;
     for (const auto &f : faces) max_m = std::max(max_m, (size_t)f.m);
     if (hipMalloc(&d_work, batch * per_job * 8) != hipSuccess || hipMalloc(&d_out, batch * 2 * max_m * max_m * 8) != hipSuccess ||
         hipMalloc(&d_perm, batch * max_nB * 4) != hipSuccess || hipMalloc(&d_desc, batch * sizeof(FaceSchurDesc)) != hipSuccess ||
-        hipMalloc(&d_panel, batch * 32 * max_nB * 8) != hipSuccess || hipMalloc(&d_sw, batch * sizeof(SweepDesc)) != hipSuccess ||
-        hipMalloc(&d_off, batch * sizeof(int64_t)) != hipSuccess) {
+        hipMalloc(&d_sweep, sweep_workspace_bound(batch, (int)max_nB)) != hipSuccess) {
         cleanup();
         err = "hipMalloc failed for the adaptive face problems";
         return BDDC_ENOMEM;
@@ -132,9 +128,8 @@ int adaptive_faces(const Structure &st, const double *d_K, const std::vector<int
             err = "hipMemcpy failed";
             return BDDC_EHIP;
         }
-        launch_face_schur(d_desc, std::vector<FaceSchurDesc>(desc.begin(), desc.begin() + nj), d_sw, d_off, d_panel,
-                          d_status, s);
-        if (hipMemcpyAsync(hout.data(), d_out, nj * 2 * max_m * max_m * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        if (launch_face_schur(d_desc, std::vector<FaceSchurDesc>(desc.begin(), desc.begin() + nj), d_sweep, d_status, s) ||
+            hipMemcpyAsync(hout.data(), d_out, nj * 2 * max_m * max_m * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess) {
             cleanup();
             err = "face Schur complements failed";

@@ -250,21 +250,15 @@ void dfree(bddc_ctx *c, void *p) {
     (void)hipFree(p);
 }
 
-// Batched symmetric sweeps (sweep.hip) of the matrices `h` (device copies of
-// the descriptors and the panel buffer are made here and freed after the
-// stream has finished them).
+// Batched symmetric sweeps (sweep.hip) of the matrices `h`; the workspace is
+// freed after the stream has finished them.
 int run_sweeps(bddc_ctx *c, const std::vector<SweepDesc> &h) {
     if (h.empty()) return 0;
-    std::vector<int64_t> off;
-    const int64_t nbuf = sweep_panel_doubles(h, off);
-    SweepDesc *dd = nullptr;
-    int64_t *doff = nullptr;
-    double *buf = nullptr;
-    int rc;
-    if ((rc = dupload(c, &dd, h)) || (rc = dupload(c, &doff, off)) || (rc = dalloc(c, &buf, (size_t)nbuf))) return rc;
-    launch_sweep_blocked(dd, doff, h, buf, c->d_status, c->stream);
+    char *ws = nullptr;
+    if (int rc = dalloc(c, &ws, sweep_workspace(h))) return rc;
+    if (launch_sweeps(h, ws, c->d_status, c->stream)) return fail(BDDC_EHIP, "upload of the sweep lists failed");
     HIPCHK(hipStreamSynchronize(c->stream));
-    dfree(c, dd); dfree(c, doff); dfree(c, buf);
+    dfree(c, ws);
     return 0;
 }
 
@@ -1393,7 +1387,7 @@ int adapt_level2(bddc_ctx *c, const std::vector<int32_t> &nc, const std::vector<
     std::vector<SweepDesc> sw(nsr);
     for (int j = 0; j < nsr; ++j) {
         const int n = (int)st.sr[j].L.size();
-        sw[j] = SweepDesc{dK + K2_off[j], n, n, 0, st.sr[j].nI, n};
+        sw[j] = SweepDesc{dK + K2_off[j], n, n, st.sr[j].nI, n};
     }
     if ((rc = run_sweeps(c, sw))) return rc;
     std::vector<double> h((size_t)K2_off[nsr]);
@@ -1467,7 +1461,7 @@ int sweep_semidefinite(bddc_ctx *c, double *A, int n, int64_t ld, const std::vec
     double *de;
     if ((rc = dupload(c, &de, e))) return rc;
     launch_rank1(A, ld, n, de, a, c->stream);
-    if ((rc = run_sweeps(c, {SweepDesc{A, n, (int)ld, 0, n, n}}))) return rc;
+    if ((rc = run_sweeps(c, {SweepDesc{A, n, (int)ld, n, n}}))) return rc;
     launch_rank1(A, ld, n, de, 1.0 / (a * ee * ee), c->stream);
     HIPCHK(hipStreamSynchronize(c->stream));
     dfree(c, de);
@@ -1839,7 +1833,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             // interior elimination: sweep the interior pivots of every K_i
             std::vector<SweepDesc> sd(nsub);
             for (int i = 0; i < nsub; ++i)
-                sd[i] = SweepDesc{c->d_K + k_off[i], st.sub[i].nloc, st.sub[i].nloc, 0, nI[i], st.sub[i].nloc};
+                sd[i] = SweepDesc{c->d_K + k_off[i], st.sub[i].nloc, st.sub[i].nloc, nI[i], st.sub[i].nloc};
             if ((rc = run_sweeps(c, sd))) return rc;
             dfree(c, dd);
         }
@@ -1956,7 +1950,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             const int nl = st.sub[i].nloc, N = nB[i] + nc[i];
             sd[i] = SaddleDesc{c->d_K + k_off[i] + (int64_t)nI[i] * nl + nI[i], nl, nB[i], nc[i],
                                d_cptr + cp_off[i], d_ccol + cc_off[i], d_cval + cc_off[i], d_M + m_off[i], N};
-            wd[i] = SweepDesc{d_M + m_off[i], N, N, 0, N, nB[i]};
+            wd[i] = SweepDesc{d_M + m_off[i], N, N, N, nB[i]};
         }
         SaddleDesc *dsd;
         if ((rc = dupload(c, &dsd, sd))) return rc;
@@ -2030,7 +2024,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         launch_gather_sum((int64_t)n * n, dp, di, c->d_KC, c->d_KCinv, s);
         if (n > 0 && c->nullc) {
             if ((rc = sweep_semidefinite(c, c->d_KCinv, n, n, coarse_null_vector(st)))) return rc;
-        } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_KCinv, n, n, 0, n, n}}))) {
+        } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_KCinv, n, n, n, n}}))) {
             return rc;
         }
         if (n > 0 && (rc = set_dense_coarse(c, c->d_KCinv, false))) return rc;
@@ -2151,9 +2145,9 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
                 const int n = nL[j], i2 = nI2[j], b = n - i2, N = b + nc3[j];
                 double *Kj = c->d_K2 + K2_off[j];
                 const double *Sj = Kj + (int64_t)i2 * n + i2;
-                s1[j] = SweepDesc{Kj, n, n, 0, i2, n};
+                s1[j] = SweepDesc{Kj, n, n, i2, n};
                 sd[j] = SaddleDesc{Sj, n, b, nc3[j], d_cptr2 + cp2[j], d_ccol2 + cc2[j], d_cval2 + cc2[j], d_M2 + M2_off[j], N};
-                s2[j] = SweepDesc{d_M2 + M2_off[j], N, N, 0, N, b};
+                s2[j] = SweepDesc{d_M2 + M2_off[j], N, N, N, b};
                 cn[j] = DenseCopyDesc{d_M2 + M2_off[j], N, b, b, -1.0, d_w2 + B2_off[j], d_w2 + B2_off[j], c->d_N2 + N2_off[j], b};
                 cp[j] = DenseCopyDesc{d_M2 + M2_off[j] + b, N, b, nc3[j], -1.0, d_w2 + B2_off[j], nullptr, c->d_Phi2 + P2_off[j], nc3[j]};
                 pt[j] = PtspDesc{Sj, n, d_M2 + M2_off[j] + b, N, -1.0, b, nc3[j], d_X2 + P2_off[j], d_K3loc + K3_off[j]};
@@ -2198,7 +2192,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
                     for (size_t q = 0; q < st.dof3_members[m3].size(); ++q)
                         e3[m3] += st.dof3_wts[m3][q] * e1[st.dof3_members[m3][q]];
                 if ((rc = sweep_semidefinite(c, c->d_K3inv, n, ld, e3))) return rc;
-            } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_K3inv, n, ld, 0, n, n}}))) {
+            } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_K3inv, n, ld, n, n}}))) {
                 return rc;
             }
             // large levels: the upper triangle in 64 x 64 blocks for the

@@ -126,7 +126,7 @@ void sym_eig(std::vector<double> a, int n, std::vector<double> &w, std::vector<d
 struct SweepDesc {
     double *A;     // row-major symmetric matrix
     int n, ld;
-    int p0, p1;    // pivots [p0, p1) are swept
+    int p1;        // pivots [0, p1) are swept
     int pos_end;   // pivots < pos_end must be > 0, others < 0
 };
 

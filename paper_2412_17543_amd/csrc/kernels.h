@@ -337,17 +337,18 @@ void launch_couple_fill(const CoupDesc *d, int n, int32_t *ib_col, double *ib_va
                         hipStream_t s);
 void launch_assemble(const AsmDesc *d, int n, hipStream_t s);
 void launch_rank1(double *A, int64_t ld, int n, const double *e, double coef, hipStream_t s);
-// batched symmetric sweeps in panels of 16 pivots (sweep.hip): the panel
-// buffer holds 2 x 16 x n doubles per matrix at the offsets the sizing call
-// returns; pivots below pos_end must be positive, the others negative
-int64_t sweep_panel_doubles(const std::vector<SweepDesc> &h, std::vector<int64_t> &off);
-void launch_sweep_blocked(const SweepDesc *d, const int64_t *d_off, const std::vector<SweepDesc> &h, double *buf,
-                          int *status, hipStream_t s);
+// batched symmetric sweeps (sweep.hip) with a device workspace of
+// sweep_workspace(h) bytes (sweep_workspace_bound: enough for any `count`
+// matrices of up to n rows); pivots below pos_end must be positive, the others
+// negative.  Nonzero: the upload of the block lists failed.
+size_t sweep_workspace(const std::vector<SweepDesc> &h);
+size_t sweep_workspace_bound(size_t count, int n);
+int launch_sweeps(const std::vector<SweepDesc> &h, void *ws, int *status, hipStream_t s);
 // face Schur complements (adaptive step): gather S(perm, perm) into work and
-// its trailing block into keep, sweep the leading p pivots (d_sw, d_off and
-// panel sized for the batch by the caller), trailing block into hat
-void launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &h, SweepDesc *d_sw, int64_t *d_off,
-                       double *panel, int *status, hipStream_t s);
+// its trailing block into keep, sweep the leading p pivots (ws: a sweep
+// workspace sized for the batch by the caller), trailing block into hat
+int launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &h, void *ws, int *status,
+                      hipStream_t s);
 void launch_build_saddle(const SaddleDesc *d, int n, hipStream_t s);
 void launch_pack(const PackDesc *d, int n, int prec, void *dst, void *phir, hipStream_t s);
 void launch_ptsp(const PtspDesc *d, int n, hipStream_t s);

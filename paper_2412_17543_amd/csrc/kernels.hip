@@ -719,21 +719,17 @@ void launch_couple_fill(const CoupDesc *d, int n, int32_t *ib_col, double *ib_va
                         hipStream_t s) {
     hipLaunchKernelGGL(k_couple_fill, dim3(n, COUP_ROWS), dim3(256), 0, s, d, ib_col, ib_val, bi_col, bi_val);
 }
-void launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &h, SweepDesc *d_sw, int64_t *d_off,
-                       double *panel, int *status, hipStream_t s) {
+int launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &h, void *ws, int *status,
+                      hipStream_t s) {
     const int n = (int)h.size();
-    if (n <= 0) return;
+    if (n <= 0) return 0;
     std::vector<SweepDesc> sw(n);
-    for (int q = 0; q < n; ++q) sw[q] = SweepDesc{h[q].work, h[q].n, h[q].n, 0, h[q].p, h[q].p};
-    std::vector<int64_t> off;
-    sweep_panel_doubles(sw, off);
-    // (synchronous: the host vectors end with this call; the caller waits for
-    // the previous batch before reusing the buffers)
-    (void)hipMemcpy(d_sw, sw.data(), n * sizeof(SweepDesc), hipMemcpyHostToDevice);
-    (void)hipMemcpy(d_off, off.data(), n * sizeof(int64_t), hipMemcpyHostToDevice);
+    for (int q = 0; q < n; ++q) sw[q] = SweepDesc{h[q].work, h[q].n, h[q].n, h[q].p, h[q].p};
     hipLaunchKernelGGL(k_face_gather, dim3(n), dim3(256), 0, s, d);
-    launch_sweep_blocked(d_sw, d_off, sw, panel, status, s);
+    // (the caller waits for the previous batch before reusing the workspace)
+    if (launch_sweeps(sw, ws, status, s)) return -1;
     hipLaunchKernelGGL(k_face_hat, dim3(n), dim3(256), 0, s, d);
+    return 0;
 }
 void launch_build_saddle(const SaddleDesc *d, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_build_saddle, dim3(n), dim3(256), 0, s, d);

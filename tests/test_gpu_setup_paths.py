@@ -51,13 +51,16 @@ def _box(nx, cells):
 @pytest.mark.parametrize("nx,part", [
     (4, _box(4, 2)),         # one interior node a subdomain, at most 19 interface nodes: rows within one wave
     (15, _box(15, 2)),       # 7^3 / 6^3 interiors, interfaces past 64 and 128 columns
-    (24, _box(24, 2)),       # 12^3 subdomains: 1,331 interior nodes, 12 prefix rounds
+    (15, _box(15, 3)),       # an interior of exactly 64 pivots beside 80 to 125
+    (24, _box(24, 2)),       # 12^3 subdomains: 1,331 interior nodes and more, two dozen panels
     (6, np.minimum(np.arange(216) % 6, 2).astype(np.int32)),   # the middle slab has no interior node
 ])
-def test_condensation_couplings(nx, part):
-    """The condensed right-hand side and the recovered interiors use the
-    couplings K_IB, K_BI: against the oracle's substructuring (each an
-    O(1)-conditioned local solve: 1e-11 of the largest entry)."""
+def test_local_operators(nx, part):
+    """Interior eliminations, saddle inverses and the couplings K_IB, K_BI at
+    sizes around their panels and waves: the condensed right-hand side, A p,
+    M^{-1} r and the recovered solution against the oracle's substructuring
+    (local condition numbers up to ~1e3 on 1e-16 rounding: 1e-11 of the
+    largest entry)."""
     torch = _torch()
     from oracle.sequence import OracleSolver
     from paper_2412_17543_amd.solver import Solver
@@ -70,6 +73,10 @@ def test_condensation_couplings(nx, part):
     bo = o.ss.condense(F[0])
     bo = bo[0] if isinstance(bo, tuple) else bo
     assert np.abs(b - bo).max() <= 1e-11 * np.abs(bo).max()
+    x = np.random.default_rng(nx).standard_normal(g.n_gamma)
+    for got, want in ((g.apply_schur, o.ss.apply_A), (g.apply_precond, o.M.apply)):
+        y, yo = got(torch.tensor(x, device="cuda")).cpu().numpy(), want(x)
+        assert np.abs(y - yo).max() <= 1e-11 * np.abs(yo).max()
     U, its, rr = g.solve_sequence(torch.tensor(F, device="cuda"), 1e-12)
     uo, _, _ = o.solve_sequence(F, 1e-12)
     assert np.abs(U[0].cpu().numpy() - uo[0]).max() <= 1e-10 * np.abs(uo[0]).max()
