@@ -49,6 +49,7 @@ struct OpHost {
     bool interior = false;          // interior operators (sizes nI, no gather lists)
     std::vector<int32_t> nchunk;    // per subdomain
     int32_t *d_items = nullptr, *d_nchunk = nullptr, *d_pb = nullptr;
+    size_t items_cap = 0, yidx_cap = 0;   // allocated lengths (the tuner rebuilds the lists many times)
     double *d_ypart = nullptr;
     int64_t ypart_len = 0;          // allocated length of the partial buffer
     int64_t ylen = 0;               // partial entries the current work list writes
@@ -374,10 +375,13 @@ void flush_timing(bddc_ctx *c) {
 // span subdomains).  Per subdomain: every subdomain is cut into about
 // tiles / (total / nblocks) equal segments, one block each (a block never
 // spans subdomains; the block count follows the rounding).
-int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub) {
+// `lists`: also the gather lists of the products' consumers (not needed to
+// time the product alone).
+int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub, bool lists = true) {
     const int nsub = c->n_sub;
     struct Seg { int k; int64_t t0, t1; int32_t c; };
-    std::vector<std::vector<Seg>> blk;   // segments of every block, in order
+    std::vector<Seg> seg;                // segments, block after block
+    std::vector<size_t> first(1, 0);     // block b: segments [first[b], first[b + 1])
     std::vector<int32_t> nch(nsub, 0), pb(nsub), xoff(nsub + 1, 0);
     int64_t ylen = 0;
     const std::vector<int32_t> &sizes = op.interior ? c->h_nI : c->h_nB;
@@ -394,14 +398,12 @@ int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub) {
             const int64_t nt = start[k + 1] - start[k];
             if (nt == 0) continue;
             const int C = (int)std::min<int64_t>(nt, std::max<int64_t>(1, (nt + target / 2) / target));
-            for (int q = 0; q < C; ++q) blk.push_back({Seg{k, nt * q / C, nt * (q + 1) / C, nch[k]++}});
+            for (int q = 0; q < C; ++q) seg.push_back(Seg{k, nt * q / C, nt * (q + 1) / C, nch[k]++});
         }
-        nblocks = (int)blk.size();
+        nblocks = (int)seg.size();
         // longest items first: the blocks that start after the first round
         // are the short ones, which fill the compute units left idle early
-        std::stable_sort(blk.begin(), blk.end(), [](const std::vector<Seg> &x, const std::vector<Seg> &y) {
-            return x[0].t1 - x[0].t0 > y[0].t1 - y[0].t0;
-        });
+        std::stable_sort(seg.begin(), seg.end(), [](const Seg &x, const Seg &y) { return x.t1 - x.t0 > y.t1 - y.t0; });
         // XCD-aware order: consecutive blocks go to the 8 XCDs in turn, each
         // with its own L2.  Subdomain indices, like the interface numbering,
         // run through the domain in slabs, so inside every run of equal
@@ -409,30 +411,32 @@ int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub) {
         // each XCD then gathers its inputs from about an eighth of the
         // interface vector.  (The results do not depend on the order.)
         constexpr int NX = 8;
-        for (size_t r0 = 0; r0 < blk.size();) {
-            const int64_t len = blk[r0][0].t1 - blk[r0][0].t0;
-            size_t r1 = r0;
-            while (r1 < blk.size() && blk[r1][0].t1 - blk[r1][0].t0 == len) ++r1;
-            std::vector<std::vector<std::vector<Seg>>> slab(NX);
-            for (size_t p = r0; p < r1; ++p) slab[(int64_t)blk[p][0].k * NX / nsub].push_back(blk[p]);
-            std::vector<size_t> next(NX, 0);
+        std::vector<Seg> slab[NX];
+        for (size_t r0 = 0; r0 < seg.size();) {
+            const int64_t len = seg[r0].t1 - seg[r0].t0;
+            size_t r1 = r0, next[NX] = {};
+            for (auto &v : slab) v.clear();
+            for (; r1 < seg.size() && seg[r1].t1 - seg[r1].t0 == len; ++r1)
+                slab[(int64_t)seg[r1].k * NX / nsub].push_back(seg[r1]);
             for (size_t p = r0; p < r1; ++p) {
                 int g = (int)(p % NX);
                 while (next[g] == slab[g].size()) g = (g + 1) % NX;   // (some slab has one left)
-                blk[p] = slab[g][next[g]++];
+                seg[p] = slab[g][next[g]++];
             }
             r0 = r1;
         }
+        first.resize(nblocks + 1);
+        std::iota(first.begin(), first.end(), size_t(0));
     } else {
-        blk.resize(nblocks);
         int i = 0;
         for (int b = 0; b < nblocks; ++b) {
             const int64_t g0 = total * b / nblocks, g1 = total * (b + 1) / nblocks;
             while (i < nsub && start[i + 1] <= g0) ++i;
             for (int k = i; k < nsub && start[k] < g1; ++k) {
                 const int64_t t0 = std::max(g0, start[k]) - start[k], t1 = std::min(g1, start[k + 1]) - start[k];
-                if (t1 > t0) blk[b].push_back(Seg{k, t0, t1, nch[k]++});
+                if (t1 > t0) seg.push_back(Seg{k, t0, t1, nch[k]++});
             }
+            first.push_back(seg.size());
         }
     }
     for (int k = 0; k < nsub; ++k) {
@@ -449,22 +453,27 @@ int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub) {
     };
     for (int b = 0; b < nblocks; ++b) {
         int prev = b;
-        for (size_t q = 0; q < blk[b].size(); ++q) {
-            if (q == 0) {
-                items[b] = record(blk[b][0]);
+        for (size_t q = first[b]; q < first[b + 1]; ++q) {
+            if (q == first[b]) {
+                items[b] = record(seg[q]);
             } else {
                 items[prev].next = (int32_t)items.size();
                 prev = (int)items.size();
-                items.push_back(record(blk[b][q]));
+                items.push_back(record(seg[q]));
             }
         }
     }
-    dfree(c, op.d_items); dfree(c, op.d_nchunk); dfree(c, op.d_pb);
-    std::vector<int32_t> raw(items.size() * (sizeof(SymvItem) / 4));
-    std::memcpy(raw.data(), items.data(), items.size() * sizeof(SymvItem));
     int rc;
-    if ((rc = dupload(c, &op.d_items, raw)) || (rc = dupload(c, &op.d_nchunk, nch)) || (rc = dupload(c, &op.d_pb, pb)))
-        return rc;
+    const size_t raw = items.size() * (sizeof(SymvItem) / 4);
+    if (raw > op.items_cap) {
+        dfree(c, op.d_items);
+        if ((rc = dalloc(c, &op.d_items, raw))) return rc;
+        op.items_cap = raw;
+    }
+    if (!op.d_nchunk && ((rc = dalloc(c, &op.d_nchunk, nsub)) || (rc = dalloc(c, &op.d_pb, nsub)))) return rc;
+    HIPCHK(hipMemcpyAsync(op.d_items, items.data(), raw * 4, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(op.d_nchunk, nch.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(op.d_pb, pb.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     if (ylen > op.ypart_len) {
         dfree(c, op.d_ypart);
         if ((rc = dalloc(c, &op.d_ypart, (size_t)ylen))) return rc;
@@ -476,23 +485,28 @@ int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub) {
     op.dev.n_blocks = total > 0 ? nblocks : 0;
     op.dev.nchunk = op.d_nchunk;
     op.dev.pb = op.d_pb;
-    if (op.interior) return 0;      // interior entries have one owner: no lists
+    // (the Neumann partials are summed by subdomain, interior entries have one
+    // owner: no lists)
+    if (&op != &c->opS || !lists) return 0;
     // flat gather lists, owners in assembly order, items in increasing order
-    {
-        std::vector<int32_t> ptr(c->n_gamma + 1, 0), idx;
-        idx.reserve(ylen);
-        for (int g = 0; g < c->n_gamma; ++g) {
-            for (int e = c->h_asm_ptr[g]; e < c->h_asm_ptr[g + 1]; ++e) {
-                const int pos = c->h_asm_idx[e];
-                const int i = c->h_pos_sub[pos];
-                const int k = pos - c->h_b_off[i];
-                for (int q = 0; q < nch[i]; ++q) idx.push_back(pb[i] + q * c->h_nB[i] + k);
-            }
-            ptr[g + 1] = (int32_t)idx.size();
+    std::vector<int32_t> ptr(c->n_gamma + 1, 0), idx((size_t)ylen);
+    size_t w = 0;
+    for (int g = 0; g < c->n_gamma; ++g) {
+        for (int e = c->h_asm_ptr[g]; e < c->h_asm_ptr[g + 1]; ++e) {
+            const int pos = c->h_asm_idx[e], i = c->h_pos_sub[pos], n = c->h_nB[i];
+            int at = pb[i] + pos - c->h_b_off[i];
+            for (int q = 0; q < nch[i]; ++q, at += n) idx[w++] = at;
         }
-        dfree(c, op.d_yptr); dfree(c, op.d_yidx);
-        if ((rc = dupload(c, &op.d_yptr, ptr)) || (rc = dupload(c, &op.d_yidx, idx))) return rc;
+        ptr[g + 1] = (int32_t)w;
     }
+    if (!op.d_yptr && (rc = dalloc(c, &op.d_yptr, ptr.size()))) return rc;
+    if (w > op.yidx_cap) {
+        dfree(c, op.d_yidx);
+        if ((rc = dalloc(c, &op.d_yidx, w))) return rc;
+        op.yidx_cap = w;
+    }
+    HIPCHK(hipMemcpyAsync(op.d_yptr, ptr.data(), ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(op.d_yidx, idx.data(), w * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     return 0;
 }
 
@@ -617,20 +631,26 @@ void run_coarse(bddc_ctx *c, hipStream_t st) {
     }
 }
 
+// Arguments of the prolongation w_i = u_i + D Phi_i u_C of a single vector.
+ProlArgs prolong_args(const bddc_ctx *c, bool gated) {
+    ProlArgs pa{};
+    pa.ctl = c->d_ctl; pa.gated = gated ? 1 : 0;
+    pa.nB = c->d_nB; pa.b_off = c->d_b_off; pa.nc = c->d_nc; pa.c_off = c->d_c_off; pa.cidx = c->d_cidx;
+    pa.nchunk = c->opN.d_nchunk; pa.pb = c->opN.d_pb; pa.upart = c->opN.d_ypart;
+    pa.phir = c->d_phir; pa.phr_off = c->d_phr_off;
+    pa.uC = c->nC > 0 ? c->d_uC : nullptr;
+    pa.wloc = c->d_wloc;
+    pa.ch_sub = c->d_pch_sub; pa.ch_row = c->d_pch_row;
+    return pa;
+}
+
 // Prolongation w_i = u_i + D Phi_i u_C and assembly z = sum_i R_i^T w_i
 // (eq. averaging_subdomain_solves), with the (r^T z, (AW)^T z) partials when
 // `reduce` is set.
 void run_prolong_assemble(bddc_ctx *c, const double *r, double *z, bool gated, bool advance, bool reduce) {
     {
         TScope ts(c, TK_VEC);
-        ProlArgs pa{};
-        pa.ctl = c->d_ctl; pa.gated = gated ? 1 : 0;
-        pa.nB = c->d_nB; pa.b_off = c->d_b_off; pa.nc = c->d_nc; pa.c_off = c->d_c_off; pa.cidx = c->d_cidx;
-        pa.nchunk = c->opN.d_nchunk; pa.pb = c->opN.d_pb; pa.upart = c->opN.d_ypart;
-        pa.phir = c->d_phir; pa.phr_off = c->d_phr_off;
-        pa.uC = c->nC > 0 ? c->d_uC : nullptr;
-        pa.wloc = c->d_wloc;
-        pa.ch_sub = c->d_pch_sub; pa.ch_row = c->d_pch_row;
+        const ProlArgs pa = prolong_args(c, gated);
         launch_prolong(pa, c->prec, c->n_pch, c->max_nc, c->stream);
         ZasmArgs a{};
         a.n = c->n_gamma;
@@ -1602,9 +1622,21 @@ int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
     return build_worklist(c, op, product_blocks(c, op.n_tiles, op.bpc), op.per_sub);
 }
 
-// Tile-level autotuning of the two batched products on the operators just
-// built: work-list granularity (items per compute unit), waves per block and
-// tiles in flight per wave; the fastest of a few timed launches is kept.
+// Tile-level autotuning of the batched products on the operators just built:
+// work-list granularity (items per compute unit), waves per block and tiles in
+// flight per wave.  Splits that give the same work list as one already timed
+// are passed over (at 16^3 all seven balanced ones are the same).  On small
+// interfaces, where a split into many segments costs the consumers as much as
+// it gains the product (16^3: 48 segments give the update kernel up to 48
+// partials a node), the sum of the partials is timed with the product; from
+// TUNE_GATHER nodes on it follows the product's own time and the lists are
+// built once, for the configuration kept.  The interior product has the Schur
+// product's shape: it is timed on the TUNE_SHORT fastest configurations of
+// that one only.  (Every split used to build and upload all lists: 176 ms of a
+// 64^3 setup, 68 ms at 32^3.  A training step with its setup: 277 -> 139 ms and
+// 95 -> 41 ms; 16^3 sequence of 10: 5.08 -> 4.92 ms, Schur call 25.9 -> 24.7 us.)
+constexpr int TUNE_GATHER = 16384, TUNE_SHORT = 8;
+
 int tune_operators(bddc_ctx *c, int mask = 7) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIPCHK(hipEventCreate(&e0));
@@ -1612,71 +1644,102 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
     int rc = 0;
     const int bpcs[7] = {1, 2, 3, 4, 5, 6, 8};
     OpHost *ops[3] = {&c->opS, &c->opN, &c->opI};
+    struct Cand { float ms; int bpc, div; bool ps; SymvCfg cfg; };   // div: 1/div of the blocks of bpc
+    std::vector<Cand> schur;             // the Schur product's candidates, fastest first
     for (int w = 0; w < 3 && rc == 0; ++w) {
         OpHost &op = *ops[w];
         if (op.dev.n_blocks == 0 || !((mask >> w) & 1)) continue;
         const int mnt = op.interior ? c->max_ntI : c->max_nt;
-        float best = 1e30f;
-        int best_bpc = op.bpc;
-        bool best_ps = op.per_sub;
-        SymvCfg best_cfg{4, 2};
-        // times `reps` launches of a configuration (after 2 untimed ones)
-        auto time_cfg = [&](int bpc, bool ps, SymvCfg cfg, int reps, float &ms) -> int {
-            int r0 = build_worklist(c, op, product_blocks(c, op.n_tiles, bpc), ps);
-            if (r0) return r0;
+        const bool gather = !op.interior && c->n_gamma <= TUNE_GATHER;
+        // times `reps` launches of a configuration on the work list in place
+        // (after one untimed), with the gather of its partials
+        auto time_cfg = [&](SymvCfg cfg, int reps, bool with_gather, float &ms) -> int {
             const size_t smem = symv_smem(op.prec, cfg.nw, mnt);
             SymvArgs a{};
             a.op = op.dev; a.x = op.interior ? c->d_tmpN : c->d_x; a.ypart = op.d_ypart;
             a.ctl = c->d_ctl;
             if (w == 1) set_restriction(c, a);
-            for (int r = 0; r < 2; ++r) launch_symv(a, (SymvOp)w, op.prec, cfg, smem, c->stream);
+            ResidArgs r{};
+            r.n = c->n_gamma; r.q = gather_of(op); r.out = c->d_tmp; r.W = c->d_W; r.ld = c->ld; r.ctl = c->d_ctl;
+            r.part = c->d_wp;
+            auto once = [&]() {
+                launch_symv(a, (SymvOp)w, op.prec, cfg, smem, c->stream);
+                if (with_gather && w == 0) launch_resid(r, 0, c->vgrid, c->stream);
+                if (with_gather && w == 1) launch_prolong(prolong_args(c, false), c->prec, c->n_pch, c->max_nc, c->stream);
+            };
+            once();
             HIPCHK(hipEventRecord(e0, c->stream));
-            for (int r = 0; r < reps; ++r) launch_symv(a, (SymvOp)w, op.prec, cfg, smem, c->stream);
+            for (int q = 0; q < reps; ++q) once();
             HIPCHK(hipEventRecord(e1, c->stream));
             HIPCHK(hipEventSynchronize(e1));
             HIPCHK(hipEventElapsedTime(&ms, e0, e1));
             ms /= reps;
             return 0;
         };
-        struct Cand { float ms; int bpc; bool ps; SymvCfg cfg; };
+        auto split = [&](int bpc, int div, bool ps, bool lists) {
+            return build_worklist(c, op, std::max(1, product_blocks(c, op.n_tiles, bpc) / div), ps, lists);
+        };
         std::vector<Cand> cand;
-        for (int trial = 0; trial < 14 && rc == 0; ++trial) {
-            const bool ps = trial >= 7;
-            const int bpc = bpcs[trial % 7];
-            for (int nw : {4, 8}) {
-                if (nw == 8 && !c->allow8) continue;
-                for (int u : {2, 4}) {
-                    float ms = 0.f;
-                    if ((rc = time_cfg(bpc, ps, SymvCfg{nw, u}, 4, ms))) break;
-                    cand.push_back(Cand{ms, bpc, ps, SymvCfg{nw, u}});
+        if (w == 2 && !schur.empty()) {
+            for (size_t k = 0; k < schur.size() && k < (size_t)TUNE_SHORT && rc == 0; ++k) {
+                Cand t = schur[k];
+                if ((rc = split(t.bpc, t.div, t.ps, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
+                cand.push_back(t);
+            }
+        } else {
+            std::vector<std::vector<int32_t>> seen[2];   // splits timed: segments per subdomain
+            // (where the partials' sum counts, a half and a quarter of the fewest
+            // blocks too)
+            const int nt = gather ? 9 : 7;
+            for (int trial = 0; trial < 2 * nt && rc == 0; ++trial) {
+                const bool ps = trial >= nt;
+                const int q = trial % nt, bpc = q < 7 ? bpcs[q] : 1, div = q < 7 ? 1 : 1 << (q - 6);
+                if ((rc = split(bpc, div, ps, gather))) break;
+                std::vector<int32_t> key = op.nchunk;
+                key.push_back(op.dev.n_blocks);          // (a balanced split is its block count)
+                if (std::find(seen[ps].begin(), seen[ps].end(), key) != seen[ps].end()) continue;
+                seen[ps].push_back(std::move(key));
+                for (int nw : {4, 8}) {
+                    if (nw == 8 && !c->allow8) continue;
+                    for (int u : {2, 4}) {
+                        float ms = 0.f;
+                        if ((rc = time_cfg(SymvCfg{nw, u}, 3, gather, ms))) break;
+                        cand.push_back(Cand{ms, bpc, div, ps, SymvCfg{nw, u}});
+                    }
+                    if (rc) break;
                 }
-                if (rc) break;
             }
         }
+        if (rc || cand.empty()) break;
         // the four fastest, timed again in turn over two rounds (a single
         // short timing can be off by several percent); the lowest total wins
-        if (rc == 0 && !cand.empty()) {
-            std::stable_sort(cand.begin(), cand.end(), [](const Cand &x, const Cand &y) { return x.ms < y.ms; });
-            const size_t nk = std::min<size_t>(4, cand.size());
-            std::vector<float> tot(nk, 0.f);
-            for (int round = 0; round < 2 && rc == 0; ++round)
-                for (size_t k = 0; k < nk && rc == 0; ++k) {
-                    float ms = 0.f;
-                    if ((rc = time_cfg(cand[k].bpc, cand[k].ps, cand[k].cfg, 6, ms))) break;
-                    tot[k] += ms;
-                }
-            size_t kb = 0;
-            for (size_t k = 1; k < nk; ++k)
-                if (tot[k] < tot[kb]) kb = k;
-            best = tot[kb] / 2 * 4;       // (kept in the unit of four launches)
-            best_bpc = cand[kb].bpc; best_ps = cand[kb].ps; best_cfg = cand[kb].cfg;
+        std::stable_sort(cand.begin(), cand.end(), [](const Cand &x, const Cand &y) { return x.ms < y.ms; });
+        if (w == 0) schur = cand;
+        const size_t nk = std::min<size_t>(4, cand.size());
+        std::vector<float> tot(nk, 0.f);
+        for (int round = 0; round < 2 && rc == 0; ++round)
+            for (size_t k = 0; k < nk && rc == 0; ++k) {
+                float ms = 0.f;
+                if ((rc = split(cand[k].bpc, cand[k].div, cand[k].ps, gather)) || (rc = time_cfg(cand[k].cfg, 6, gather, ms))) break;
+                tot[k] += ms;
+            }
+        if (rc) break;
+        size_t kb = 0;
+        for (size_t k = 1; k < nk; ++k)
+            if (tot[k] < tot[kb]) kb = k;
+        const Cand &best = cand[kb];
+        op.cfg = best.cfg;
+        op.bpc = best.bpc;
+        op.per_sub = best.ps;
+        op.smem = symv_smem(op.prec, best.cfg.nw, mnt);
+        float us = tot[kb] / 2 * 1e3f;
+        if ((rc = split(best.bpc, best.div, best.ps, true))) break;
+        if (gather) {                                    // (reported: the product alone)
+            float ms = 0.f;
+            if ((rc = time_cfg(best.cfg, 6, false, ms))) break;
+            us = ms * 1e3f;
         }
-        if (rc == 0) rc = build_worklist(c, op, product_blocks(c, op.n_tiles, best_bpc), best_ps);
-        op.cfg = best_cfg;
-        op.bpc = best_bpc;
-        op.per_sub = best_ps;
-        op.smem = symv_smem(op.prec, best_cfg.nw, mnt);
-        op.tuned_us = best * 1e3f / 4;
+        op.tuned_us = us;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -2303,7 +2366,10 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         }
     }
     init_null_column(c);
-    if (c->opts.autotune && (rc = tune_operators(c))) return rc;
+    if (c->opts.autotune) {   // (a pinned product is not tuned)
+        const int mask = 7 & ~(c->opts.product_cfg[0] > 0 ? 1 : 0) & ~(c->opts.product_cfg[4] > 0 ? 2 : 0);
+        if ((rc = tune_operators(c, mask))) return rc;
+    }
     {   // pinned configurations
         OpHost *ops[2] = {&c->opS, &c->opN};
         for (int w = 0; w < 2; ++w) {
