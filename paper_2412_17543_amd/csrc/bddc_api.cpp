@@ -106,7 +106,7 @@ struct bddc_ctx {
     // condensation of up to CBLK right-hand sides per pass over the interior
     // tiles (k_symm): per-column partials, condensed b and ||b||^2 partials
     int cblk_state = 0;             // 0 not set up, 1 ready, -1 unavailable (LDS)
-    size_t cblk_smem = 0;
+    int cblk_nt = 0;                // most tile rows of an interior operator
     int64_t cblk_ylen = 0;
     BlockItem *d_cblk_items = nullptr;
     int32_t *d_cblk_ones = nullptr;
@@ -847,8 +847,8 @@ constexpr int CBLK = 16;            // right-hand sides condensed per pass over 
 int cblk_setup(bddc_ctx *c) {
     if (c->cblk_state) return 0;
     const int nsub = c->n_sub;
-    c->cblk_smem = symm_smem_bytes(c->max_nI);
-    if (c->cblk_smem > 160 * 1024) { c->cblk_state = -1; return 0; }
+    if (c->max_nI > SYMM_MAX_N) { c->cblk_state = -1; return 0; }
+    for (int n : c->h_nI) c->cblk_nt = std::max(c->cblk_nt, tile_rows(n));
     std::vector<BlockItem> items(nsub);
     std::vector<int32_t> ones(nsub, 1);
     int64_t slot = 0, y = 0;
@@ -876,12 +876,12 @@ int cblk_setup(bddc_ctx *c) {
 // interior tiles, then t_i = K_BI y_I and b per column, into the group buffers.
 int run_condense_block(bddc_ctx *c, const double *F, int g) {
     TScope ts(c, TK_COND);
-    if (set_symm_smem_limit(c->cblk_smem)) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
+    if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     BlockSymvArgs a{};
     a.tiles = c->d_KI; a.items = c->d_cblk_items; a.gB = c->d_nodesI;
     a.X = F; a.ldx = c->n_nodes; a.ncols = g;
     a.ypart = c->d_cblk_y; a.ylen = c->cblk_ylen;
-    launch_symm(a, c->n_sub, c->cblk_smem, c->stream);
+    launch_symm(a, c->n_sub, c->max_nI, c->cblk_nt, c->stream);
     for (int q = 0; q < g; ++q) {
         CondArgs ca{};
         ca.nI = c->d_nI; ca.nB = c->d_nB; ca.i_off = c->d_i_off; ca.b_off = c->d_b_off;
@@ -919,12 +919,12 @@ int run_recover_block(bddc_ctx *c, const double *F, double *u, int g) {
         a.out = c->d_cblk_t + (size_t)q * c->n_nodes;
         launch_rec_rhs(a, c->n_sub, c->max_nB, c->stream);
     }
-    if (set_symm_smem_limit(c->cblk_smem)) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
+    if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     BlockSymvArgs b{};
     b.tiles = c->d_KI; b.items = c->d_cblk_items; b.gB = c->d_nodesI;
     b.X = c->d_cblk_t; b.ldx = c->n_nodes; b.ncols = g;
     b.ypart = c->d_cblk_y; b.ylen = c->cblk_ylen;
-    launch_symm(b, c->n_sub, c->cblk_smem, c->stream);
+    launch_symm(b, c->n_sub, c->max_nI, c->cblk_nt, c->stream);
     for (int q = 0; q < g; ++q) {
         double *uq = u + (size_t)q * c->n_nodes;
         a.ypart = c->d_cblk_y + (size_t)q * c->cblk_ylen; a.u = uq;
@@ -2429,7 +2429,7 @@ struct BlockWork {
            *u2 = nullptr, *c3loc = nullptr, *u3 = nullptr, *r3 = nullptr;
     int64_t i2len = 1, b2len = 1, c3len = 1, n3len = 1, nclen = 1;
     int64_t ylen = 0, clen = 0;
-    size_t smem = 0;
+    int max_nt = 0;                  // most tile rows of a Schur or Neumann operator
     static constexpr int GSZ = 64 * 64, CSZ = 96 * 64;
 };
 
@@ -2484,7 +2484,7 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
     // partial slots that no kernel writes (none with one chunk per subdomain) stay zero
     launch_fill((int64_t)b.ylen * BMAX, 0.0, b.yN, c->stream);
     launch_fill((int64_t)b.clen * BMAX, 0.0, b.cN, c->stream);
-    b.smem = symm_smem_bytes(c->max_nB);
+    for (int n : c->h_nB) b.max_nt = std::max(b.max_nt, tile_rows(n));
     return 0;
 }
 
@@ -2524,7 +2524,7 @@ void block_A(bddc_ctx *c, BlockWork &b, const double *X, int ncols, double *out)
     BlockSymvArgs a{};
     a.tiles = c->d_S; a.items = b.items; a.gB = c->d_gB; a.X = X; a.ldx = c->ld; a.ncols = ncols;
     a.ypart = b.yS; a.ylen = b.ylen;
-    launch_symm(a, c->n_sub, b.smem, c->stream);
+    launch_symm(a, c->n_sub, c->max_nB, b.max_nt, c->stream);
     launch_gather_block(c->n_gamma, c->d_asm_ptr, c->d_asm_idx, b.yS, b.ylen, out, c->ld, ncols, c->stream);
 }
 
@@ -2571,7 +2571,7 @@ void block_M(bddc_ctx *c, BlockWork &b, const double *R, int ncols, double *Z) {
         BlockSymvArgs a{};
         a.tiles = (const double *)c->d_Nx[prec_slot(64)]; a.items = b.items; a.gB = c->d_gB; a.X = R; a.ldx = c->ld;
         a.ncols = ncols; a.ypart = b.yN; a.ylen = b.ylen;
-        launch_symm(a, c->n_sub, b.smem, c->stream);
+        launch_symm(a, c->n_sub, c->max_nB, b.max_nt, c->stream);
     }
     if (c->nC > 0) block_coarse(c, b, R, ncols, c->stream);
     TScope ts(c, TK_VEC);
@@ -2861,7 +2861,7 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
     if (c->nullc) return fail(BDDC_EINVAL, "bddc_adjoint_grad_block: not for the pure Neumann problem");
     if (!(c->prec_built & 1))
         return fail(BDDC_EINVAL, "bddc_adjoint_grad_block: needs the float64 Neumann operators (local_prec 64 or local_prec_set bit 1)");
-    if (symm_smem_bytes(c->max_nB) > 160 * 1024)
+    if (c->max_nB > SYMM_MAX_N)
         return fail(BDDC_EINVAL, "bddc_adjoint_grad_block: a subdomain interface is too large for the block product");
     if (iters) *iters = 0;
     if (n_rhs == 0) {
@@ -2874,7 +2874,7 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
         int rc0;
         if ((rc0 = end_sync_issue(c, false)) || (rc0 = end_sync_wait(c))) return rc0;
     }
-    if (set_symm_smem_limit(symm_smem_bytes(c->max_nB))) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
+    if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     BlockWork b;
     int rc = alloc_block(c, b);
     double *xsave = nullptr;
@@ -2897,10 +2897,8 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
         }
     }
     if (rc) { launch_copy(c->n_gamma, xsave, c->d_x, c->stream); (void)hipStreamSynchronize(c->stream); dfree(c, xsave); free_block(c, b); return rc; }
-    // (set_symm_smem_limit again: the grouped condensation set its own)
-    if (set_symm_smem_limit(symm_smem_bytes(c->max_nB))) rc = fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     int it = 0;
-    if (!rc) rc = block_solve(c, b, n_rhs, rtol, &it);
+    rc = block_solve(c, b, n_rhs, rtol, &it);
     if (iters) *iters = it;
     if (rc == 0 || rc == BDDC_ENOTCONV) {
         for (int g0 = 0; g0 < n_rhs; g0 += CBLK) {

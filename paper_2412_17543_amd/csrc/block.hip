@@ -4,21 +4,30 @@
 // (interior), 16 columns at a time, on the matrix cores, and the assembly of
 // the per-subdomain results.
 //
-// k_symm: one block per (subdomain, 16-column chunk), 4 waves; a wave keeps
-// PF tiles in flight (a fixed ring of load slots, reissued on every step).  The block
-// stages X_i (n x 16) in LDS, then walks the packed upper-triangle tiles one
-// tile row I at a time; inside a row, wave w takes the tiles q = w, w + 4, ...
-// (J = I + q):
-//   row part    Y_I += T X_J          (accumulated in the wave's registers)
-//   column part Y_J += T^T X_I, J > I (added to LDS; each J once per row)
-// After the row the waves' row parts are added into Y_I in wave order, so
-// every entry is summed in a fixed order (the product is reproducible bit by
-// bit).  A short ragged tail stored as a strip after the tiles (uses_strip)
-// follows as one more tile row.  A tile is loaded once (two 16-byte loads
-// per lane, the layout of tile_index), written to the wave's LDS slot in
-// row-major order and read
-// back as MFMA operands: v_mfma_f64_16x16x4f64 takes A[i][k] and B[k][j] in
-// lane i (j) + 16 k and returns (i, j) in lane j + 16 (i % 4), register i / 4.
+// k_symm: one block of 8 waves per (subdomain, 16-column chunk).  Wave w owns
+// the tile columns J = w, w + 8, ... (NJ of them) and keeps their results Y_J
+// in MFMA registers; the block walks the packed upper-triangle tiles one tile
+// row I at a time, each wave its own columns J >= I:
+//   column part Y_J += T^T X_I, J > I  (in the wave's registers: with k-slot g
+//               of step s standing for row 4 g + s, the tile's storage layout,
+//               tile_index, is the operand as loaded)
+//   row part    Y_I += T X_J           (the tile transposed through the wave's
+//               LDS slot; the waves' sums are added in wave order by the wave
+//               that owns column I)
+// so every entry is summed in a fixed order (the product is reproducible bit
+// by bit) and LDS carries one write and one read of a tile, X (staged in
+// operand order) and 8 partial tiles a row.  Each column's next tile, one row
+// down, is requested as soon as the current one is used: NJ tiles in flight a
+// wave, in fixed registers.  A short ragged tail stored as a strip after the
+// tiles (uses_strip) follows as one more tile row.
+// What bounds it: the matrix cores, 8 v_mfma_f64_16x16x4f64 a tile and chunk
+// (about 70 cycles each: 0.21 ms for the 0.46 M tiles of 96^3 and two chunks;
+// the tiles' bytes take 0.15 ms).  Two blocks a compute unit (at most 80 KB of
+// LDS, 128 registers) cover each other's row ends.  Measured at 96^3, 20 columns:
+// 0.83 -> 0.42 ms a product, against 4 waves, X and Y in 126 KB of LDS and both
+// parts read back through it (block adjoint 65.0 -> 47.1 ms).
+// v_mfma_f64_16x16x4f64 takes A[i][k] and B[k][j] in lane i (j) + 16 k and
+// returns (i, j) in lane j + 16 (i % 4), register i / 4.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -31,8 +40,7 @@ namespace {
 typedef double dvec4 __attribute__((ext_vector_type(4)));
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 
-constexpr int XS = 17;              // LDS row stride (doubles) of X, Y and a tile
-constexpr int PF = 8;               // tiles each wave has in flight (one wave per SIMD: registers to spare)
+constexpr int NW = 8;               // waves of a block
 
 // Workgroup barrier that orders LDS only: the tile loads in flight are not
 // waited for (a plain __syncthreads() would drain them at every row end).
@@ -56,185 +64,202 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void *p, int64_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)min(bytes, (int64_t)INT32_MAX), 0x00020000);
 }
 
-// The tiles of one wave in order: rows I = 0, 1, ... and in row I the tiles
-// q = w, w + 4, ... (nt - I of them); `tile` is the index in the
-// subdomain's packed sequence, past the end once the wave has no more.
-struct TileSeq {
-    int I, q, nt, w;
-    int64_t base;
-    __device__ void norm() {
-        while (I < nt && q >= nt - I) { base += nt - I; ++I; q = w; }
-    }
-    __device__ void next() { q += 4; norm(); }
-    __device__ int64_t tile(int64_t total) const { return I < nt ? base + q : total; }
-};
-
-__global__ void __launch_bounds__(256) k_symm(BlockSymvArgs a) {
+// Two blocks per compute unit (4 waves per SIMD) up to NJ = 4.
+template <int NJ>
+__global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs a, int nsub) {
     extern __shared__ __align__(16) double sm[];
-    // the column chunks of one subdomain are adjacent blocks: they run at the
-    // same time, so the second reads the tiles from the shared cache
+    // the column chunks of one subdomain are 8 blocks apart: the same XCD takes
+    // them at the same time, so the second reads the tiles from its L2
     const int nch = (a.ncols + 15) / 16;
-    const BlockItem it = a.items[blockIdx.x / nch];
-    const int c0 = 16 * (int)(blockIdx.x % nch);
+    int sub, chunk;
+    {
+        const int b = blockIdx.x, grp = b / (8 * nch), q = b - grp * 8 * nch, m = min(8, nsub - 8 * grp);
+        sub = 8 * grp + q % m;
+        chunk = q / m;
+    }
+    const BlockItem it = a.items[sub];
+    const int c0 = 16 * chunk;
     const int n = it.n;
     const int nt = tile_rows(n), npad = 16 * ((n + 15) / 16);   // nt: tile rows (without a strip's rows)
     const int64_t total = full_tiles(n);
-    double *xs = sm;                                   // npad x 16 (stride XS)
-    double *ys = xs + (size_t)npad * XS;               // npad x 16
-    double *ts = ys + (size_t)npad * XS;               // 4 tiles of 16 x 16
-    double *red = ts + 4 * 16 * XS;                    // 4 x 256
-    const int tid = threadIdx.x, w = tid >> 6, L = tid & 63, li = L & 15, lk = L >> 4;
-    const int wu = __builtin_amdgcn_readfirstlane(w);
+    double *xs = sm;                                   // X in operand order: [tile][s][lane]
+    double *ts = xs + (size_t)npad * 16;               // per wave one 16 x 16 tile
+    const int tid = threadIdx.x, L = tid & 63, li = L & 15, lk = L >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t *gb = a.gB + it.xoff;
-    // the wave's first PF tiles are requested before anything else
+    // the wave's tiles of row 0, requested before anything else; tile (I, J)
+    // is number S(I) + J of the packed sequence, S(I + 1) = S(I) + nt - I - 1
     const __amdgpu_buffer_rsrc_t rs = raw_rsrc(a.tiles + it.tile * 256, total * 2048);
-    TileSeq ld{0, wu, nt, wu, 0};
-    ld.norm();
-    uvec4 fa[PF], fb[PF];
+    const int end = (int)total * 2048;
+    uvec4 fa[NJ], fb[NJ];
+    auto request = [&](int jj, int I, int S) {         // (past the triangle: zeros, no access)
+        const int J = jj * NW + w;
+        const int off = (J < nt && J >= I ? (S + J) * 2048 : end) + L * 16;
+        fa[jj] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        fb[jj] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 1024, 0, 0);
+    };
 #pragma unroll
-    for (int d = 0; d < PF; ++d) {
-        const int off = (int)ld.tile(total) * 2048 + L * 16;
-        fa[d] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-        fb[d] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 1024, 0, 0);
-        ld.next();
-    }
+    for (int jj = 0; jj < NJ; ++jj) request(jj, 0, 0);
     // X_i: 8 entries per thread at a time, all index loads before the gathers
-    for (int e0 = tid; e0 < 16 * npad; e0 += 256 * 8) {
+    for (int e0 = tid; e0 < 16 * npad; e0 += NW * 64 * 8) {
         int gi[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int e = e0 + 256 * u, cc = e / npad, k = e - cc * npad;
+            const int e = e0 + NW * 64 * u, cc = e / npad, k = e - cc * npad;
             gi[u] = (e < 16 * npad && k < n && c0 + cc < a.ncols) ? gb[k] : -1;
         }
         double v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int e = e0 + 256 * u, cc = e / npad;
+            const int e = e0 + NW * 64 * u, cc = e / npad;
             v[u] = gi[u] >= 0 ? a.X[(int64_t)(c0 + cc) * a.ldx + gi[u]] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int e = e0 + 256 * u, cc = e / npad, k = e - cc * npad;
-            if (e < 16 * npad) xs[k * XS + cc] = v[u];
+            const int e = e0 + NW * 64 * u, cc = e / npad, k = e - cc * npad;
+            if (e < 16 * npad) xs[(k >> 4) * 256 + (k & 3) * 64 + cc + 16 * ((k & 15) >> 2)] = v[u];
         }
     }
-    for (int e = tid; e < npad * XS; e += 256) ys[e] = 0.0;
     __syncthreads();
-    double *tw = ts + w * 16 * XS;
-    dvec4 racc = {0.0, 0.0, 0.0, 0.0};
-    int rows_done = 0;
-    // end of row I: the waves' row parts into Y_I in wave order (every wave
-    // passes here once per row, in row order)
-    auto row_end = [&](int I) {
+    double *tw = ts + w * 256;
+    // entry (r, c) of the transposed tile at 16 p(r) + (c ^ (r & 11)), p swapping
+    // bits 0 and 2: both the writes (lanes c, rows 4 lk + s) and the reads
+    // (lanes r, columns 4 lk + s) touch every bank once
+    const int wb = 16 * (((lk & 2) << 2) | (lk & 1)) + (li ^ ((lk & 2) << 2));
+    const int rb = 16 * ((li & 10) | ((li & 1) << 2) | ((li >> 2) & 1)) + ((4 * lk) ^ (li & 11));
+    auto transpose = [&](const double (&t)[4], double (&u)[4]) {
+        wave_sync();                                   // the previous tile is read
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[w * 256 + (4 * r + lk) * 16 + li] = racc[r];
-        lds_barrier();
-        {
-            const int row = tid >> 4, col = tid & 15;
-            ys[(16 * I + row) * XS + col] += ((red[tid] + red[256 + tid]) + red[512 + tid]) + red[768 + tid];
-        }
-        lds_barrier();
-        racc = dvec4{0.0, 0.0, 0.0, 0.0};
-    };
-    TileSeq cur{0, wu, nt, wu, 0};
-    cur.norm();
-    // one tile from ring slot d, whose load is then reissued for the tile PF
-    // places later (slots are never copied, so no wait but for slot d's own load)
-    auto step = [&](uvec4 &sa, uvec4 &sb) {
-        const bool valid = cur.I < nt;                 // (wave-uniform)
-        const int I = cur.I, J = cur.I + cur.q;
-        if (valid) {
-            while (rows_done < I) row_end(rows_done++);
-            tw[(4 * lk + 0) * XS + li] = __hiloint2double(sa.y, sa.x);
-            tw[(4 * lk + 1) * XS + li] = __hiloint2double(sa.w, sa.z);
-            tw[(4 * lk + 2) * XS + li] = __hiloint2double(sb.y, sb.x);
-            tw[(4 * lk + 3) * XS + li] = __hiloint2double(sb.w, sb.z);
-        }
-        // reissued on every step (past the end: a zero read, no access), so
-        // that the count of loads in flight is the same on every path
-        const int off = (int)ld.tile(total) * 2048 + L * 16;
-        sa = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-        sb = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 1024, 0, 0);
-        ld.next();
-        if (!valid) return;
+        for (int s = 0; s < 4; ++s) tw[(wb ^ s) + 16 * ((s & 2) | ((s & 1) << 2))] = t[s];
         wave_sync();
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            racc = __builtin_amdgcn_mfma_f64_16x16x4f64(tw[li * XS + 4 * s + lk],
-                                                        xs[(16 * J + 4 * s + lk) * XS + li], racc, 0, 0, 0);
-        if (J > I) {
-            dvec4 cacc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                cacc = __builtin_amdgcn_mfma_f64_16x16x4f64(tw[(4 * s + lk) * XS + li],
-                                                            xs[(16 * I + 4 * s + lk) * XS + li], cacc, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ys[(16 * J + 4 * r + lk) * XS + li] += cacc[r];
-        }
-        wave_sync();
-        cur.next();
+        for (int s = 0; s < 4; ++s) u[s] = tw[rb ^ s];
     };
-    while (cur.I < nt) {
+    const dvec4 zero = {0.0, 0.0, 0.0, 0.0};
+    dvec4 yacc[NJ], racc = zero;
 #pragma unroll
-        for (int d = 0; d < PF; ++d) step(fa[d], fb[d]);
+    for (int jj = 0; jj < NJ; ++jj) yacc[jj] = zero;
+    // the waves' row parts, in wave order, in the registers of wave `owner`
+    auto row_sum = [&](int owner, dvec4 &y) {
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tw[r * 64 + L] = racc[r];
+        lds_barrier();
+        if (w == owner) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double v = ts[r * 64 + L];
+#pragma unroll
+                for (int q = 1; q < NW; ++q) v += ts[q * 256 + r * 64 + L];
+                y[r] += v;
+            }
+        }
+        lds_barrier();
+        racc = zero;
+    };
+    int S = 0;
+#pragma unroll
+    for (int ib = 0; ib < NJ; ++ib) {
+        for (int wi = 0; wi < NW; ++wi) {
+            const int I = ib * NW + wi;
+            if (I >= nt) break;
+            double xi[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) xi[s] = xs[I * 256 + s * 64 + L];
+            const int Sn = S + nt - I - 1;
+#pragma unroll
+            for (int jj = ib; jj < NJ; ++jj) {
+                const int J = jj * NW + w;
+                const bool live = J < nt && J >= I;    // (wave-uniform)
+                double t[4] = {__hiloint2double(fa[jj].y, fa[jj].x), __hiloint2double(fa[jj].w, fa[jj].z),
+                               __hiloint2double(fb[jj].y, fb[jj].x), __hiloint2double(fb[jj].w, fb[jj].z)};
+                double u[4];
+                if (live) {
+                    transpose(t, u);
+                    if (J > I) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            yacc[jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[s], xi[s], yacc[jj], 0, 0, 0);
+                    }
+                }
+                // on every path, so that the number of loads in flight is known
+                request(jj, I + 1, Sn);
+                if (live) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        racc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s], xs[J * 256 + s * 64 + L], racc, 0, 0, 0);
+                }
+            }
+            row_sum(wi, yacc[ib]);
+            S = Sn;
+        }
     }
-    while (rows_done < nt) row_end(rows_done++);
     // loads issued past the wave's last tile read nothing; make sure none is
     // outstanding at exit
 #pragma unroll
-    for (int d = 0; d < PF; ++d) asm volatile("" ::"v"(fa[d]), "v"(fb[d]));
+    for (int d = 0; d < NJ; ++d) asm volatile("" ::"v"(fa[d]), "v"(fb[d]));
     // The ragged tail rows n0 + r, r < rem, stored whole as a row-major strip
     // after the tiles: one more tile row, whose 16-column chunks are the
-    // chunks q < nt (row part and column part, as for a tile) and the corner
-    // q = nt (the full rem x rem block: row part only).  Wave w takes the
-    // chunks q = w, w + 4, ...; a chunk's rows of Y belong to that wave alone.
+    // chunks q < nt (row part and column part, as for a tile, by the wave that
+    // owns column q) and the corner (the full rem x rem block: row part only,
+    // wave nt % 8).
     const int rem = uses_strip(n) ? n % 16 : 0;
+    dvec4 yrag = zero;
     if (rem > 0) {
-        const int n0 = 16 * nt, nq = nt + 1;
+        const int n0 = 16 * nt;
         const double *sp = a.tiles + (it.tile + total) * 256;
-        constexpr int G = 4;        // chunks whose entries are requested together
-        for (int q0 = wu; q0 < nq; q0 += 4 * G) {
-            double v[G][4];
+        constexpr int G = 2;        // chunks whose entries are requested together
+        double xr[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) xr[s] = xs[nt * 256 + s * 64 + L];
+#pragma unroll
+        for (int j0 = 0; j0 <= NJ; j0 += G) {
+            double v[G][4], u[4];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int q = q0 + 4 * g;
-                const int cb = q < nt ? 16 * q : n0;
-                const int cv = q < nt ? 16 : rem;
+                const int jj = j0 + g, q = jj < NJ ? jj * NW + w : nt;
+                const int cv = jj < NJ ? (q < nt ? 16 : 0) : jj == NJ && w == nt % NW ? rem : 0;
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const int r = 4 * lk + s;
-                    v[g][s] = (q < nq && r < rem && li < cv) ? sp[(int64_t)r * n + cb + li] : 0.0;
+                    v[g][s] = (r < rem && li < cv) ? sp[(int64_t)r * n + 16 * q + li] : 0.0;
                 }
             }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int q = q0 + 4 * g;
-                if (q >= nq) break;                        // (wave-uniform)
+                const int jj = j0 + g, q = jj < NJ ? jj * NW + w : nt;
+                if (jj < NJ ? q < nt : jj == NJ && w == nt % NW) {     // (wave-uniform)
+                    transpose(v[g], u);
+                    if (jj < NJ) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) tw[(4 * lk + s) * XS + li] = v[g][s];
-                wave_sync();
-                // row part: Y_rag += T X_q (the corner: X rows n0..)
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    racc = __builtin_amdgcn_mfma_f64_16x16x4f64(tw[li * XS + 4 * s + lk],
-                                                                xs[(16 * q + 4 * s + lk) * XS + li], racc, 0, 0, 0);
-                if (q != nt) {          // column part: Y_q += T^T X_rag
-                    dvec4 cacc = {0.0, 0.0, 0.0, 0.0};
+                        for (int s = 0; s < 4; ++s)
+                            yacc[jj < NJ ? jj : 0] =
+                                __builtin_amdgcn_mfma_f64_16x16x4f64(v[g][s], xr[s], yacc[jj < NJ ? jj : 0], 0, 0, 0);
+                    }
 #pragma unroll
                     for (int s = 0; s < 4; ++s)
-                        cacc = __builtin_amdgcn_mfma_f64_16x16x4f64(tw[(4 * s + lk) * XS + li],
-                                                                    xs[(n0 + 4 * s + lk) * XS + li], cacc, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) ys[(16 * q + 4 * r + lk) * XS + li] += cacc[r];
+                        racc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s], xs[q * 256 + s * 64 + L], racc, 0, 0, 0);
                 }
-                wave_sync();
             }
         }
-        row_end(nt);                // the waves' row parts into Y rows n0.. in wave order
+        row_sum(0, yrag);
     }
-    for (int e = tid; e < 16 * n; e += 256) {
+    // Y through LDS ([column][row], odd stride, over X and the tiles' slots),
+    // so that it is written in whole lines
+    __syncthreads();
+    const int ldy = npad + 1;
+    auto put = [&](int J, const dvec4 &y) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sm[li * ldy + 16 * J + 4 * r + lk] = y[r];
+    };
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+        if (jj * NW + w < nt) put(jj * NW + w, yacc[jj]);
+    if (rem > 0 && w == 0) put(nt, yrag);
+    __syncthreads();
+    for (int e = tid; e < 16 * n; e += NW * 64) {
         const int cc = e / n, k = e - cc * n, col = c0 + cc;
-        if (col < a.ncols) a.ypart[(int64_t)col * a.ylen + it.xoff + k] = ys[k * XS + cc];
+        if (col < a.ncols) a.ypart[(int64_t)col * a.ylen + it.xoff + k] = sm[cc * ldy + k];
     }
 }
 
@@ -255,21 +280,24 @@ __global__ void __launch_bounds__(256) k_gather_block(int n, const int32_t *ptr,
 
 }  // namespace
 
-size_t symm_smem_bytes(int max_n) {
-    const int npad = 16 * ((max_n + 15) / 16);
-    return sizeof(double) * ((size_t)2 * npad * XS + 4 * 16 * XS + 4 * 256);
+static size_t symm_smem(int max_n) { return sizeof(double) * ((size_t)16 * 16 * ((max_n + 15) / 16) + NW * 256); }
+
+int set_symm_smem_limit() {
+    const void *f[3] = {(const void *)k_symm<3>, (const void *)k_symm<4>, (const void *)k_symm<5>};
+    for (const void *p : f)
+        if (hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)symm_smem(SYMM_MAX_N)) != hipSuccess)
+            return 1;
+    return 0;
 }
 
-int set_symm_smem_limit(size_t bytes) {
-    return hipFuncSetAttribute((const void *)k_symm, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) !=
-                   hipSuccess
-               ? 1
-               : 0;
-}
-
-void launch_symm(const BlockSymvArgs &a, int nsub, size_t smem, hipStream_t s) {
+// max_n: the largest subdomain size, max_nt: the most tile rows of one
+void launch_symm(const BlockSymvArgs &a, int nsub, int max_n, int max_nt, hipStream_t s) {
     if (nsub <= 0 || a.ncols <= 0) return;
-    hipLaunchKernelGGL(k_symm, dim3(nsub * ((a.ncols + 15) / 16)), dim3(256), smem, s, a);
+    const dim3 grid(nsub * ((a.ncols + 15) / 16)), block(NW * 64);
+    const size_t smem = symm_smem(max_n);
+    if (max_nt <= 3 * NW) hipLaunchKernelGGL(k_symm<3>, grid, block, smem, s, a, nsub);
+    else if (max_nt <= 4 * NW) hipLaunchKernelGGL(k_symm<4>, grid, block, smem, s, a, nsub);
+    else hipLaunchKernelGGL(k_symm<5>, grid, block, smem, s, a, nsub);
 }
 
 void launch_gather_block(int n, const int32_t *ptr, const int32_t *idx, const double *part, int64_t plen, double *out,

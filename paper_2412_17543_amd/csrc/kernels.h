@@ -377,9 +377,9 @@ struct BlockSymvArgs {
     const double *X; int64_t ldx; int ncols;   // input block, column-major
     double *ypart; int64_t ylen;    // y of subdomain i, column c: ypart[c ylen + xoff_i + k]
 };
-size_t symm_smem_bytes(int max_n);
-int set_symm_smem_limit(size_t bytes);
-void launch_symm(const BlockSymvArgs &a, int nsub, size_t smem, hipStream_t s);
+constexpr int SYMM_MAX_N = 528;     // rows of a subdomain in a block product
+int set_symm_smem_limit();
+void launch_symm(const BlockSymvArgs &a, int nsub, int max_n, int max_nt, hipStream_t s);
 void launch_gather_block(int n, const int32_t *ptr, const int32_t *idx, const double *part, int64_t plen, double *out,
                          int64_t ldo, int ncols, hipStream_t s);
 void launch_elem_grad(const GradArgs &a, hipStream_t s);
