@@ -2052,7 +2052,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         launch_pack(dps, nsub, 64, c->d_S, nullptr, s);
         for (int p : {64, 32, 16})   // each storage precision from the same float64 solves
             if ((c->prec_built >> prec_slot(p)) & 1) launch_pack(dpn, nsub, p, c->d_Nx[prec_slot(p)], c->d_phirx[prec_slot(p)], s);
-        launch_ptsp(dpt, nsub, s);
+        launch_ptsp(dpt, nsub, c->max_nB, c->max_nc, s);
         HIPCHK(hipStreamSynchronize(s));
         dfree(c, dsd); dfree(c, dps); dfree(c, dpn); dfree(c, dpt);
     }
@@ -2226,7 +2226,11 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             if ((rc = run_sweeps(c, s2))) return rc;
             launch_dense_copy(dcn, nsr, s);
             launch_dense_copy(dcp, nsr, s);
-            launch_ptsp(dpt, nsr, s);
+            {
+                int mb = 0, mc = 0;
+                for (int j = 0; j < nsr; ++j) { mb = std::max(mb, nL[j] - nI2[j]); mc = std::max(mc, nc3[j]); }
+                launch_ptsp(dpt, nsr, mb, mc, s);
+            }
             HIPCHK(hipStreamSynchronize(s));
             dfree(c, dsd); dfree(c, dcn); dfree(c, dcp); dfree(c, dpt);
         }

@@ -351,7 +351,7 @@ int launch_face_schur(const FaceSchurDesc *d, const std::vector<FaceSchurDesc> &
                       hipStream_t s);
 void launch_build_saddle(const SaddleDesc *d, int n, hipStream_t s);
 void launch_pack(const PackDesc *d, int n, int prec, void *dst, void *phir, hipStream_t s);
-void launch_ptsp(const PtspDesc *d, int n, hipStream_t s);
+void launch_ptsp(const PtspDesc *d, int n, int max_n, int max_nc, hipStream_t s);   // sizes: the largest of the batch
 void launch_dense_copy(const DenseCopyDesc *d, int n, hipStream_t s);
 void launch_pad_rows(const double *src, int n, bool trans, double *dst, int64_t ldm, hipStream_t s);
 void launch_gather_sum(int64_t n, const int32_t *ptr, const int32_t *idx, const double *src, double *out, hipStream_t s);

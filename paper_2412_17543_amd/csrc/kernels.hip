@@ -262,25 +262,90 @@ __global__ void __launch_bounds__(256) k_pack_symblk(const double *M, int64_t ld
 }
 
 // ---------------------------------------------------------------------------
-// setup: K_C = Phi^T S Phi (coarse element matrices, eq. coarse_problem)
+// setup: K_C = Phi^T S Phi (coarse element matrices, eq. coarse_problem) on
+// the matrix cores (operand layout as below, at the recycling products).
+// k_ptsp_x: X = S Phi; a wave takes 16 rows of one subdomain and 16 NT columns,
+// reading S by its columns (symmetric: 16 consecutive entries a load).
+// k_ptsp_out: 16 x 16 tiles (ta, tb >= ta) of Phi^T X; the block's waves split
+// the n rows and are added in wave order; the upper triangle is mirrored.
+// (One block per subdomain with a thread per entry of X took 84 ms on the
+// holed 64^3 cube, where the largest subdomain has 1,302 rows, 3.0 ms at 64^3
+// and 32 ms at 192^3; these two take 0.6, 0.2 and 6.6 ms.)
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_ptsp(const PtspDesc *descs) {
+typedef double dvec4 __attribute__((ext_vector_type(4)));
+
+template <int NT>
+__global__ void __launch_bounds__(256) k_ptsp_x(const PtspDesc *descs) {
     const PtspDesc d = descs[blockIdx.x];
-    for (int64_t t = threadIdx.x; t < (int64_t)d.n * d.nc; t += blockDim.x) {
-        const int i = (int)(t / d.nc), a = (int)(t - (int64_t)i * d.nc);
-        double s = 0.0;
-        for (int j = 0; j < d.n; ++j) s += d.S[(size_t)i * d.ldS + j] * d.Phi[(size_t)j * d.ldPhi + a];
-        d.X[t] = d.phisign * s;
+    const int w = threadIdx.x >> 6, L = threadIdx.x & 63, li = L & 15, lk = L >> 4;
+    const int i0 = (blockIdx.y * 4 + w) * 16;
+    if (i0 >= d.n) return;                           // (the whole wave)
+    const bool iok = i0 + li < d.n;
+    constexpr int G = 4;                             // steps of 4 rows whose operands are requested together
+    for (int a0 = 0; a0 < d.nc; a0 += 16 * NT) {
+        dvec4 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = dvec4{0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 0; k0 < d.n; k0 += 4 * G) {
+            double av[G], bv[G][NT];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int k = k0 + 4 * g + lk;
+                av[g] = iok && k < d.n ? d.S[(size_t)k * d.ldS + i0 + li] : 0.0;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    bv[g][t] = k < d.n && a0 + 16 * t + li < d.nc ? d.Phi[(size_t)k * d.ldPhi + a0 + 16 * t + li] : 0.0;
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g], bv[g][t], acc[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = i0 + lk + 4 * r, a = a0 + 16 * t + li;
+                if (i < d.n && a < d.nc) d.X[(size_t)i * d.nc + a] = d.phisign * acc[t][r];
+            }
     }
-    __syncthreads();
-    for (int t = threadIdx.x; t < d.nc * d.nc; t += blockDim.x) {
-        const int a = t / d.nc, b = t - a * d.nc;
-        if (b < a) continue;
-        double s = 0.0;
-        for (int i = 0; i < d.n; ++i) s += d.Phi[(size_t)i * d.ldPhi + a] * d.X[(size_t)i * d.nc + b];
-        s *= d.phisign;
-        d.out[a * d.nc + b] = s;
-        d.out[b * d.nc + a] = s;
+}
+
+__global__ void __launch_bounds__(256) k_ptsp_out(const PtspDesc *descs) {
+    __shared__ double red[4][256];
+    const PtspDesc d = descs[blockIdx.x];
+    const int T = (d.nc + 15) / 16;
+    const int w = threadIdx.x >> 6, L = threadIdx.x & 63, li = L & 15, lk = L >> 4;
+    constexpr int G = 8;
+    const int per = ((d.n + 3) / 4 + 3) / 4 * 4;     // rows of a wave, whole steps
+    const int k1 = min(d.n, (w + 1) * per);
+    for (int tt = blockIdx.y; tt < T * T; tt += gridDim.y) {
+        const int ta = tt / T, tb = tt - ta * T;
+        if (tb < ta) continue;                       // (block-uniform)
+        dvec4 acc = {0.0, 0.0, 0.0, 0.0};
+        const bool aok = 16 * ta + li < d.nc, bok = 16 * tb + li < d.nc;
+        for (int k0 = w * per; k0 < k1; k0 += 4 * G) {
+            double av[G], bv[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int k = k0 + 4 * g + lk;
+                av[g] = aok && k < k1 ? d.Phi[(size_t)k * d.ldPhi + 16 * ta + li] : 0.0;
+                bv[g] = bok && k < k1 ? d.X[(size_t)k * d.nc + 16 * tb + li] : 0.0;
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g], bv[g], acc, 0, 0, 0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[w][(lk + 4 * r) * 16 + li] = acc[r];
+        __syncthreads();
+        const int e = threadIdx.x, a = 16 * ta + (e >> 4), b = 16 * tb + (e & 15);
+        if (a < d.nc && b < d.nc && b >= a) {
+            const double s = d.phisign * (((red[0][e] + red[1][e]) + red[2][e]) + red[3][e]);
+            d.out[(size_t)a * d.nc + b] = s;
+            d.out[(size_t)b * d.nc + a] = s;
+        }
     }
 }
 
@@ -408,8 +473,6 @@ __global__ void __launch_bounds__(256) k_scatter_gamma(int n, const int32_t *gam
 // operand entries of Y (a few KB, read through the cache), and each result
 // register holds 16 consecutive rows of one output column.
 // ---------------------------------------------------------------------------
-typedef double dvec4 __attribute__((ext_vector_type(4)));
-
 template <int NT>
 __global__ void __launch_bounds__(256) k_recycle_gemm(GemmArgs a) {
     const int y = blockIdx.y;
@@ -743,8 +806,13 @@ void launch_pack_symblk(const double *M, int64_t ldm, int n, int nb, const int32
                         hipStream_t s) {
     if (nb > 0) hipLaunchKernelGGL(k_pack_symblk, dim3(nb * (nb + 1) / 2), dim3(256), 0, s, M, ldm, n, nb, bI, sign, B);
 }
-void launch_ptsp(const PtspDesc *d, int n, hipStream_t s) {
-    hipLaunchKernelGGL(k_ptsp, dim3(n), dim3(256), 0, s, d);
+void launch_ptsp(const PtspDesc *d, int n, int max_n, int max_nc, hipStream_t s) {
+    if (n <= 0 || max_nc <= 0) return;
+    const dim3 gx(n, nblk(max_n, 64));
+    if (max_nc <= 32) hipLaunchKernelGGL(k_ptsp_x<2>, gx, dim3(256), 0, s, d);
+    else hipLaunchKernelGGL(k_ptsp_x<4>, gx, dim3(256), 0, s, d);
+    const unsigned T = nblk(max_nc, 16);
+    hipLaunchKernelGGL(k_ptsp_out, dim3(n, std::min(T * T, 64u)), dim3(256), 0, s, d);
 }
 void launch_dense_copy(const DenseCopyDesc *d, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_dense_copy, dim3(n), dim3(256), 0, s, d);
