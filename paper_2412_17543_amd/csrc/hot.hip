@@ -120,38 +120,16 @@ struct Frag<uint16_t> {
     }
 };
 
-// Cross-lane moves without LDS: DPP within rows of 16 lanes, and the gfx950
-// row-swap permutes across rows.  Every lane of the wave must be active.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-constexpr int DPP_XOR1 = 0xB1;      // quad_perm [1,0,3,2]
-constexpr int DPP_XOR2 = 0x4E;      // quad_perm [2,3,0,1]
-constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <-> i ^ 7 within 8 lanes
-constexpr int DPP_ROR8 = 0x128;     // lane i <-> i ^ 8 within 16 lanes
+using dev::DPP_HALF_MIRROR;
+using dev::DPP_ROR4;
+using dev::DPP_ROR8;
+using dev::DPP_XOR1;
+using dev::DPP_XOR2;
+using dev::dpp;
 
-// v + v[l ^ 16] and then + [l ^ 32]: the sum over the four lanes l % 16 + 16 g.
-__device__ __forceinline__ float col_sum4(float v) {
-    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
-__device__ __forceinline__ double col_sum4(double v) {
-    auto pl = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    auto ph = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = __hiloint2double(ph[0], pl[0]) + __hiloint2double(ph[1], pl[1]);
-    auto ql = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    auto qh = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    return __hiloint2double(qh[0], ql[0]) + __hiloint2double(qh[1], ql[1]);
-}
+// the sum over the four lanes l % 16 + 16 g
+template <typename T>
+__device__ __forceinline__ T col_sum4(T v) { return dev::add_xor32(dev::add_xor16(v)); }
 
 // Sums of ra[0..3] over the 16 lanes of a row of the wave, by exchange:
 // lanes with bit 3 set keep rows 2, 3 and pass rows 0, 1 to lane ^ 8 (and
@@ -292,6 +270,25 @@ __device__ bool block_done(const Ctl *c) {
     if (threadIdx.x == 0) s_done = c->done;
     __syncthreads();
     return s_done != 0;
+}
+
+// y = M x with M (k x k row-major), x and y in LDS, k <= RMAX, by a block of
+// 256 threads: 16 lanes a row, lane c taking the columns c, c + 16, ... (one
+// thread a row is a chain of k LDS reads and adds, 20 of them 1 us).  No
+// barrier at the end.
+__device__ __forceinline__ void small_matvec(const double *M, int k, const double *x, double *y) {
+    const int c = threadIdx.x & 15;
+    for (int r0 = 0; r0 < k; r0 += 16) {               // (block-uniform: every lane takes part in the sum)
+        const int r = r0 + (threadIdx.x >> 4);
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < RMAX / 16; ++u) {
+            const int q = c + 16 * u;
+            if (r < k && q < k) s += M[r * k + q] * x[q];
+        }
+        s = dev::row16_sum(s);
+        if (c == 0 && r < k) y[r] = s;
+    }
 }
 
 // y_r = sum_{q < ncol} M[q * ldm + r] x[q] for r in [r0, r1) (M read column
@@ -966,11 +963,7 @@ __global__ void __launch_bounds__(256) k_pupd(PupdArgs a) {
         block_sum_cols<KM + 1>(acc, k + 1, lds, tv);
     }
     // (block_sum_cols ends with a barrier: wawi is complete)
-    if (threadIdx.x < k) {
-        double s = 0.0;
-        for (int q = 0; q < k; ++q) s += wawi[threadIdx.x * k + q] * tv[1 + q];
-        mu[threadIdx.x] = s;
-    }
+    small_matvec(wawi, k, tv + 1, mu);
     __syncthreads();
     const double rho = tv[0];
     const double beta = a.first ? 0.0 : rho / a.rho_hist[j - 1];
@@ -1059,11 +1052,7 @@ __global__ void __launch_bounds__(256) k_defl_init(DeflArgs a) {
     }
     for (int e = threadIdx.x; e < k * k; e += blockDim.x) lds[e] = a.WAWinv[e];
     __syncthreads();
-    if (threadIdx.x < k) {
-        double s = 0.0;
-        for (int q = 0; q < k; ++q) s += lds[threadIdx.x * k + q] * tv[1 + q];
-        gam[threadIdx.x] = s;
-    }
+    small_matvec(lds, k, tv + 1, gam);
     __syncthreads();
     double rr = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -1243,7 +1232,6 @@ __global__ void __launch_bounds__(ROWS * 64) k_coarse_dense(CoarseDenseArgs a) {
 // row part B x_J is summed over the quad of the row; for J > I the column
 // part B^T x_I over the 16 rows of the wave (row rotations within 16 lanes,
 // then the row-swap permutes) and the 4 waves in order.
-constexpr int DPP_ROR4 = 0x124;     // row_ror:4 within 16 lanes
 __device__ __forceinline__ int symblk_start(int I, int nb) { return I * nb - I * (I - 1) / 2; }
 
 __global__ void __launch_bounds__(256) k_symblk(SymBlkArgs a) {
