@@ -127,7 +127,7 @@ struct bddc_ctx {
     // coarse
     bool three = false;
     double *d_KCinv = nullptr, *d_uC = nullptr;
-    int nsr = 0, n3 = 0, max_nL = 0, ld3 = 0;
+    int nsr = 0, n3 = 0, max_nL = 0, nB2 = 0, ld3 = 0;
     int32_t *d_nL = nullptr, *d_nI2 = nullptr, *d_L_off = nullptr, *d_L = nullptr, *d_I2_off = nullptr,
             *d_B2_off = nullptr, *d_g2 = nullptr, *d_asm2_ptr = nullptr, *d_asm2_idx = nullptr,
             *d_pos_sr = nullptr, *d_nc3 = nullptr, *d_C3_off = nullptr, *d_c3 = nullptr,
@@ -546,7 +546,7 @@ L2Args l2_args(const bddc_ctx *c, const Gather &rc) {
     l.P2_off = c->d_P2_off; l.Phi2 = c->d_Phi2; l.nc3 = c->d_nc3; l.C3_off = c->d_C3_off; l.c3 = c->d_c3;
     l.u2 = c->d_u2; l.c3loc = c->d_c3loc; l.pos_sr = c->d_pos_sr; l.own2 = c->d_own2; l.u3 = c->d_u3;
     l.uC = c->d_uC;
-    l.ph_off = c->d_ph_off2; l.c3o = c->d_c3o; l.n3p = c->d_n3p; l.n3 = c->n3; l.max_nL = c->max_nL;
+    l.ph_off = c->d_ph_off2; l.c3o = c->d_c3o; l.n3p = c->d_n3p; l.n3 = c->n3; l.max_nL = c->max_nL; l.nB2 = c->nB2;
     return l;
 }
 
@@ -2126,6 +2126,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             c->max_nL = std::max(c->max_nL, nL[j]);
         }
         if ((size_t)c->max_nL * 8 > 65536) return fail(BDDC_EINVAL, "a subregion has too many coarse DOFs");
+        c->nB2 = B2_off[nsr];
         {
             // per level-2 interface position: its D Phi row and level-3 DOF list
             std::vector<int64_t> ph_off2(B2_off[nsr]);
@@ -2141,7 +2142,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
                 (rc = dupload(c, &c->d_n3p, n3p)))
                 return rc;
             c->smem_l2d = l2_d_smem(c->max_nL);
-            if (set_l2_d_smem_limit(c->smem_l2d)) return fail(BDDC_EHIP, "hipFuncSetAttribute (dynamic LDS) failed");
+            if (set_l2_smem_limit(c->smem_l2d)) return fail(BDDC_EHIP, "hipFuncSetAttribute (dynamic LDS) failed");
         }
         if ((rc = dupload(c, &c->d_nL, nL)) || (rc = dupload(c, &c->d_nI2, nI2)) || (rc = dupload(c, &c->d_nc3, nc3)) ||
             (rc = dupload(c, &c->d_L_off, L_off)) || (rc = dupload(c, &c->d_I2_off, I2_off)) ||

@@ -10,7 +10,7 @@
 //                coarse residual partials c_i = (D Phi_i)^T r_i
 //   coarse       k_coarse_dense (two levels, or three levels in explicit form);
 //                three levels as a chain: k_l2_a, k_l2_b, level 3 by the
-//                dense product, k_l2_d
+//                dense product, k_l2_c, k_l2_d
 //   k_prolong    w_i = u_i + D Phi_i u_C            eq. averaging_subdomain_solves
 //   k_zasm       z = sum_i R_i^T w_i, r^T z, (AW)^T z   line 13
 //   k_pupd       beta, mu, p = z + beta p - W mu    lines 14-16
@@ -293,27 +293,30 @@ __device__ __forceinline__ void small_matvec(const double *M, int k, const doubl
 
 // y_r = sum_{q < ncol} M[q * ldm + r] x[q] for r in [r0, r1) (M read column
 // by column, i.e. the transposed access of a row-major symmetric matrix, so
-// consecutive lanes read consecutive addresses).  The NW waves of the block
-// split the columns; lanes take the rows; partial sums are added in wave
-// order by wave 0, which calls store(r, y_r).  x is in LDS.
+// consecutive lanes read consecutive addresses).  Lanes take 64 rows; the NW
+// waves take as many row blocks as there are (up to NW) and split the columns
+// of each among the waves left over (these are chains of loads: more waves,
+// fewer round trips); partial sums are added in wave order by the first wave
+// of a row block, which calls store(r, y_r).  x is in LDS.
 template <int NW, typename F>
 __device__ __forceinline__ void cm_matvec(const double *M, int64_t ldm, int r0, int r1, int ncol, const double *x,
                                           double (*part)[64], F store) {
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int q0 = (int)((int64_t)ncol * w / NW), q1 = (int)((int64_t)ncol * (w + 1) / NW);
-    for (int rb = r0; rb < r1; rb += 64) {
-        const int r = rb + l;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int nrb = (r1 - r0 + 63) / 64, G = max(1, min(nrb, NW)), P = NW / G, g = w / P, pt = w - g * P;
+    const int q0 = (int)((int64_t)ncol * pt / P), q1 = (int)((int64_t)ncol * (pt + 1) / P);
+    for (int b0 = 0; b0 < nrb; b0 += G) {
+        const int r = r0 + 64 * (b0 + g) + l;
+        const bool live = g < G && r < r1;
         double s = 0.0;
-        if (r < r1) {
+        if (live) {
 #pragma unroll 8
             for (int q = q0; q < q1; ++q) s += M[(int64_t)q * ldm + r] * x[q];
         }
         part[w][l] = s;
         __syncthreads();
-        if (w == 0 && r < r1) {
+        if (live && pt == 0) {
             double t = 0.0;
-#pragma unroll
-            for (int q = 0; q < NW; ++q) t += part[q][l];
+            for (int q = 0; q < P; ++q) t += part[w + q][l];
             store(r, t);
         }
         __syncthreads();
@@ -1319,12 +1322,19 @@ __device__ __forceinline__ void l2_cols(L2Args &a) {
     a.uC += col * a.cs_uC;
 }
 
+// Waves of a level-2 block: 16 where one block per compute unit takes all
+// (a launch then lasts as long as one block's chain of loads: 125 subregions,
+// a 9.0 -> 7.9, b 10.9 -> 9.4 us), 4 where the blocks queue (1,728 subregions: b
+// 19 us with 4 waves, 62 with 16).
+constexpr int L2_ONE_ROUND = 256;
+
 // Level 2, phase A (one block per subregion): the subregion's coarse
 // residual r_L, interior pre-solve v_I = K_II^{-1} r_I and its interface
 // coupling t = K_BI K_II^{-1} r_I (from the swept subregion matrix).
-__global__ void __launch_bounds__(256) k_l2_a(L2Args a) {
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) k_l2_a(L2Args a) {
     extern __shared__ double rL[];
-    __shared__ double part[4][64];
+    __shared__ double part[NW][64];
     if (a.ctl->done) return;
     l2_cols(a);
     const int j = blockIdx.x;
@@ -1333,7 +1343,7 @@ __global__ void __launch_bounds__(256) k_l2_a(L2Args a) {
     for (int q = threadIdx.x; q < nL; q += blockDim.x) rL[q] = gather_sum(a.rc, a.L[loff + q]);
     __syncthreads();
     double *vI2 = a.vI2 + a.I2_off[j], *t2 = a.t2 + a.B2_off[j], *rB2 = a.rB2 + a.B2_off[j];
-    cm_matvec<4>(a.K2 + a.K2_off[j], nL, 0, nL, nI, rL, part, [&](int q, double y) {
+    cm_matvec<NW>(a.K2 + a.K2_off[j], nL, 0, nL, nI, rL, part, [&](int q, double y) {
         if (q < nI) vI2[q] = -y;
         else { t2[q - nI] = y; rB2[q - nI] = rL[q]; }
     });
@@ -1341,9 +1351,10 @@ __global__ void __launch_bounds__(256) k_l2_a(L2Args a) {
 
 // Level 2, phase B (one block per subregion): level-2 interface residual
 // g = r_G - sum_j R_j^T t_j, then u = (D N D) g and c3 = (D Phi)^T g.
-__global__ void __launch_bounds__(256) k_l2_b(L2Args a) {
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) k_l2_b(L2Args a) {
     extern __shared__ double gs[];
-    __shared__ double part[4][64];
+    __shared__ double part[NW][64];
     if (a.ctl->done) return;
     l2_cols(a);
     const int j = blockIdx.x;
@@ -1351,25 +1362,50 @@ __global__ void __launch_bounds__(256) k_l2_b(L2Args a) {
     const int b2 = a.B2_off[j];
     for (int k = threadIdx.x; k < nB; k += blockDim.x) {
         const int gi = a.g2[b2 + k];
-        double s = a.rB2[b2 + k];
-        for (int t = a.asm2_ptr[gi]; t < a.asm2_ptr[gi + 1]; ++t) s -= a.t2[a.asm2_idx[t]];
-        gs[k] = s;
+        const double r = a.rB2[b2 + k];
+        gs[k] = r - gather_range<4>(a.asm2_idx, a.t2, a.asm2_ptr[gi], a.asm2_ptr[gi + 1], 0.0);
     }
     __syncthreads();
     double *u2 = a.u2 + b2, *c3 = a.c3loc + a.C3_off[j];
-    cm_matvec<4>(a.N2 + a.N2_off[j], nB, 0, nB, nB, gs, part, [&](int k, double y) { u2[k] = y; });
-    cm_matvec<4>(a.Phi2 + a.P2_off[j], a.nc3[j], 0, a.nc3[j], nB, gs, part, [&](int q, double y) { c3[q] = y; });
+    cm_matvec<NW>(a.N2 + a.N2_off[j], nB, 0, nB, nB, gs, part, [&](int k, double y) { u2[k] = y; });
+    cm_matvec<NW>(a.Phi2 + a.P2_off[j], a.nc3[j], 0, a.nc3[j], nB, gs, part, [&](int q, double y) { c3[q] = y; });
+}
+
+// Level 2, phase C: u_j + (D Phi_j) u3 at every interface position of every
+// subregion, 16 lanes a position (each position once: phase D needs it in
+// every subregion that shares the DOF, and summed it there as a chain of a
+// dozen round trips).
+__global__ void __launch_bounds__(256) k_l2_c(L2Args a) {
+    if (a.ctl->done) return;
+    l2_cols(a);
+    const int pos = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 4), c = threadIdx.x & 15;
+    const bool live = pos < a.nB2;
+    double v = 0.0, u = 0.0;
+    if (live) {
+        const double *ph = a.Phi2 + a.ph_off[pos];
+        const int32_t *c3 = a.c3 + a.c3o[pos];
+        const int n3j = a.n3p[pos];
+        u = a.u2[pos];
+#pragma unroll 4
+        for (int q = c; q < n3j; q += 16) v += ph[q] * a.u3[c3[q]];
+    }
+    v = dev::row16_sum(v);
+    if (live && c == 0) a.u2[pos] = u + v;
 }
 
 // Level 2, phase D (one block per subregion): level-2 interface solution
-// x_G = sum_j R_j^T (u_j + (D Phi_j) u3) on the subregion's interface and the
-// interior post-correction x_I = v_I - T^T x_G give the level-1 coarse
-// solution u_C on the coarse DOFs of the subregion (every subregion sharing
-// an interface DOF computes the same value in the same order; its owner
-// writes it) for the prolongation, k_prolong.
-__global__ void __launch_bounds__(256) k_l2_d(L2Args a) {
+// x_G = sum_j R_j^T (u_j + (D Phi_j) u3) on the subregion's interface (from
+// phase C) and the interior post-correction x_I = v_I - T^T x_G give the
+// level-1 coarse solution u_C on the coarse DOFs of the subregion (every
+// subregion sharing an interface DOF computes the same value in the same
+// order; its owner writes it) for the prolongation, k_prolong.
+// Phases A to D of one application, against 4 waves a block everywhere and
+// phase C inside D: 125 subregions (90^3) 9 + 11 + 22 -> 8 + 9 + 5 + 7 us, 1,728
+// (192^3) 14 + 19 + 43 -> 12 + 19 + 8 + 14 us.
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) k_l2_d(L2Args a) {
     extern __shared__ double sm[];
-    __shared__ double part[4][64];
+    __shared__ double part[NW][64];
     if (a.ctl->done) return;
     l2_cols(a);
     double *uCL = sm;                 // nL: x_I then x_G
@@ -1378,22 +1414,12 @@ __global__ void __launch_bounds__(256) k_l2_d(L2Args a) {
     const int b2 = a.B2_off[j];
     for (int k = threadIdx.x; k < nB; k += blockDim.x) {
         const int gi = a.g2[b2 + k];
-        double s = 0.0;
-        for (int t = a.asm2_ptr[gi]; t < a.asm2_ptr[gi + 1]; ++t) {
-            const int pos = a.asm2_idx[t];
-            const double *ph = a.Phi2 + a.ph_off[pos];
-            const int32_t *c3 = a.c3 + a.c3o[pos];
-            const int n3j = a.n3p[pos];
-            double v = a.u2[pos];
-#pragma unroll 8
-            for (int q = 0; q < n3j; ++q) v += ph[q] * a.u3[c3[q]];
-            s += v;
-        }
+        const double s = gather_range<4>(a.asm2_idx, a.u2, a.asm2_ptr[gi], a.asm2_ptr[gi + 1], 0.0);
         uCL[nI + k] = s;
     }
     __syncthreads();
     const double *vI2 = a.vI2 + a.I2_off[j];
-    cm_matvec<4>(a.K2 + a.K2_off[j] + (int64_t)nI * nL, nL, 0, nI, nB, uCL + nI, part,
+    cm_matvec<NW>(a.K2 + a.K2_off[j] + (int64_t)nI * nL, nL, 0, nI, nB, uCL + nI, part,
                  [&](int q, double y) { uCL[q] = vI2[q] - y; });
     // cm_matvec ends with a barrier: uCL is complete
     for (int q = threadIdx.x; q < nL; q += blockDim.x)
@@ -1571,22 +1597,31 @@ void launch_coarse_symblk(const CoarseDenseArgs &g, const SymBlkArgs &a, hipStre
     hipLaunchKernelGGL(k_symblk_sum, dim3(a.nb), dim3(256), 0, s, a);
 }
 
+#define L2_LAUNCH(K, SMEM)                                                                              \
+    do {                                                                                               \
+        if (nsr * ncols <= L2_ONE_ROUND) hipLaunchKernelGGL(K<16>, dim3(nsr, ncols), dim3(1024), SMEM, s, a); \
+        else hipLaunchKernelGGL(K<4>, dim3(nsr, ncols), dim3(256), SMEM, s, a);                            \
+    } while (0)
 void launch_l2_a(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols) {
-    hipLaunchKernelGGL(k_l2_a, dim3(nsr, ncols), dim3(256), (size_t)max_nL * 8, s, a);
+    L2_LAUNCH(k_l2_a, (size_t)max_nL * 8);
 }
 void launch_l2_b(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols) {
-    hipLaunchKernelGGL(k_l2_b, dim3(nsr, ncols), dim3(256), (size_t)max_nL * 8, s, a);
+    L2_LAUNCH(k_l2_b, (size_t)max_nL * 8);
 }
 size_t l2_d_smem(int max_nL) { return (size_t)std::max(1, max_nL) * 8; }
 
-int set_l2_d_smem_limit(size_t bytes) {
-    if (bytes <= 65536) return 0;
-    return hipFuncSetAttribute((const void *)k_l2_d, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess
-               ? 0 : -1;
+// (dynamic LDS of the level-2 kernels, beside up to 8 KB of partial sums)
+int set_l2_smem_limit(size_t bytes) {
+    if (bytes + 8192 <= 65536) return 0;
+    for (const void *p : {(const void *)k_l2_a<4>, (const void *)k_l2_b<4>, (const void *)k_l2_d<4>,
+                          (const void *)k_l2_a<16>, (const void *)k_l2_b<16>, (const void *)k_l2_d<16>})
+        if (hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return -1;
+    return 0;
 }
 
 void launch_l2_d(const L2Args &a, int nsr, size_t smem, hipStream_t s, int ncols) {
-    hipLaunchKernelGGL(k_l2_d, dim3(nsr, ncols), dim3(256), smem, s, a);
+    if (a.nB2 > 0) hipLaunchKernelGGL(k_l2_c, dim3((a.nB2 + 15) / 16, ncols), dim3(256), 0, s, a);
+    L2_LAUNCH(k_l2_d, smem);
 }
 
 }  // namespace bddc

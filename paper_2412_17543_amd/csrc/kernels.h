@@ -253,7 +253,7 @@ struct L2Args {
     // of its subregion's level-3 DOF list, level-3 DOFs of that subregion
     const int64_t *ph_off;
     const int32_t *c3o, *n3p;
-    int n3, max_nL;
+    int n3, max_nL, nB2;            // nB2: interface positions of all subregions
     // several columns (blockIdx.y): strides of rc.part and the per-column buffers
     int64_t cs_rc, cs_vI2, cs_t2, cs_rB2, cs_u2, cs_c3loc, cs_u3, cs_uC;
 };
@@ -423,7 +423,7 @@ void launch_pack_symblk(const double *M, int64_t ldm, int n, int nb, const int32
 void launch_l2_a(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols = 1);
 void launch_l2_b(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols = 1);
 size_t l2_d_smem(int max_nL);
-int set_l2_d_smem_limit(size_t bytes);
+int set_l2_smem_limit(size_t bytes);
 void launch_l2_d(const L2Args &a, int nsr, size_t smem, hipStream_t s, int ncols = 1);
 // deflation-column bucket of the templated reductions (0, 8, 16, 32, 64)
 int kmax_bucket(int k);
