@@ -2424,10 +2424,12 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
 constexpr int BMAX = 32;            // columns of one block solve
 
 struct BlockWork {
+    char *mem = nullptr;            // holds every device buffer below
     BlockItem *items = nullptr;     // one per subdomain (the Schur and Neumann tiles share the layout)
     int32_t *ones = nullptr;
     double *B = nullptr, *X = nullptr, *R = nullptr, *Z = nullptr, *P = nullptr, *Q = nullptr;
     double *yS = nullptr, *yN = nullptr, *cN = nullptr, *gp = nullptr, *gout = nullptr, *coef = nullptr;
+    double *xsave = nullptr;         // the forward sequence's previous solution
     double *h = nullptr;             // pinned: 4 Gram results, then 6 coefficient slots
     // per-column buffers of the coarse levels and the prolongation
     double *rC = nullptr, *uC = nullptr, *wloc = nullptr, *vI2 = nullptr, *t2 = nullptr, *rB2 = nullptr,
@@ -2439,11 +2441,7 @@ struct BlockWork {
 };
 
 void free_block(bddc_ctx *c, BlockWork &b) {
-    dfree(c, b.items); dfree(c, b.ones);
-    dfree(c, b.B); dfree(c, b.X); dfree(c, b.R); dfree(c, b.Z); dfree(c, b.P); dfree(c, b.Q);
-    dfree(c, b.yS); dfree(c, b.yN); dfree(c, b.cN); dfree(c, b.gp); dfree(c, b.gout); dfree(c, b.coef);
-    dfree(c, b.rC); dfree(c, b.uC); dfree(c, b.wloc); dfree(c, b.vI2); dfree(c, b.t2); dfree(c, b.rB2);
-    dfree(c, b.u2); dfree(c, b.c3loc); dfree(c, b.u3); dfree(c, b.r3);
+    dfree(c, b.mem);
     if (b.h) (void)hipHostFree(b.h);
     b = BlockWork{};
 }
@@ -2458,19 +2456,6 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
     }
     b.ylen = std::max<int64_t>(1, (int64_t)c->h_b_off[nsub - 1] + c->h_nB[nsub - 1]);
     b.clen = std::max<int64_t>(1, (int64_t)c->h_c_off[nsub - 1] + c->h_nc[nsub - 1]);
-    const size_t nv = (size_t)c->ld * BMAX;
-    int rc;
-    std::vector<int32_t> ones(nsub, 1);
-    if ((rc = dupload(c, &b.items, is)) || (rc = dupload(c, &b.ones, ones)) ||
-        (rc = dalloc(c, &b.B, nv)) || (rc = dalloc(c, &b.X, nv)) || (rc = dalloc(c, &b.R, nv)) ||
-        (rc = dalloc(c, &b.Z, nv)) || (rc = dalloc(c, &b.P, nv)) || (rc = dalloc(c, &b.Q, nv)) ||
-        (rc = dalloc(c, &b.yS, (size_t)b.ylen * BMAX)) || (rc = dalloc(c, &b.yN, (size_t)b.ylen * BMAX)) ||
-        (rc = dalloc(c, &b.cN, (size_t)b.clen * BMAX)) ||
-        (rc = dalloc(c, &b.gp, (size_t)c->gram_nb * BlockWork::GSZ)) ||
-        (rc = dalloc(c, &b.gout, (size_t)4 * BlockWork::GSZ)) || (rc = dalloc(c, &b.coef, (size_t)6 * BlockWork::CSZ)))
-        return rc;
-    if (hipHostMalloc((void **)&b.h, sizeof(double) * (4 * BlockWork::GSZ + 6 * BlockWork::CSZ)) != hipSuccess)
-        return fail(BDDC_ENOMEM, "hipHostMalloc failed (block adjoint)");
     b.nclen = std::max(1, c->nC);
     if (c->three) {
         int64_t i2 = 0, b2 = 0, c3 = 0;
@@ -2480,12 +2465,35 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
         b.c3len = std::max<int64_t>(1, c3);
         b.n3len = std::max(1, c->n3);
     }
-    if ((rc = dalloc(c, &b.rC, (size_t)b.nclen * BMAX)) || (rc = dalloc(c, &b.uC, (size_t)b.nclen * BMAX)) ||
-        (rc = dalloc(c, &b.wloc, (size_t)b.ylen * BMAX)) || (rc = dalloc(c, &b.vI2, (size_t)b.i2len * BMAX)) ||
-        (rc = dalloc(c, &b.t2, (size_t)b.b2len * BMAX)) || (rc = dalloc(c, &b.rB2, (size_t)b.b2len * BMAX)) ||
-        (rc = dalloc(c, &b.u2, (size_t)b.b2len * BMAX)) || (rc = dalloc(c, &b.c3loc, (size_t)b.c3len * BMAX)) ||
-        (rc = dalloc(c, &b.u3, (size_t)b.n3len * BMAX)) || (rc = dalloc(c, &b.r3, (size_t)b.n3len * BMAX)))
-        return rc;
+    // one allocation (and one free, which waits for the device) a call for all
+    // device buffers: places first, then the memory
+    const size_t nv = (size_t)c->ld * BMAX, ny = (size_t)b.ylen * BMAX;
+    const std::pair<double **, size_t> parts[] = {
+        {&b.B, nv}, {&b.X, nv}, {&b.R, nv}, {&b.Z, nv}, {&b.P, nv}, {&b.Q, nv}, {&b.yS, ny}, {&b.yN, ny}, {&b.wloc, ny},
+        {&b.cN, (size_t)b.clen * BMAX}, {&b.gp, (size_t)c->gram_nb * BlockWork::GSZ},
+        {&b.gout, (size_t)4 * BlockWork::GSZ}, {&b.coef, (size_t)6 * BlockWork::CSZ},
+        {&b.rC, (size_t)b.nclen * BMAX}, {&b.uC, (size_t)b.nclen * BMAX}, {&b.vI2, (size_t)b.i2len * BMAX},
+        {&b.t2, (size_t)b.b2len * BMAX}, {&b.rB2, (size_t)b.b2len * BMAX}, {&b.u2, (size_t)b.b2len * BMAX},
+        {&b.c3loc, (size_t)b.c3len * BMAX}, {&b.u3, (size_t)b.n3len * BMAX}, {&b.r3, (size_t)b.n3len * BMAX},
+        {&b.xsave, (size_t)c->n_gamma}};
+    auto up = [](size_t doubles) { return (doubles * sizeof(double) + 255) & ~size_t(255); };
+    const size_t si = (nsub * sizeof(BlockItem) + 255) & ~size_t(255), so = (nsub * sizeof(int32_t) + 255) & ~size_t(255);
+    size_t total = si + so;
+    for (const auto &q : parts) total += up(q.second);
+    if (int rc = dalloc(c, &b.mem, total)) return rc;
+    char *at = b.mem;
+    b.items = reinterpret_cast<BlockItem *>(at);
+    b.ones = reinterpret_cast<int32_t *>(at + si);
+    at += si + so;
+    for (const auto &q : parts) {
+        *q.first = reinterpret_cast<double *>(at);
+        at += up(q.second);
+    }
+    const std::vector<int32_t> ones(nsub, 1);
+    HIPCHK(hipMemcpyAsync(b.items, is.data(), nsub * sizeof(BlockItem), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(b.ones, ones.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+    if (hipHostMalloc((void **)&b.h, sizeof(double) * (4 * BlockWork::GSZ + 6 * BlockWork::CSZ)) != hipSuccess)
+        return fail(BDDC_ENOMEM, "hipHostMalloc failed (block adjoint)");
     // partial slots that no kernel writes (none with one chunk per subdomain) stay zero
     launch_fill((int64_t)b.ylen * BMAX, 0.0, b.yN, c->stream);
     launch_fill((int64_t)b.clen * BMAX, 0.0, b.cN, c->stream);
@@ -2533,17 +2541,10 @@ void block_A(bddc_ctx *c, BlockWork &b, const double *X, int ncols, double *out)
     launch_gather_block(c->n_gamma, c->d_asm_ptr, c->d_asm_idx, b.yS, b.ylen, out, c->ld, ncols, c->stream);
 }
 
-// The coarse levels of block_M on stream st: restriction of all columns,
-// then the coarse problems (one grid row per column).
-void block_coarse(bddc_ctx *c, BlockWork &b, const double *R, int ncols, hipStream_t st) {
+// The coarse levels of block_M on stream st, from the restrictions of the
+// Neumann product (one grid row per column).
+void block_coarse(bddc_ctx *c, BlockWork &b, int ncols, hipStream_t st) {
     TScope ts(c, TK_COARSE);
-    CrestArgs ra{};
-    ra.ctl = c->d_ctl;
-    ra.nB = c->d_nB; ra.b_off = c->d_b_off; ra.gB = c->d_gB; ra.nc = c->d_nc; ra.c_off = c->d_c_off;
-    ra.phir = c->d_phirx[prec_slot(64)]; ra.phr_off = c->d_phr_off;
-    ra.X = R; ra.ldx = c->ld; ra.part = b.cN; ra.cs = b.clen; ra.ncols = ncols;
-    ra.cols = crest_cols(64, c->max_nB, ncols);
-    launch_crest(ra, 64, c->n_sub, c->max_nB, st);
     const Gather rc{c->d_casm_ptr, c->d_casm_idx, b.cN};
     if (c->coarse_dense) {
         CoarseDenseArgs ca{};
@@ -2576,9 +2577,13 @@ void block_M(bddc_ctx *c, BlockWork &b, const double *R, int ncols, double *Z) {
         BlockSymvArgs a{};
         a.tiles = (const double *)c->d_Nx[prec_slot(64)]; a.items = b.items; a.gB = c->d_gB; a.X = R; a.ldx = c->ld;
         a.ncols = ncols; a.ypart = b.yN; a.ylen = b.ylen;
+        if (c->nC > 0) {
+            a.phir = (const double *)c->d_phirx[prec_slot(64)]; a.phr_off = c->d_phr_off;
+            a.nc = c->d_nc; a.c_off = c->d_c_off; a.cpart = b.cN; a.cs = b.clen;
+        }
         launch_symm(a, c->n_sub, c->max_nB, b.max_nt, c->stream);
     }
-    if (c->nC > 0) block_coarse(c, b, R, ncols, c->stream);
+    if (c->nC > 0) block_coarse(c, b, ncols, c->stream);
     TScope ts(c, TK_VEC);
     ProlArgs pa{};
     pa.ctl = c->d_ctl; pa.gated = 0;
@@ -2882,14 +2887,12 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
     if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     BlockWork b;
     int rc = alloc_block(c, b);
-    double *xsave = nullptr;
-    if (!rc) rc = dalloc(c, &xsave, c->n_gamma);
     if (rc) { free_block(c, b); return rc; }
-    launch_copy(c->n_gamma, c->d_x, xsave, c->stream);
+    launch_copy(c->n_gamma, c->d_x, b.xsave, c->stream);
     launch_set_done(c->d_ctl, 0, c->stream);
     // condensation and recovery: CBLK right-hand sides per pass over the
     // interior operators when the block product can stage them
-    if (n_rhs > 1 && (rc = cblk_setup(c))) { dfree(c, xsave); free_block(c, b); return rc; }
+    if (n_rhs > 1 && (rc = cblk_setup(c))) { free_block(c, b); return rc; }
     const bool grouped = n_rhs > 1 && c->cblk_state == 1;
     for (int g0 = 0; g0 < n_rhs; g0 += CBLK) {
         const int gn = std::min(CBLK, n_rhs - g0);
@@ -2901,7 +2904,7 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
                         c->stream);
         }
     }
-    if (rc) { launch_copy(c->n_gamma, xsave, c->d_x, c->stream); (void)hipStreamSynchronize(c->stream); dfree(c, xsave); free_block(c, b); return rc; }
+    if (rc) { launch_copy(c->n_gamma, b.xsave, c->d_x, c->stream); (void)hipStreamSynchronize(c->stream); free_block(c, b); return rc; }
     int it = 0;
     rc = block_solve(c, b, n_rhs, rtol, &it);
     if (iters) *iters = it;
@@ -2927,10 +2930,9 @@ int bddc_adjoint_grad_block(bddc_ctx *c, const double *dLdu_seq, int32_t n_rhs, 
         g.lam = grad_rhs_seq; g.u = u_seq; g.grad = grad_logcoef;
         launch_elem_grad(g, c->stream);
     }
-    launch_copy(c->n_gamma, xsave, c->d_x, c->stream);
+    launch_copy(c->n_gamma, b.xsave, c->d_x, c->stream);
     c->have_solve = false;
     (void)hipStreamSynchronize(c->stream);
-    dfree(c, xsave);
     free_block(c, b);
     return rc;
 }

@@ -1,6 +1,7 @@
 // Block products of the block adjoint and of grouped condensation (several
 // right-hand sides at once): the batched symmetric products y_i = S_i x_i
-// (Schur), u_i = D N_i D g_i (Neumann, eq. localCorr) or K_II^{-1} b_i
+// (Schur), u_i = D N_i D g_i (Neumann, eq. localCorr, with the coarse
+// restriction (D Phi_i)^T g_i of eq. coarse_problem) or K_II^{-1} b_i
 // (interior), 16 columns at a time, on the matrix cores, and the assembly of
 // the per-subdomain results.
 //
@@ -136,6 +137,53 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
         for (int s = 0; s < 4; ++s) u[s] = tw[rb ^ s];
     };
     const dvec4 zero = {0.0, 0.0, 0.0, 0.0};
+    // Coarse restriction c_i = (D Phi_i)^T X_i from the staged X, 16 coarse DOFs
+    // at a time: wave w takes the 16-row tiles w, w + 8, ..., U of them
+    // requested together (four consecutive entries of a DOF's row a lane, the
+    // steps' operands as loaded), the waves' sums added in wave order.
+    if (a.phir) {
+        constexpr int U = 4;
+        const int nci = a.nc[sub], ldp = phi_ld(n), tt = npad / 16, pend = nci * ldp * 8;
+        const __amdgpu_buffer_rsrc_t pr = raw_rsrc(a.phir + a.phr_off[sub], pend);
+        for (int q0 = 0; q0 < nci; q0 += 16) {
+            dvec4 acc = zero;
+            for (int t0 = w; t0 < tt; t0 += NW * U) {
+                uvec4 pa[U], pb[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int t = t0 + NW * u, k = 16 * t + 4 * lk;
+                    const int off = t < tt && k < ldp && q0 + li < nci ? ((q0 + li) * ldp + k) * 8 : pend;
+                    pa[u] = __builtin_amdgcn_raw_buffer_load_b128(pr, off, 0, 0);
+                    pb[u] = __builtin_amdgcn_raw_buffer_load_b128(pr, off + 16, 0, 0);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int t = t0 + NW * u;
+                    if (t < tt) {                      // (wave-uniform)
+                        const double v[4] = {__hiloint2double(pa[u].y, pa[u].x), __hiloint2double(pa[u].w, pa[u].z),
+                                             __hiloint2double(pb[u].y, pb[u].x), __hiloint2double(pb[u].w, pb[u].z)};
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[s], xs[t * 256 + s * 64 + L], acc, 0, 0, 0);
+                    }
+                }
+                // (a tile past the last: its zero read is not left outstanding)
+#pragma unroll
+                for (int u = 0; u < U; ++u) asm volatile("" ::"v"(pa[u]), "v"(pb[u]));
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tw[r * 64 + L] = acc[r];
+            lds_barrier();
+            if (tid < 256) {
+                double v = ts[tid];
+#pragma unroll
+                for (int q = 1; q < NW; ++q) v += ts[q * 256 + tid];
+                const int q = q0 + lk + 4 * w, col = c0 + li;      // (w = tid / 64 < 4: register of the result)
+                if (q < nci && col < a.ncols) a.cpart[(int64_t)col * a.cs + a.c_off[sub] + q] = v;
+            }
+            lds_barrier();
+        }
+    }
     dvec4 yacc[NJ], racc = zero;
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) yacc[jj] = zero;

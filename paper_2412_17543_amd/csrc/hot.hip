@@ -729,79 +729,6 @@ __device__ __forceinline__ double ld_rc_as<uint16_t>(__amdgpu_buffer_rsrc_t r, i
     return (double)dev::bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, i * 2, 0, 0));
 }
 
-// Coarse residual partials c_i = (D Phi_i)^T R_i x of every subdomain (the
-// right-hand side of eq. coarse_problem) for several columns at once (the
-// block products; a single-vector Neumann product computes them itself):
-// one block per subdomain, one float64 partial per (column, local coarse
-// DOF).  D Phi_i is stored
-// column-major, so each coarse DOF's entries are one contiguous row: wave w
-// takes the DOFs w, w + 4, ...; a lane holds 16-byte pieces of QB of them
-// (JM pieces each per round trip, the first requested before the gather of
-// x), dots them with the gathered x staged in LDS (zero past n), and the
-// wave's sum gives the partial (a fixed order: the result does not depend
-// on timing).  Pieces of DOFs past nc_i read as zero through the range check.
-template <typename T>
-__global__ void __launch_bounds__(256) k_crest(CrestArgs a) {
-    constexpr int V = 16 / (int)sizeof(T), W = 64 * V, QB = 4, JM = 2;
-    extern __shared__ double xs[];          // [cols][XL]
-    if (a.ctl->done) return;
-    const int i = blockIdx.x, n = a.nB[i], nci = a.nc[i];
-    if (nci == 0) return;
-    const int ld = phi_ld(n), J = (ld + W - 1) / W, XL = J * W;   // pieces per DOF row, staged length
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int32_t *gb = a.gB + a.b_off[i];
-    const __amdgpu_buffer_rsrc_t pr =
-        tile_rsrc(reinterpret_cast<const T *>(a.phir) + a.phr_off[i], nci * ld * (int)sizeof(T));
-    uvec4 f[QB][JM];
-    auto issue = [&](int q0, int jb) {
-#pragma unroll
-        for (int qi = 0; qi < QB; ++qi)
-#pragma unroll
-            for (int jj = 0; jj < JM; ++jj)
-                f[qi][jj] = jb + jj < J ? __builtin_amdgcn_raw_buffer_load_b128(
-                                              pr, ((q0 + 4 * qi) * ld + (jb + jj) * W + V * l) * (int)sizeof(T), 0, 0)
-                                        : uvec4{0u, 0u, 0u, 0u};
-    };
-    issue(w, 0);
-    bool held = true;                       // f holds (DOFs from w, pieces 0..JM-1)
-    for (int c0 = 0; c0 < a.ncols; c0 += a.cols) {
-        const int cg = min(a.cols, a.ncols - c0);
-        __syncthreads();                    // the previous columns are used
-        for (int e = threadIdx.x; e < cg * XL; e += 256) {
-            const int cc = e / XL, k = e - cc * XL;
-            xs[e] = k < n ? a.X[(int64_t)(c0 + cc) * a.ldx + gb[k]] : 0.0;
-        }
-        __syncthreads();
-        for (int q0 = w; q0 < nci; q0 += 4 * QB) {
-            for (int cc = 0; cc < cg; ++cc) {
-                double acc[QB];
-#pragma unroll
-                for (int qi = 0; qi < QB; ++qi) acc[qi] = 0.0;
-                for (int jb = 0; jb < J; jb += JM) {
-                    if (!held) issue(q0, jb);
-                    held = false;
-#pragma unroll
-                    for (int qi = 0; qi < QB; ++qi)
-#pragma unroll
-                        for (int jj = 0; jj < JM; ++jj)
-                            if (jb + jj < J) acc[qi] += dot16<T>(f[qi][jj], xs + cc * XL + (jb + jj) * W + V * l);
-                }
-#pragma unroll
-                for (int qi = 0; qi < QB; ++qi) {
-                    const double s = wave_sum(acc[qi]);
-                    const int q = q0 + 4 * qi;
-                    if (l == 0 && q < nci) a.part[(int64_t)(c0 + cc) * a.cs + a.c_off[i] + q] = s;
-                }
-            }
-        }
-    }
-    // a wave without DOFs leaves its first requests unused: none outstanding at exit
-#pragma unroll
-    for (int qi = 0; qi < QB; ++qi)
-#pragma unroll
-        for (int jj = 0; jj < JM; ++jj) asm volatile("" ::"v"(f[qi][jj]));
-}
-
 template <typename T>
 __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
     extern __shared__ double uCl[];
@@ -1477,25 +1404,6 @@ void launch_symv(const SymvArgs &a, SymvOp op, int prec, SymvCfg cfg, size_t sme
 void launch_update(const UpdArgs &a, int grid, hipStream_t s) {
     if (a.n > (int64_t)grid * 256 * 2) hipLaunchKernelGGL(k_update<4>, dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_update<1>, dim3(grid), dim3(256), 0, s, a);
-}
-
-// staged length of the gathered x of the restriction for interfaces of up
-// to max_nB entries (whole 16-byte pieces of a wave)
-static int crest_xl(int prec, int max_nB) {
-    const int W = 64 * (128 / prec);
-    return (phi_ld(std::max(1, max_nB)) + W - 1) / W * W;
-}
-// columns staged at a time: up to 4096 values (32 KiB of LDS)
-int crest_cols(int prec, int max_nB, int ncols) {
-    return std::max(1, std::min(ncols, 4096 / crest_xl(prec, max_nB)));
-}
-
-void launch_crest(const CrestArgs &a, int prec, int nsub, int max_nB, hipStream_t s) {
-    if (nsub <= 0 || a.ncols <= 0) return;
-    const size_t smem = (size_t)a.cols * crest_xl(prec, max_nB) * 8;
-    if (prec == 64) hipLaunchKernelGGL(k_crest<double>, dim3(nsub), dim3(256), smem, s, a);
-    else if (prec == 32) hipLaunchKernelGGL(k_crest<float>, dim3(nsub), dim3(256), smem, s, a);
-    else hipLaunchKernelGGL(k_crest<uint16_t>, dim3(nsub), dim3(256), smem, s, a);
 }
 
 void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s, int ncols) {

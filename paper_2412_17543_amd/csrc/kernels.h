@@ -111,17 +111,6 @@ struct UpdArgs {                    // Alg. 1, lines 9-11
     int hist_cap;
 };
 
-struct CrestArgs {                  // c_i = (D Phi_i)^T R_i x (right-hand side of eq. coarse_problem)
-    Ctl *ctl;                       // returns when ctl->done
-    const int32_t *nB, *b_off, *gB, *nc, *c_off;
-    const void *phir;               // D Phi_i, column-major (rows of phi_ld(n) entries), local precision
-    const int64_t *phr_off;
-    const double *X; int64_t ldx;   // ncols columns of the interface vector
-    double *part; int64_t cs;       // partial of column j, DOF q of subdomain i: part[j * cs + c_off[i] + q]
-    int ncols;
-    int cols;                       // columns whose gathered x is staged in LDS at a time
-};
-
 struct ProlArgs {                   // w_i = u_i + D Phi_i u_C (eq. averaging_subdomain_solves)
     Ctl *ctl;
     int gated;
@@ -376,6 +365,12 @@ struct BlockSymvArgs {
     const int32_t *gB;              // local interface position -> interface index
     const double *X; int64_t ldx; int ncols;   // input block, column-major
     double *ypart; int64_t ylen;    // y of subdomain i, column c: ypart[c ylen + xoff_i + k]
+    // coarse restriction (Neumann products; null phir: none): c_i = (D Phi_i)^T X_i,
+    // float64, in cpart[c cs + c_off_i + q]
+    const double *phir;
+    const int64_t *phr_off;
+    const int32_t *nc, *c_off;
+    double *cpart; int64_t cs;
 };
 constexpr int SYMM_MAX_N = 528;     // rows of a subdomain in a block product
 int set_symm_smem_limit();
@@ -406,8 +401,6 @@ size_t symv_smem(int prec, int nw, int max_nt);
 int set_symv_smem_limit(size_t bytes);
 void launch_symv(const SymvArgs &a, SymvOp op, int prec, SymvCfg cfg, size_t smem, hipStream_t s);
 void launch_update(const UpdArgs &a, int grid, hipStream_t s);
-void launch_crest(const CrestArgs &a, int prec, int nsub, int max_nB, hipStream_t s);
-int crest_cols(int prec, int max_nB, int ncols);
 void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s, int ncols = 1);
 void launch_zasm(const ZasmArgs &a, int kmax, int grid, hipStream_t s, int ncols = 1);
 void launch_pupd(const PupdArgs &a, int kmax, int grid, hipStream_t s);
