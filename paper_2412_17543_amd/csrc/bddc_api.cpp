@@ -96,6 +96,10 @@ struct bddc_ctx {
     int64_t *d_k_off = nullptr, *d_s_off = nullptr, *d_phr_off = nullptr;
     int32_t *d_pch_sub = nullptr, *d_pch_row = nullptr;   // prolongation blocks: subdomain, first row
     int n_pch = 0;
+    int32_t *d_ich_sub = nullptr, *d_ich_row = nullptr;   // blocks over interior rows: subdomain, first row
+    int n_ich = 0, n_int = 0;                             // those blocks, interior dofs
+    int32_t *d_src = nullptr;                             // source of every node's value (RecOutArgs)
+    double *d_yI = nullptr;                               // interior product summed over its segments
     double *d_K = nullptr, *d_S = nullptr, *d_KC = nullptr;
     void *d_N = nullptr, *d_phir = nullptr;      // Neumann operators in use (local precision c->prec)
     void *d_Nx[3] = {}, *d_phirx[3] = {};        // the storage precisions built: float64, float32, bfloat16
@@ -109,7 +113,6 @@ struct bddc_ctx {
     int cblk_nt = 0;                // most tile rows of an interior operator
     int64_t cblk_ylen = 0;
     BlockItem *d_cblk_items = nullptr;
-    int32_t *d_cblk_ones = nullptr;
     double *d_cblk_y = nullptr, *d_cblk_b = nullptr, *d_cblk_bbp = nullptr;
     double *d_cblk_x = nullptr, *d_cblk_t = nullptr;   // interface solutions, recovery right-hand sides
     std::vector<int32_t> h_nB, h_nI, h_nc, h_b_off, h_c_off, h_pos_sub;
@@ -122,7 +125,7 @@ struct bddc_ctx {
     // iteration vectors
     int vgrid = 1;
     double *d_b = nullptr, *d_x = nullptr, *d_r = nullptr, *d_z = nullptr, *d_p = nullptr, *d_tmp = nullptr;
-    double *d_locq = nullptr, *d_wloc = nullptr;
+    double *d_wloc = nullptr;
     double *d_rr = nullptr, *d_bbp = nullptr, *d_zp = nullptr, *d_wp = nullptr, *d_dotS = nullptr, *d_gp = nullptr;
     // coarse
     bool three = false;
@@ -824,20 +827,48 @@ void run_interior(bddc_ctx *c, const double *v) {
     launch_symv(a, SYMV_INTERIOR, 64, c->opI.cfg, c->opI.smem, c->stream);
 }
 
-// Condensation (Section 3.1): y_I = K_II^{-1} F_I, t_i = K_BI y_I,
-// b = F_G - sum_i R_i^T t_i, per-block ||b||^2 partials.
+// y_I of the last single interior product: its partials, summed over the
+// segments where a subdomain was cut into several (else they are y_I already).
+const double *interior_sums(bddc_ctx *c) {
+    if (c->opI.ylen == c->n_int) return c->opI.d_ypart;
+    IntSumArgs a{};
+    a.ch_sub = c->d_ich_sub; a.ch_row = c->d_ich_row; a.nI = c->d_nI; a.nchunk = c->opI.d_nchunk; a.pb = c->opI.d_pb;
+    a.i_off = c->d_i_off; a.ypart = c->opI.d_ypart; a.y = c->d_yI;
+    launch_int_sum(a, c->n_ich, c->stream);
+    return c->d_yI;
+}
+
+// b = F_G - sum_i R_i^T K_BI y_I of g right-hand sides, per-block ||b||^2 partials
+void condense_rows(bddc_ctx *c, const double *F, const double *y, int64_t ldy, double *b, double *part, int g) {
+    CondArgs a{};
+    a.n = c->n_gamma; a.gamma = c->d_gamma; a.ptr = c->d_asm_ptr; a.idx = c->d_asm_idx;
+    a.kbi_ptr = c->d_kbi_ptr; a.kbi_col = c->d_kbi_col; a.kbi_val = c->d_kbi_val;
+    a.F = F; a.y = y; a.b = b; a.part = part;
+    a.ldF = c->n_nodes; a.ldy = ldy; a.ldb = c->ld; a.ldp = c->vgrid;
+    launch_condense(a, c->vgrid, g, c->stream);
+}
+
+// out[nodesI] = F_I - K_IB x_B of g right-hand sides
+void recover_rhs(bddc_ctx *c, const double *F, const double *x, double *out, int g) {
+    RecRhsArgs a{};
+    a.n = c->n_int; a.nodesI = c->d_nodesI; a.kib_ptr = c->d_kib_ptr; a.kib_col = c->d_kib_col; a.kib_val = c->d_kib_val;
+    a.F = F; a.x = x; a.out = out; a.ldF = c->n_nodes; a.ldx = c->ld; a.ldo = c->n_nodes;
+    launch_rec_rhs(a, g, c->stream);
+}
+
+// u = (x_I, x_G) of g right-hand sides
+void recover_out(bddc_ctx *c, const double *y, int64_t ldy, const double *x, double *u, int g) {
+    RecOutArgs a{};
+    a.n = c->n_nodes; a.src = c->d_src; a.y = y; a.x = x; a.u = u; a.ldy = ldy; a.ldx = c->ld; a.ldu = c->n_nodes;
+    launch_rec_out(a, g, c->stream);
+}
+
+// Condensation (Section 3.1): y_I = K_II^{-1} F_I, b = F_G - sum_i R_i^T K_BI y_I,
+// per-block ||b||^2 partials.
 void run_condense(bddc_ctx *c, const double *F) {
     TScope ts(c, TK_COND);
     run_interior(c, F);
-    CondArgs a{};
-    a.nI = c->d_nI; a.nB = c->d_nB; a.i_off = c->d_i_off; a.b_off = c->d_b_off;
-    a.nchunk = c->opI.d_nchunk; a.pb = c->opI.d_pb; a.ypart = c->opI.d_ypart;
-    a.kbi_ptr = c->d_kbi_ptr; a.kbi_col = c->d_kbi_col; a.kbi_val = c->d_kbi_val; a.t = c->d_locq;
-    launch_cond_local(a, c->n_sub, c->max_nI, c->stream);
-    CondAsmArgs b{};
-    b.n = c->n_gamma; b.gamma = c->d_gamma; b.ptr = c->d_asm_ptr; b.idx = c->d_asm_idx; b.F = F; b.loc = c->d_locq;
-    b.b = c->d_b; b.part = c->d_bbp;
-    launch_cond_asm(b, c->vgrid, c->stream);
+    condense_rows(c, F, interior_sums(c), 0, c->d_b, c->d_bbp, 1);
 }
 
 constexpr int CBLK = 16;            // right-hand sides condensed per pass over the interior tiles
@@ -850,7 +881,6 @@ int cblk_setup(bddc_ctx *c) {
     if (c->max_nI > SYMM_MAX_N) { c->cblk_state = -1; return 0; }
     for (int n : c->h_nI) c->cblk_nt = std::max(c->cblk_nt, tile_rows(n));
     std::vector<BlockItem> items(nsub);
-    std::vector<int32_t> ones(nsub, 1);
     int64_t slot = 0, y = 0;
     for (int i = 0; i < nsub; ++i) {
         items[i] = BlockItem{slot, c->h_nI[i], (int32_t)y};
@@ -860,7 +890,7 @@ int cblk_setup(bddc_ctx *c) {
     if (y > INT32_MAX) { c->cblk_state = -1; return 0; }
     c->cblk_ylen = std::max<int64_t>(1, y);
     int rc;
-    if ((rc = dupload(c, &c->d_cblk_items, items)) || (rc = dupload(c, &c->d_cblk_ones, ones)) ||
+    if ((rc = dupload(c, &c->d_cblk_items, items)) ||
         (rc = dalloc(c, &c->d_cblk_y, (size_t)c->cblk_ylen * CBLK)) ||
         (rc = dalloc(c, &c->d_cblk_b, (size_t)c->ld * CBLK)) ||
         (rc = dalloc(c, &c->d_cblk_bbp, (size_t)c->vgrid * CBLK)) ||
@@ -873,7 +903,7 @@ int cblk_setup(bddc_ctx *c) {
 
 // Condensation (Section 3.1) of the g <= CBLK right-hand sides F[0..g) (rows
 // of n_nodes): y_I = K_II^{-1} F_I for all of them in one pass over the
-// interior tiles, then t_i = K_BI y_I and b per column, into the group buffers.
+// interior tiles, then b of all columns, into the group buffers.
 int run_condense_block(bddc_ctx *c, const double *F, int g) {
     TScope ts(c, TK_COND);
     if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
@@ -882,18 +912,7 @@ int run_condense_block(bddc_ctx *c, const double *F, int g) {
     a.X = F; a.ldx = c->n_nodes; a.ncols = g;
     a.ypart = c->d_cblk_y; a.ylen = c->cblk_ylen;
     launch_symm(a, c->n_sub, c->max_nI, c->cblk_nt, c->stream);
-    for (int q = 0; q < g; ++q) {
-        CondArgs ca{};
-        ca.nI = c->d_nI; ca.nB = c->d_nB; ca.i_off = c->d_i_off; ca.b_off = c->d_b_off;
-        ca.nchunk = c->d_cblk_ones; ca.pb = c->d_i_off; ca.ypart = c->d_cblk_y + (size_t)q * c->cblk_ylen;
-        ca.kbi_ptr = c->d_kbi_ptr; ca.kbi_col = c->d_kbi_col; ca.kbi_val = c->d_kbi_val; ca.t = c->d_locq;
-        launch_cond_local(ca, c->n_sub, c->max_nI, c->stream);
-        CondAsmArgs b{};
-        b.n = c->n_gamma; b.gamma = c->d_gamma; b.ptr = c->d_asm_ptr; b.idx = c->d_asm_idx;
-        b.F = F + (size_t)q * c->n_nodes; b.loc = c->d_locq;
-        b.b = c->d_cblk_b + (size_t)q * c->ld; b.part = c->d_cblk_bbp + (size_t)q * c->vgrid;
-        launch_cond_asm(b, c->vgrid, c->stream);
-    }
+    condense_rows(c, F, c->d_cblk_y, c->cblk_ylen, c->d_cblk_b, c->d_cblk_bbp, g);
     return 0;
 }
 
@@ -909,45 +928,23 @@ void take_condensed(bddc_ctx *c, int q) {
 // one pass over the interior tiles; u[q] = (x_I, x_G).
 int run_recover_block(bddc_ctx *c, const double *F, double *u, int g) {
     TScope ts(c, TK_COND);
-    RecArgs a{};
-    a.nI = c->d_nI; a.nB = c->d_nB; a.i_off = c->d_i_off; a.b_off = c->d_b_off; a.nodesI = c->d_nodesI;
-    a.gB = c->d_gB;
-    a.kib_ptr = c->d_kib_ptr; a.kib_col = c->d_kib_col; a.kib_val = c->d_kib_val;
-    a.nchunk = c->d_cblk_ones; a.pb = c->d_i_off;
-    for (int q = 0; q < g; ++q) {
-        a.x = c->d_cblk_x + (size_t)q * c->ld; a.F = F + (size_t)q * c->n_nodes;
-        a.out = c->d_cblk_t + (size_t)q * c->n_nodes;
-        launch_rec_rhs(a, c->n_sub, c->max_nB, c->stream);
-    }
+    recover_rhs(c, F, c->d_cblk_x, c->d_cblk_t, g);
     if (set_symm_smem_limit()) return fail(BDDC_EHIP, "hipFuncSetAttribute (block product LDS) failed");
     BlockSymvArgs b{};
     b.tiles = c->d_KI; b.items = c->d_cblk_items; b.gB = c->d_nodesI;
     b.X = c->d_cblk_t; b.ldx = c->n_nodes; b.ncols = g;
     b.ypart = c->d_cblk_y; b.ylen = c->cblk_ylen;
     launch_symm(b, c->n_sub, c->max_nI, c->cblk_nt, c->stream);
-    for (int q = 0; q < g; ++q) {
-        double *uq = u + (size_t)q * c->n_nodes;
-        a.ypart = c->d_cblk_y + (size_t)q * c->cblk_ylen; a.u = uq;
-        launch_fill(c->n_nodes, 0.0, uq, c->stream);
-        launch_rec_out(a, c->n_sub, c->stream);
-        launch_scatter_gamma(c->n_gamma, c->d_gamma, c->d_cblk_x + (size_t)q * c->ld, uq, c->stream);
-    }
+    recover_out(c, c->d_cblk_y, c->cblk_ylen, c->d_cblk_x, u, g);
     return 0;
 }
 
 // Interior recovery (Section 3.1): x_I = K_II^{-1} (F_I - K_IB x_B), u = (x_I, x_G).
 int run_recover(bddc_ctx *c, const double *F, double *u) {
     TScope ts(c, TK_COND);
-    RecArgs a{};
-    a.nI = c->d_nI; a.nB = c->d_nB; a.i_off = c->d_i_off; a.b_off = c->d_b_off; a.nodesI = c->d_nodesI;
-    a.gB = c->d_gB; a.x = c->d_x; a.F = F;
-    a.kib_ptr = c->d_kib_ptr; a.kib_col = c->d_kib_col; a.kib_val = c->d_kib_val; a.out = c->d_tmpN;
-    a.nchunk = c->opI.d_nchunk; a.pb = c->opI.d_pb; a.ypart = c->opI.d_ypart; a.u = u;
-    launch_rec_rhs(a, c->n_sub, c->max_nB, c->stream);
+    recover_rhs(c, F, c->d_x, c->d_tmpN, 1);
     run_interior(c, c->d_tmpN);
-    launch_fill(c->n_nodes, 0.0, u, c->stream);
-    launch_rec_out(a, c->n_sub, c->stream);
-    launch_scatter_gamma(c->n_gamma, c->d_gamma, c->d_x, u, c->stream);
+    recover_out(c, interior_sums(c), 0, c->d_x, u, 1);
     return 0;
 }
 
@@ -1534,17 +1531,21 @@ int setup_couplings(bddc_ctx *c, const std::vector<int64_t> &k_off) {
     hipStream_t s = c->stream;
     int64_t ni = 0, nb = 0;
     for (const SubHost &sh : st.sub) { ni += sh.nI; nb += sh.nB; }
+    if (std::max(ni, nb) > INT32_MAX / 2) return fail(BDDC_EINVAL, "too many local interface or interior entries");
+    std::vector<int32_t> gB;
+    gB.reserve((size_t)nb);
+    for (const SubHost &sh : st.sub) gB.insert(gB.end(), sh.gB.begin(), sh.gB.end());
     int32_t *d_tot;
     CoupDesc *dd;
     int rc;
-    if ((rc = dalloc(c, &c->d_kib_ptr, (size_t)ni + 1)) || (rc = dalloc(c, &c->d_kbi_ptr, (size_t)nb + 1)) ||
+    if ((rc = dupload(c, &c->d_gB, gB)) || (rc = dalloc(c, &c->d_kib_ptr, (size_t)ni + 1)) || (rc = dalloc(c, &c->d_kbi_ptr, (size_t)nb + 1)) ||
         (rc = dalloc(c, &d_tot, 2 * (size_t)nsub)) || (rc = dalloc(c, &dd, (size_t)nsub)))
         return rc;
     std::vector<CoupDesc> cd(nsub);
     ni = nb = 0;
     for (int i = 0; i < nsub; ++i) {
         const SubHost &sh = st.sub[i];
-        cd[i] = CoupDesc{c->d_K + k_off[i], sh.nloc, sh.nI, c->d_kib_ptr + ni, c->d_kbi_ptr + nb, 0, 0};
+        cd[i] = CoupDesc{c->d_K + k_off[i], sh.nloc, sh.nI, c->d_kib_ptr + ni, c->d_kbi_ptr + nb, 0, 0, c->d_gB + nb, (int32_t)ni};
         ni += sh.nI;
         nb += sh.nB;
     }
@@ -1927,7 +1928,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
     std::vector<int32_t> nI(nsub), nB(nsub), nc(nsub), i_off(nsub + 1, 0), b_off(nsub + 1, 0), c_off(nsub + 1, 0);
     std::vector<int64_t> k_off(nsub + 1, 0), s_off(nsub + 1, 0), kc_off(nsub + 1, 0),
         m_off(nsub + 1, 0), x_off(nsub + 1, 0), phr_off(nsub + 1, 0);
-    std::vector<int32_t> gB, nodesI, cidx, pos_sub;
+    std::vector<int32_t> nodesI, cidx, pos_sub;
     for (int i = 0; i < nsub; ++i) {
         const SubHost &sh = st.sub[i];
         nI[i] = sh.nI; nB[i] = sh.nB; nc[i] = (int)sh.cidx.size();
@@ -1941,7 +1942,6 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         m_off[i + 1] = m_off[i] + (int64_t)(sh.nB + nc[i]) * (sh.nB + nc[i]);
         x_off[i + 1] = x_off[i] + (int64_t)sh.nB * nc[i];
         phr_off[i + 1] = phr_off[i] + (int64_t)phi_ld(sh.nB) * nc[i];
-        gB.insert(gB.end(), sh.gB.begin(), sh.gB.end());
         nodesI.insert(nodesI.end(), sh.nodes.begin(), sh.nodes.begin() + sh.nI);
         cidx.insert(cidx.end(), sh.cidx.begin(), sh.cidx.end());
         pos_sub.insert(pos_sub.end(), sh.nB, i);
@@ -1958,6 +1958,16 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         c->n_pch = (int)ch_sub.size();
         if ((rc = dupload(c, &c->d_pch_sub, ch_sub)) || (rc = dupload(c, &c->d_pch_row, ch_row))) return rc;
     }
+    {   // blocks over interior rows
+        std::vector<int32_t> ch_sub, ch_row;
+        for (int i = 0; i < nsub; ++i)
+            for (int r = 0; r < nI[i]; r += 256) { ch_sub.push_back(i); ch_row.push_back(r); }
+        c->n_ich = (int)ch_sub.size();
+        c->n_int = i_off[nsub];
+        if ((rc = dupload(c, &c->d_ich_sub, ch_sub)) || (rc = dupload(c, &c->d_ich_row, ch_row)) ||
+            (rc = dalloc(c, &c->d_yI, (size_t)c->n_int)) || (rc = dalloc(c, &c->d_src, (size_t)c->n_nodes)))
+            return rc;
+    }
     c->h_nB = nB; c->h_nI = nI; c->h_nc = nc; c->h_pos_sub = pos_sub;
     c->h_b_off.assign(b_off.begin(), b_off.end() - 1);
     c->h_c_off.assign(c_off.begin(), c_off.end() - 1);
@@ -1965,10 +1975,11 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
         (rc = dupload(c, &c->d_i_off, i_off)) || (rc = dupload(c, &c->d_b_off, b_off)) ||
         (rc = dupload(c, &c->d_c_off, c_off)) || (rc = dupload(c, &c->d_k_off, k_off)) ||
         (rc = dupload(c, &c->d_s_off, s_off)) ||
-        (rc = dupload(c, &c->d_phr_off, phr_off)) || (rc = dupload(c, &c->d_gB, gB)) ||
+        (rc = dupload(c, &c->d_phr_off, phr_off)) ||
         (rc = dupload(c, &c->d_nodesI, nodesI)) || (rc = dupload(c, &c->d_cidx, cidx)) ||
         (rc = dupload(c, &c->d_gamma, st.gamma)) || (rc = dupload(c, &c->d_pos_sub, pos_sub)))
         return rc;
+    launch_node_src(c->n_nodes, c->n_int, c->d_nodesI, c->n_gamma, c->d_gamma, c->d_src, s);
     // interface assembly lists (owner-computes, ordered by subdomain)
     {
         std::vector<std::pair<int64_t, int32_t>> pr;
@@ -2308,7 +2319,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
     c->hcopy = std::min(c->hist_cap, c->save_cap + 2);
     if ((rc = dalloc(c, &c->d_b, ng)) || (rc = dalloc(c, &c->d_x, ng)) || (rc = dalloc(c, &c->d_r, ng)) ||
         (rc = dalloc(c, &c->d_z, ng)) || (rc = dalloc(c, &c->d_p, ng)) || (rc = dalloc(c, &c->d_tmp, ng)) ||
-        (rc = dalloc(c, &c->d_locq, (size_t)b_off[nsub])) || (rc = dalloc(c, &c->d_wloc, (size_t)b_off[nsub])) ||
+        (rc = dalloc(c, &c->d_wloc, (size_t)b_off[nsub])) ||
         (rc = dalloc(c, &c->d_rr, (size_t)c->vgrid)) || (rc = dalloc(c, &c->d_bbp, (size_t)c->vgrid)) ||
         (rc = dalloc(c, &c->d_zp, (size_t)c->vgrid * (RMAX + 1))) ||
         (rc = dalloc(c, &c->d_wp, (size_t)c->vgrid * (RMAX + 1))) ||

@@ -26,12 +26,15 @@ struct AsmDesc {
 };
 
 // Couplings K_IB, K_BI of one subdomain from its assembled matrix (row-major,
-// interior rows first): CSR rows at ib_ptr (nI of them) and bi_ptr (nloc - nI).
+// interior rows first): CSR rows at ib_ptr (nI of them) and bi_ptr (nloc - nI),
+// with columns numbered over the whole interface and over all interiors.
 struct CoupDesc {
     const double *K;
     int nloc, nI;
     int32_t *ib_ptr, *bi_ptr;
     int32_t ib0, bi0;               // the subdomain's first entry in the CSR arrays
+    const int32_t *gB;              // columns of K_IB: interface indices of its interface nodes
+    int32_t i_off;                  // columns of K_BI: i_off + local interior index
 };
 
 // ======================================================== operator products
@@ -249,31 +252,40 @@ struct L2Args {
 
 
 // ====================================================== per-solve kernels
-struct CondArgs {                   // t_i = K_BI y_I, y_I from the interior-product partials
-    const int32_t *nI, *nB, *i_off, *b_off;
-    const int32_t *nchunk, *pb;
+// Condensation and recovery of one right-hand side, or of several with one grid
+// row (blockIdx.y) each, ld* apart.
+struct IntSumArgs {                 // y_I summed over the segments of the interior product
+    const int32_t *ch_sub, *ch_row; // blocks: subdomain, first of up to 256 rows
+    const int32_t *nI, *nchunk, *pb, *i_off;
     const double *ypart;
-    const int32_t *kbi_ptr, *kbi_col;   // interface rows (b_off based), interior columns
+    double *y;                      // interior dof i_off + k
+};
+
+struct CondArgs {                   // b = F_G - sum_i R_i^T K_BI y_I; per-block ||b||^2
+    int n;                          // interface nodes
+    const int32_t *gamma, *ptr, *idx;   // node -> positions in the subdomains' interfaces
+    const int32_t *kbi_ptr, *kbi_col;   // rows: positions, columns: interior dofs
     const double *kbi_val;
-    double *t;
-};
-
-struct CondAsmArgs {
-    int n;
-    const int32_t *gamma, *ptr, *idx;
-    const double *F, *loc;
+    const double *F, *y;
     double *b, *part;
+    int64_t ldF, ldy, ldb, ldp;
 };
 
-struct RecArgs {                    // out[nodesI] = F_I - K_IB x_B; then u[nodesI] = y_I
-    const int32_t *nI, *nB, *i_off, *b_off, *nodesI, *gB;
-    const double *x, *F;
-    const int32_t *kib_ptr, *kib_col;   // interior rows (i_off based), interface columns
+struct RecRhsArgs {                 // out[nodesI] = F_I - K_IB x_B
+    int n;                          // interior dofs
+    const int32_t *nodesI, *kib_ptr, *kib_col;  // columns: interface nodes
     const double *kib_val;
+    const double *F, *x;
     double *out;
-    const int32_t *nchunk, *pb;
-    const double *ypart;
+    int64_t ldF, ldx, ldo;
+};
+
+struct RecOutArgs {                 // u = (x_I, x_G), 0 elsewhere
+    int64_t n;                      // nodes
+    const int32_t *src;             // interior dof q: q, interface node g: -2 - g, else -1
+    const double *y, *x;
     double *u;
+    int64_t ldy, ldx, ldu;
 };
 
 // Two products of the same shape (blockIdx.y picks one): out[y] = [V1[y], V2[y]] Y.
@@ -345,11 +357,12 @@ void launch_dense_copy(const DenseCopyDesc *d, int n, hipStream_t s);
 void launch_pad_rows(const double *src, int n, bool trans, double *dst, int64_t ldm, hipStream_t s);
 void launch_gather_sum(int64_t n, const int32_t *ptr, const int32_t *idx, const double *src, double *out, hipStream_t s);
 // per solve (kernels.hip)
-void launch_cond_local(const CondArgs &a, int nsub, int max_nI, hipStream_t s);
-void launch_cond_asm(const CondAsmArgs &a, int grid, hipStream_t s);
-void launch_rec_rhs(const RecArgs &a, int nsub, int max_nB, hipStream_t s);
-void launch_rec_out(const RecArgs &a, int nsub, hipStream_t s);
-void launch_scatter_gamma(int n, const int32_t *gamma, const double *x, double *u, hipStream_t s);
+void launch_int_sum(const IntSumArgs &a, int nblocks, hipStream_t s);
+void launch_condense(const CondArgs &a, int grid, int ncols, hipStream_t s);
+void launch_rec_rhs(const RecRhsArgs &a, int ncols, hipStream_t s);
+void launch_rec_out(const RecOutArgs &a, int ncols, hipStream_t s);
+void launch_node_src(int64_t n_nodes, int n_int, const int32_t *nodesI, int n_gamma, const int32_t *gamma, int32_t *src,
+                     hipStream_t s);
 void launch_recycle_gemm(const GemmArgs &a, hipStream_t s, int ny = 2);   // ny: outputs (1 or 2)
 void launch_gram(const GramArgs &a, int nblocks, hipStream_t s);
 

@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256) k_couple_fill(const CoupDesc *descs, int3
             const uint64_t b = __ballot(v != 0.0);
             if (v != 0.0) {
                 const int at = e + __popcll(b & ((1ull << l) - 1));
-                col[at] = c + l;
+                col[at] = in ? d.gB[c + l] : d.i_off + c + l;
                 val[at] = v;
             }
             e += __popcll(b);
@@ -390,74 +390,110 @@ __global__ void __launch_bounds__(256) k_gather_sum(int64_t n, const int32_t *pt
 // condensation and interior recovery (Section 3.1) with the packed interior
 // inverses (products in hot.hip's k_symv) and the sparse couplings K_IB, K_BI
 // ---------------------------------------------------------------------------
-// One block per subdomain: y_I summed from its work items into LDS, then
-// t_k = sum_a K_BI[k][a] y_I[a] for the interface rows.
-__global__ void __launch_bounds__(256) k_cond_local(CondArgs a) {
-    extern __shared__ double yI[];
-    const int i = blockIdx.x;
-    const int nI = a.nI[i], nB = a.nB[i], C = a.nchunk[i];
-    const double *yp = a.ypart + a.pb[i];
-    for (int k = threadIdx.x; k < nI; k += blockDim.x) {
-        double s = 0.0;
-        for (int q = 0; q < C; ++q) s += yp[(int64_t)q * nI + k];
-        yI[k] = s;
+// Every kernel runs over rows, whatever subdomain they belong to, with one grid
+// row per right-hand side: chains of a few dependent loads, so they need many
+// waves (one block per subdomain and one launch per right-hand side took 118 us
+// for the condensed rows, 113 for the interiors and 42 for the interior
+// right-hand sides on the holed 64^3 cube, whose largest interior has 3,370 rows
+// in dozens of segments; now 14 + 5, 5 + 5 and 10 us.  64^3, 16 right-hand sides
+// a launch: 6 + 5 + 4 us a side -> 6, 10 -> 5).
+
+// y_I from the interior product's segments, in segment order, eight at a time
+__global__ void __launch_bounds__(256) k_int_sum(IntSumArgs a) {
+    const int i = a.ch_sub[blockIdx.x], r = a.ch_row[blockIdx.x] + threadIdx.x, n = a.nI[i], C = a.nchunk[i];
+    if (r >= n) return;
+    const double *yp = a.ypart + a.pb[i] + r;
+    constexpr int U = 8;
+    double s = 0.0;
+    for (int c = 0; c < C; c += U) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = c + u < C ? yp[(int64_t)(c + u) * n] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c + u < C) s += v[u];
     }
-    __syncthreads();
-    const int boff = a.b_off[i];
-    for (int k = threadIdx.x; k < nB; k += blockDim.x) {
-        double s = 0.0;
-        for (int e = a.kbi_ptr[boff + k]; e < a.kbi_ptr[boff + k + 1]; ++e) s += a.kbi_val[e] * yI[a.kbi_col[e]];
-        a.t[boff + k] = s;
-    }
+    a.y[a.i_off[i] + r] = s;
 }
 
-// b = F_G - sum_i R_i^T t_i (grid-stride); per-block ||b||^2 partials
-__global__ void __launch_bounds__(256) k_cond_asm(CondAsmArgs a) {
+// sum of val[p] x[col[p]], p in [p0, p1), in order, four at a time
+__device__ __forceinline__ double csr_row(const int32_t *col, const double *val, const double *x, int p0, int p1) {
+    constexpr int U = 4;
+    double s = 0.0;
+    for (int p = p0; p < p1; p += U) {
+        int c[U];
+        double v[U], xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c[u] = p + u < p1 ? col[p + u] : -1;
+            v[u] = p + u < p1 ? val[p + u] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) xv[u] = c[u] >= 0 ? x[c[u]] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u] * xv[u];
+    }
+    return s;
+}
+
+// b = F_G - sum_i R_i^T (K_BI y_I) (grid-stride); per-block ||b||^2 partials
+__global__ void __launch_bounds__(256) k_condense(CondArgs a) {
     __shared__ double red[16];
+    const int64_t q = blockIdx.y;
+    const double *F = a.F + q * a.ldF, *y = a.y + q * a.ldy;
+    double *b = a.b + q * a.ldb;
     double bb = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < a.n; g += stride) {
-        double s = a.F[a.gamma[g]];
-        for (int k = a.ptr[g]; k < a.ptr[g + 1]; ++k) s -= a.loc[a.idx[k]];
-        a.b[g] = s;
+        const int e0 = a.ptr[g], e1 = a.ptr[g + 1];
+        double s = F[a.gamma[g]];
+        for (int e = e0; e < e1; e += 2) {   // two subdomains together (every node has at least two)
+            const int k0 = a.idx[e], k1 = e + 1 < e1 ? a.idx[e + 1] : -1;
+            const int p0 = a.kbi_ptr[k0], p1 = a.kbi_ptr[k0 + 1];
+            const int q0 = k1 >= 0 ? a.kbi_ptr[k1] : 0, q1 = k1 >= 0 ? a.kbi_ptr[k1 + 1] : 0;
+            const double t0 = csr_row(a.kbi_col, a.kbi_val, y, p0, p1), t1 = csr_row(a.kbi_col, a.kbi_val, y, q0, q1);
+            s -= t0;
+            if (k1 >= 0) s -= t1;
+        }
+        b[g] = s;
         bb += s * s;
     }
     bb = block_sum(bb, red);
-    if (threadIdx.x == 0) a.part[blockIdx.x] = bb;
+    if (threadIdx.x == 0) a.part[q * a.ldp + blockIdx.x] = bb;
 }
 
-// One block per subdomain: out[nodesI] = F_I - K_IB x_B (the interior
-// right-hand side of the recovery, written at the subdomain's own nodes).
-__global__ void __launch_bounds__(256) k_rec_rhs(RecArgs a) {
-    extern __shared__ double xB[];
-    const int i = blockIdx.x;
-    const int nI = a.nI[i], nB = a.nB[i];
-    const int boff = a.b_off[i], ioff = a.i_off[i];
-    for (int k = threadIdx.x; k < nB; k += blockDim.x) xB[k] = a.x[a.gB[boff + k]];
-    __syncthreads();
-    for (int r = threadIdx.x; r < nI; r += blockDim.x) {
-        const int node = a.nodesI[ioff + r];
-        double s = a.F[node];
-        for (int e = a.kib_ptr[ioff + r]; e < a.kib_ptr[ioff + r + 1]; ++e) s -= a.kib_val[e] * xB[a.kib_col[e]];
-        a.out[node] = s;
-    }
+// out[nodesI] = F_I - K_IB x_B (the interior right-hand side of the recovery,
+// at the subdomains' own nodes)
+__global__ void __launch_bounds__(256) k_rec_rhs(RecRhsArgs a) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= a.n) return;
+    const int64_t q = blockIdx.y;
+    const int node = a.nodesI[r], p0 = a.kib_ptr[r], p1 = a.kib_ptr[r + 1];
+    const double f = a.F[q * a.ldF + node];
+    a.out[q * a.ldo + node] = f - csr_row(a.kib_col, a.kib_val, a.x + q * a.ldx, p0, p1);
 }
 
-// u[nodesI] = x_I summed from the interior product's work items.
-__global__ void __launch_bounds__(256) k_rec_out(RecArgs a) {
-    const int i = blockIdx.x;
-    const int nI = a.nI[i], C = a.nchunk[i], ioff = a.i_off[i];
-    const double *yp = a.ypart + a.pb[i];
-    for (int r = threadIdx.x; r < nI; r += blockDim.x) {
-        double s = 0.0;
-        for (int q = 0; q < C; ++q) s += yp[(int64_t)q * nI + r];
-        a.u[a.nodesI[ioff + r]] = s;
-    }
+// u = x_I at the interior nodes, x_G at the interface nodes, 0 elsewhere, node
+// by node (whole lines written once)
+__global__ void __launch_bounds__(256) k_rec_out(RecOutArgs a) {
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= a.n) return;
+    const int64_t q = blockIdx.y;
+    const int s = a.src[n];
+    a.u[q * a.ldu + n] = s >= 0 ? a.y[q * a.ldy + s] : s == -1 ? 0.0 : a.x[q * a.ldx - 2 - s];
 }
 
-__global__ void __launch_bounds__(256) k_scatter_gamma(int n, const int32_t *gamma, const double *x, double *u) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < n) u[gamma[g]] = x[g];
+// setup: the source of every node's value, for k_rec_out (-1 everywhere, then
+// the interior and interface nodes)
+__global__ void __launch_bounds__(256) k_node_none(int64_t n, int32_t *src) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) src[t] = -1;
+}
+__global__ void __launch_bounds__(256) k_node_src(int n_int, const int32_t *nodesI, int n_gamma, const int32_t *gamma,
+                                                  int32_t *src) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n_int) src[nodesI[t]] = t;
+    if (t < n_gamma) src[gamma[t]] = -2 - t;
 }
 
 // ---------------------------------------------------------------------------
@@ -824,20 +860,23 @@ void launch_pad_rows(const double *src, int n, bool trans, double *dst, int64_t 
 void launch_gather_sum(int64_t n, const int32_t *ptr, const int32_t *idx, const double *src, double *out, hipStream_t s) {
     if (n > 0) hipLaunchKernelGGL(k_gather_sum, dim3(nblk(n, 256)), dim3(256), 0, s, n, ptr, idx, src, out);
 }
-void launch_cond_local(const CondArgs &a, int nsub, int max_nI, hipStream_t s) {
-    hipLaunchKernelGGL(k_cond_local, dim3(nsub), dim3(256), (size_t)std::max(1, max_nI) * 8, s, a);
+void launch_int_sum(const IntSumArgs &a, int nblocks, hipStream_t s) {
+    if (nblocks > 0) hipLaunchKernelGGL(k_int_sum, dim3(nblocks), dim3(256), 0, s, a);
 }
-void launch_cond_asm(const CondAsmArgs &a, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_cond_asm, dim3(grid), dim3(256), 0, s, a);
+void launch_condense(const CondArgs &a, int grid, int ncols, hipStream_t s) {
+    hipLaunchKernelGGL(k_condense, dim3(grid, ncols), dim3(256), 0, s, a);
 }
-void launch_rec_rhs(const RecArgs &a, int nsub, int max_nB, hipStream_t s) {
-    hipLaunchKernelGGL(k_rec_rhs, dim3(nsub), dim3(256), (size_t)std::max(1, max_nB) * 8, s, a);
+void launch_rec_rhs(const RecRhsArgs &a, int ncols, hipStream_t s) {
+    if (a.n > 0) hipLaunchKernelGGL(k_rec_rhs, dim3(nblk(a.n, 256), ncols), dim3(256), 0, s, a);
 }
-void launch_rec_out(const RecArgs &a, int nsub, hipStream_t s) {
-    hipLaunchKernelGGL(k_rec_out, dim3(nsub), dim3(256), 0, s, a);
+void launch_rec_out(const RecOutArgs &a, int ncols, hipStream_t s) {
+    hipLaunchKernelGGL(k_rec_out, dim3(nblk(a.n, 256), ncols), dim3(256), 0, s, a);
 }
-void launch_scatter_gamma(int n, const int32_t *gamma, const double *x, double *u, hipStream_t s) {
-    if (n > 0) hipLaunchKernelGGL(k_scatter_gamma, dim3(nblk(n, 256)), dim3(256), 0, s, n, gamma, x, u);
+void launch_node_src(int64_t n_nodes, int n_int, const int32_t *nodesI, int n_gamma, const int32_t *gamma, int32_t *src,
+                     hipStream_t s) {
+    hipLaunchKernelGGL(k_node_none, dim3(nblk(n_nodes, 256)), dim3(256), 0, s, n_nodes, src);
+    const int m = std::max(n_int, n_gamma);
+    if (m > 0) hipLaunchKernelGGL(k_node_src, dim3(nblk(m, 256)), dim3(256), 0, s, n_int, nodesI, n_gamma, gamma, src);
 }
 void launch_recycle_gemm(const GemmArgs &a, hipStream_t s, int ny) {
     if (a.n <= 0) return;
