@@ -577,7 +577,11 @@ void run_l2_chain(const bddc_ctx *c, const L2Args &l, hipStream_t st) {
 }
 
 void run_coarse(bddc_ctx *c, hipStream_t st);
-void run_prolong_assemble(bddc_ctx *c, const double *r, double *z, bool gated, bool advance, bool reduce);
+void run_prolong_assemble(bddc_ctx *c, const double *r, double *z, bool gated, bool advance, bool reduce, bool fused);
+
+// Small dense coarse spaces: the prolongation's blocks solve the coarse problem
+// themselves (not while the kernel classes are timed; same results).
+bool fuse_coarse(const bddc_ctx *c) { return c->coarse_dense && c->nC > 0 && c->nC <= FUSED_MAX_NC && !c->timing; }
 
 // Coarse restriction of a single-vector Neumann product: the first segment
 // of every subdomain writes c_i = (D Phi_i)^T x_i (none without a coarse space).
@@ -611,8 +615,9 @@ void run_precond(bddc_ctx *c, const double *r, double *z, int test, bool gated, 
         set_restriction(c, a);
         launch_symv(a, SYMV_NEUMANN, c->prec, c->opN.cfg, c->opN.smem, c->stream);
     }
-    run_coarse(c, c->stream);
-    run_prolong_assemble(c, r, z, gated, advance, reduce);
+    const bool fused = fuse_coarse(c);
+    if (!fused) run_coarse(c, c->stream);
+    run_prolong_assemble(c, r, z, gated, advance, reduce, fused);
 }
 
 // Coarse levels of one BDDC application on stream st: the coarse residual
@@ -649,11 +654,16 @@ ProlArgs prolong_args(const bddc_ctx *c, bool gated) {
 
 // Prolongation w_i = u_i + D Phi_i u_C and assembly z = sum_i R_i^T w_i
 // (eq. averaging_subdomain_solves), with the (r^T z, (AW)^T z) partials when
-// `reduce` is set.
-void run_prolong_assemble(bddc_ctx *c, const double *r, double *z, bool gated, bool advance, bool reduce) {
+// `reduce` is set; `fused`: with the coarse solve (u_C is not written).
+void run_prolong_assemble(bddc_ctx *c, const double *r, double *z, bool gated, bool advance, bool reduce, bool fused) {
     {
         TScope ts(c, TK_VEC);
-        const ProlArgs pa = prolong_args(c, gated);
+        ProlArgs pa = prolong_args(c, gated);
+        if (fused) {
+            pa.fused = 1;
+            pa.nC = c->nC; pa.rc = Gather{c->d_casm_ptr, c->d_casm_idx, c->d_crest};
+            pa.M = c->d_Mc; pa.ldm = c->ldm; pa.sign = c->three ? 1.0 : -1.0;
+        }
         launch_prolong(pa, c->prec, c->n_pch, c->max_nc, c->stream);
         ZasmArgs a{};
         a.n = c->n_gamma;
@@ -3300,7 +3310,7 @@ int bddc_time_kernels(bddc_ctx *c, int32_t reps, double *out, int32_t n) {
     const double cb = coarse_bytes(c), pb = prolong_bytes(c);
     timed(3, c->opN.bytes + cb + pb, [&] { run_precond(c, c->d_r, c->d_tmp, 0, false, false, false); });
     timed(4, cb, [&] { run_coarse(c, c->stream); });
-    timed(5, pb, [&] { run_prolong_assemble(c, c->d_r, c->d_tmp, false, false, false); });
+    timed(5, pb, [&] { run_prolong_assemble(c, c->d_r, c->d_tmp, false, false, false, false); });
     c->timing = tk;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

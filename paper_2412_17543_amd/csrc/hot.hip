@@ -729,7 +729,16 @@ __device__ __forceinline__ double ld_rc_as<uint16_t>(__amdgpu_buffer_rsrc_t r, i
     return (double)dev::bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, i * 2, 0, 0));
 }
 
-template <typename T>
+// FUSED (dense coarse operators of up to FUSED_MAX_NC rows, one column): the
+// block computes the entries of u_C that its subdomain needs from the coarse
+// partials, a wave per entry with the operands of four entries requested
+// before r_C is gathered, in the summation order of k_coarse_rhs and
+// k_coarse_dense, whose two launches (about 6 us, whatever the size) it
+// replaces.  One preconditioner application: 18 coarse DOFs (16^3) 19.8 -> 16.1
+// us, 82 24.1 -> 20.0, 216 (32^3) 28.0 -> 23.8, 444 37.8 -> 33.9.  Above, every
+// block's rows of M (nc_i nC entries) cost what the launches do: with room for
+// 2,048 columns 790 DOFs take 45.8 us either way, 1,932 take 45.9 against 31.7.
+template <typename T, bool FUSED>
 __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
     extern __shared__ double uCl[];
     constexpr int PF = 16, CF = 4;      // basis entries / partials of a row requested early
@@ -767,7 +776,48 @@ __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
         pr0[q] = ld_rc_as<T>(pr, q * ld + k0);
         pr1[q] = ld_rc_as<T>(pr, q * ld + k1);
     }
-    for (int q = threadIdx.x; q < nci; q += blockDim.x) uCl[q] = a.uC[ci[q]];
+    if constexpr (FUSED) {
+        constexpr int EG = 4;
+        __shared__ double rs[FUSED_MAX_NC];
+        const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, ldm = (int)a.ldm;
+        const __amdgpu_buffer_rsrc_t mr = tile_rsrc(a.M, a.nC * ldm * 8);
+        uvec4 m[EG][4];
+        auto request = [&](int q0) {                   // entries q0, q0 + 4, ... (past the last: zeros, no access)
+#pragma unroll
+            for (int j = 0; j < EG; ++j) {
+                const int q = q0 + 4 * j, row = q < nci ? ci[q] : a.nC;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int col = 2 * l + 128 * u;
+                    m[j][u] = __builtin_amdgcn_raw_buffer_load_b128(mr, (col < ldm ? row * ldm + col : a.nC * ldm) * 8, 0, 0);
+                }
+            }
+        };
+        request(wv);
+        for (int q = threadIdx.x; q < FUSED_MAX_NC; q += 256) rs[q] = q < a.nC ? gather_sum(a.rc, q) : 0.0;
+        __syncthreads();
+        for (int q0 = wv; q0 < nci; q0 += 4 * EG) {
+            if (q0 != wv) request(q0);
+#pragma unroll
+            for (int j = 0; j < EG; ++j) {
+                double s[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int col = 2 * l + 128 * u;
+                    s[u] = __hiloint2double(m[j][u].y, m[j][u].x) * rs[col] + __hiloint2double(m[j][u].w, m[j][u].z) * rs[col + 1];
+                }
+                const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+                if (l == 0 && q0 + 4 * j < nci) uCl[q0 + 4 * j] = a.sign * t;
+            }
+        }
+        // (a wave without entries leaves its first requests unused: none outstanding at exit)
+#pragma unroll
+        for (int j = 0; j < EG; ++j)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(m[j][u]));
+    } else {
+        for (int q = threadIdx.x; q < nci; q += blockDim.x) uCl[q] = a.uC[ci[q]];
+    }
     __syncthreads();
     // w = sum of the partials, then the basis terms, in column order
     auto row = [&](int k, const double (&u)[CF], const double (&r)[PF]) {
@@ -1409,9 +1459,13 @@ void launch_update(const UpdArgs &a, int grid, hipStream_t s) {
 void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s, int ncols) {
     const size_t smem = (size_t)std::max(1, max_nc) * 8;
     const dim3 grid(nblocks, ncols);
-    if (prec == 64) hipLaunchKernelGGL(k_prolong<double>, grid, dim3(256), smem, s, a);
-    else if (prec == 32) hipLaunchKernelGGL(k_prolong<float>, grid, dim3(256), smem, s, a);
-    else hipLaunchKernelGGL(k_prolong<uint16_t>, grid, dim3(256), smem, s, a);
+    if (a.fused) {
+        if (prec == 64) hipLaunchKernelGGL((k_prolong<double, true>), grid, dim3(256), smem, s, a);
+        else if (prec == 32) hipLaunchKernelGGL((k_prolong<float, true>), grid, dim3(256), smem, s, a);
+        else hipLaunchKernelGGL((k_prolong<uint16_t, true>), grid, dim3(256), smem, s, a);
+    } else if (prec == 64) hipLaunchKernelGGL((k_prolong<double, false>), grid, dim3(256), smem, s, a);
+    else if (prec == 32) hipLaunchKernelGGL((k_prolong<float, false>), grid, dim3(256), smem, s, a);
+    else hipLaunchKernelGGL((k_prolong<uint16_t, false>), grid, dim3(256), smem, s, a);
 }
 
 int kmax_bucket(int k) { return k == 0 ? 0 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : k <= 48 ? 48 : 64; }

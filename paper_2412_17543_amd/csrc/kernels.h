@@ -126,7 +126,14 @@ struct ProlArgs {                   // w_i = u_i + D Phi_i u_C (eq. averaging_su
     double *wloc;
     const int32_t *ch_sub, *ch_row; // block b: subdomain ch_sub[b], rows ch_row[b] .. +511
     int64_t cs_u, cs_uC, cs_w;      // several columns (blockIdx.y): strides of upart, uC, wloc
+    // small dense coarse spaces (`fused`): every block forms the entries of u_C
+    // that it needs itself, u_C = sign M r_C, r_C from the coarse partials
+    int fused, nC;
+    Gather rc;
+    const double *M; int64_t ldm;
+    double sign;
 };
+constexpr int FUSED_MAX_NC = 512;
 
 struct ZasmArgs {                   // z = sum_i R_i^T w_i, rho, (AW)^T z
     int n;

@@ -80,3 +80,25 @@ def test_local_operators(nx, part):
     U, its, rr = g.solve_sequence(torch.tensor(F, device="cuda"), 1e-12)
     uo, _, _ = o.solve_sequence(F, 1e-12)
     assert np.abs(U[0].cpu().numpy() - uo[0]).max() <= 1e-10 * np.abs(uo[0]).max()
+
+
+@pytest.mark.parametrize("nx,part,cons,prec", [
+    (8, _box(8, 2), ("corners", "faces"), 64),                 # 18 coarse DOFs
+    (24, "c3s", ("corners", "edges"), 32),                    # an odd count, uneven subdomains
+    (40, _box(40, 5), ("corners", "faces"), 16),               # 444: two passes of r_C, several groups of rows
+    (20, _box(20, 5), ("corners", "faces", "edges"), 64),      # above the limit: both calls the separate kernels
+])
+def test_coarse_solve_inside_the_prolongation(nx, part, cons, prec):
+    """Small coarse spaces are solved by the prolongation's own blocks, in the
+    summation order of the separate kernels (which run while the kernel classes
+    are timed): bitwise equal."""
+    torch = _torch()
+    from paper_2412_17543_amd.solver import Solver
+    s = workload.workload("c3s") if isinstance(part, str) else dict(elem_to_sub=part, sub_to_subregion=None, elem_keep=None)
+    g = Solver(nx, s["elem_to_sub"], workload.lognormal_coef(nx ** 3, 0.5), sub_to_subregion=s["sub_to_subregion"],
+               elem_keep=s["elem_keep"], constraints=cons, local_prec=prec, autotune=False)
+    print("[gpu] coarse solve in the prolongation: %d^3, %d coarse DOFs" % (nx, g.info()["n_coarse"]), flush=True)
+    r = torch.randn(g.n_gamma, dtype=torch.float64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    z = g.apply_precond(r)
+    g.enable_timing(True)
+    assert torch.equal(z, g.apply_precond(r))
