@@ -709,64 +709,70 @@ __global__ void k_set_state(RecState *st, int k, int ok) {
     if (threadIdx.x == 0) { st->k = k; st->ok = ok; }
 }
 
-// One wave: symmetrise the new W^T A W and invert it in LDS by a symmetric
+// One wave: symmetrise the new W^T A W and invert it by a symmetric
 // Gauss-Jordan sweep of all pivots (lane t owns row t; after the sweep the
 // matrix holds -(W^T A W)^{-1}).  Every pivot of a symmetric positive
 // definite matrix is positive (it is a diagonal entry of a Schur
 // complement), so state->ok = 1 exactly when the matrix is positive definite
 // (Section 4.1: W^T A W must be invertible for the projection of
-// eq. projectionQ).  k <= RMAX = 64.
+// eq. projectionQ).  k <= KM <= RMAX = 64.  The chain of pivots is what it
+// costs: rows in registers, the pivot's row (by symmetry its column too)
+// broadcast through LDS, KM multiply-adds a pivot (every row in LDS, read and
+// written back a pivot: 53 us for 20 columns, 176 for 40; now 24 and 77).
+template <int KM>
 __global__ void __launch_bounds__(64) k_chol_inv(CholArgs a) {
-    __shared__ double A[RMAX][RMAX + 1];
-    __shared__ double row[RMAX];
+    __shared__ double A[KM][KM + 1];
+    __shared__ double row[2][KM];
     const int k = a.k, t = threadIdx.x;
+    double v[KM];
     // lane t reads row t (all loads issued before any store), then the
-    // symmetric part is formed in LDS
+    // symmetric part is formed through LDS
+#pragma unroll
+    for (int j = 0; j < KM; ++j) v[j] = t < k && j < k ? a.waw[t * k + j] : 0.0;
+    if (t < KM) {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) A[t][j] = v[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KM; ++j) v[j] = t < k ? 0.5 * (v[j] + A[j][t < KM ? t : 0]) : 0.0;
     if (t < k) {
-        double v[RMAX];
 #pragma unroll
-        for (int j = 0; j < RMAX; ++j) v[j] = j < k ? a.waw[t * k + j] : 0.0;
-#pragma unroll
-        for (int j = 0; j < RMAX; ++j) A[t][j] = v[j];
+        for (int j = 0; j < KM; ++j)
+            if (j < k) a.waw_sym[t * k + j] = v[j];
     }
-    __syncthreads();
-    {
-        double v[RMAX];
-#pragma unroll
-        for (int j = 0; j < RMAX; ++j) v[j] = (t < k) ? 0.5 * (A[t][j] + A[j][t]) : 0.0;
-        __syncthreads();
-        if (t < k) {
-#pragma unroll
-            for (int j = 0; j < RMAX; ++j) A[t][j] = v[j];
-#pragma unroll
-            for (int j = 0; j < RMAX; ++j)
-                if (j < k) a.waw_sym[t * k + j] = v[j];
-        }
-    }
-    __syncthreads();
     for (int p = 0; p < k; ++p) {
-        if (t < k) row[t] = A[p][t];
+        double *rp = row[p & 1];
+        if (t == p) {
+#pragma unroll
+            for (int j = 0; j < KM; ++j) rp[j] = v[j];
+        }
         __syncthreads();
-        const double piv = row[p];
+        const double piv = rp[p];
         if (!(piv > 0.0 && isfinite(piv))) {     // the same value in every lane
             if (t == 0) a.state->ok = 0;
             return;
         }
         const double inv = 1.0 / piv;
-        if (t < k) {
-            if (t == p) {
-                for (int j = 0; j < k; ++j) A[p][j] = (j == p) ? -inv : row[j] * inv;
-            } else {
-                const double f = row[t] * inv;     // A(t, p) = A(p, t) by symmetry
-                for (int j = 0; j < k; ++j) A[t][j] = (j == p) ? f : A[t][j] - f * row[j];
-            }
+        // row p itself: 0 - (-1/piv) row; the others: v - (r_t / piv) row
+        const double f = t == p ? -inv : rp[t < KM ? t : 0] * inv;
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            const double b = t == p ? 0.0 : v[j];
+            v[j] = j == p ? f : b - f * rp[j];
         }
-        __syncthreads();
     }
+    // -(the symmetric part)
+    __syncthreads();
+    if (t < KM) {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) A[t][j] = v[j];
+    }
+    __syncthreads();
     if (t < k) {
 #pragma unroll
-        for (int j = 0; j < RMAX; ++j)
-            if (j < k) a.inv[t * k + j] = -0.5 * (A[t][j] + A[j][t]);
+        for (int j = 0; j < KM; ++j)
+            if (j < k) a.inv[t * k + j] = -0.5 * (v[j] + A[j][t]);
     }
     if (t == 0) a.state->ok = 1;
 }
@@ -919,7 +925,9 @@ void launch_set_state(RecState *state, int k, int ok, hipStream_t s) {
     hipLaunchKernelGGL(k_set_state, dim3(1), dim3(64), 0, s, state, k, ok);
 }
 void launch_chol_inv(const CholArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(64), 0, s, a);
+    if (a.k <= 24) hipLaunchKernelGGL(k_chol_inv<24>, dim3(1), dim3(64), 0, s, a);
+    else if (a.k <= 40) hipLaunchKernelGGL(k_chol_inv<40>, dim3(1), dim3(64), 0, s, a);
+    else hipLaunchKernelGGL(k_chol_inv<RMAX>, dim3(1), dim3(64), 0, s, a);
 }
 void launch_commit(const CommitArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_commit, dim3(1), dim3(256), 0, s, a);
