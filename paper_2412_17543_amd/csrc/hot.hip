@@ -900,7 +900,10 @@ __global__ void __launch_bounds__(256) k_zasm(ZasmArgs a) {
 // mu for the recycling step.  `hist_only` records without updating p (the
 // extra preconditioner application after convergence).
 // ---------------------------------------------------------------------------
-template <int KM>
+// The partials (at most VGRID = 2 x 256 a column) and the operands of the
+// thread's first UN nodes are all requested before the first wait (90^3, 20
+// columns: 17.6 -> 15.9 us; two nodes a pass gained nothing in the assembly).
+template <int KM, int UN>
 __global__ void __launch_bounds__(256) k_pupd(PupdArgs a) {
     __shared__ double lds[16 * 256];
     __shared__ double tv[KM + 1];
@@ -918,27 +921,39 @@ __global__ void __launch_bounds__(256) k_pupd(PupdArgs a) {
                       a.res_hist, a.hist_cap))
             hist_only = true;
     }
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double z0 = 0.0, p0 = 0.0, w0[KM > 0 ? KM : 1];
+    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    static_assert(VGRID <= 512, "two partials a thread and column");
+    double z0[UN], p0[UN], w0[UN][KM > 0 ? KM : 1];
+    // columns q >= k and nodes past n read as zero through the range check, so
+    // every load is unconditional
+    const __amdgpu_buffer_rsrc_t wr = vec_rsrc(a.W, (int64_t)k * a.ld);
+    auto fetch = [&](int64_t gb) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t g = gb + u * stride;
+            const bool ok = g < a.n;
+            z0[u] = ok ? a.z[g] : 0.0;
+            p0[u] = ok ? a.p[g] : 0.0;
+#pragma unroll
+            for (int q = 0; q < KM; ++q) w0[u][q] = ld_rc(wr, ok ? (int64_t)q * a.ld + g : (int64_t)k * a.ld);
+        }
+    };
     {
-        double acc[KM + 1];
+        double acc[KM + 1], ac2[KM + 1];
+        const int64_t zend = (int64_t)(k + 1) * a.zpart_n;
+        const __amdgpu_buffer_rsrc_t zr = vec_rsrc(a.zpart, zend);
+        const int b0 = threadIdx.x, b1 = threadIdx.x + 256;
 #pragma unroll
-        for (int q = 0; q <= KM; ++q) acc[q] = 0.0;
-        const __amdgpu_buffer_rsrc_t zr = vec_rsrc(a.zpart, (int64_t)(k + 1) * a.zpart_n);
-        for (int b = threadIdx.x; b < a.zpart_n; b += blockDim.x) {
+        for (int q = 0; q <= KM; ++q) acc[q] = ld_rc(zr, b0 < a.zpart_n ? (int64_t)q * a.zpart_n + b0 : zend);
+        if (a.zpart_n > 256) {
 #pragma unroll
-            for (int q = 0; q <= KM; ++q) acc[q] += ld_rc(zr, (int64_t)q * a.zpart_n + b);
+            for (int q = 0; q <= KM; ++q) ac2[q] = ld_rc(zr, b1 < a.zpart_n ? (int64_t)q * a.zpart_n + b1 : zend);
+#pragma unroll
+            for (int q = 0; q <= KM; ++q) acc[q] += ac2[q];
         }
-        // the operands of this thread's first node do not depend on beta and
-        // mu: their loads overlap the reductions (columns q >= k read as zero
-        // through the range check, so every load is unconditional)
-        if (!hist_only && g0 < a.n) {
-            z0 = a.z[g0];
-            p0 = a.p[g0];
-            const __amdgpu_buffer_rsrc_t wr = vec_rsrc(a.W, (int64_t)k * a.ld);
-#pragma unroll
-            for (int q = 0; q < KM; ++q) w0[q] = ld_rc(wr, (int64_t)q * a.ld + g0);
-        }
+        // the operands of this thread's first nodes do not depend on beta and
+        // mu: their loads overlap the reductions
+        if (!hist_only) fetch(g0);
         for (int e = threadIdx.x; e < k * k; e += blockDim.x) wawi[e] = a.WAWinv[e];
         block_sum_cols<KM + 1>(acc, k + 1, lds, tv);
     }
@@ -958,28 +973,21 @@ __global__ void __launch_bounds__(256) k_pupd(PupdArgs a) {
     }
     if (hist_only || bad) return;
     const bool rec = a.P && c->record && j < a.cap;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (g0 < a.n) {
-        double p = z0 + beta * p0;
+    // all loads of a pass issued at once; summation in column order
+    for (int64_t gb = g0; gb < a.n; gb += UN * stride) {
+        if (gb != g0) fetch(gb);
 #pragma unroll
-        for (int q = 0; q < KM; ++q)
-            if (q < k) p -= w0[q] * mu[q];
-        a.p[g0] = p;
-        if (rec) a.P[(int64_t)j * a.ld + g0] = p;
-    }
-    // the other nodes the same way: all KM loads of a node issued at once
-    // (columns q >= k read as zero without an access), same summation order
-    const __amdgpu_buffer_rsrc_t wr = vec_rsrc(a.W, (int64_t)k * a.ld);
-    for (int64_t g = g0 + stride; g < a.n; g += stride) {
-        double w[KM > 0 ? KM : 1];
+        for (int u = 0; u < UN; ++u) {
+            const int64_t g = gb + u * stride;
+            double p = z0[u] + beta * p0[u];
 #pragma unroll
-        for (int q = 0; q < KM; ++q) w[q] = ld_rc(wr, (int64_t)q * a.ld + g);
-        double p = a.z[g] + beta * a.p[g];
-#pragma unroll
-        for (int q = 0; q < KM; ++q)
-            if (q < k) p -= w[q] * mu[q];
-        a.p[g] = p;
-        if (rec) a.P[(int64_t)j * a.ld + g] = p;
+            for (int q = 0; q < KM; ++q)
+                if (q < k) p -= w0[u][q] * mu[q];
+            if (g < a.n) {
+                a.p[g] = p;
+                if (rec) a.P[(int64_t)j * a.ld + g] = p;
+            }
+        }
     }
 }
 
@@ -1468,76 +1476,61 @@ void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStr
     else hipLaunchKernelGGL((k_prolong<uint16_t, false>), grid, dim3(256), smem, s, a);
 }
 
-int kmax_bucket(int k) { return k == 0 ? 0 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : k <= 48 ? 48 : 64; }
+// Registers and loads are laid out for KM columns: buckets of 8 up to 48 (a
+// basis of 20 in a bucket of 32 issues 12 loads a node for nothing, one of 40
+// in a bucket of 48 8: 192^3 direction update 133 -> 122 us, assembly 147 -> 140).
+int kmax_bucket(int k) { return k <= 48 ? (k + 7) / 8 * 8 : 64; }
 
-void launch_zasm(const ZasmArgs &a, int kmax, int grid, hipStream_t s, int ncols) {
-    switch (kmax) {
-        case 0: hipLaunchKernelGGL(k_zasm<0>, dim3(grid, ncols), dim3(256), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(k_zasm<8>, dim3(grid, ncols), dim3(256), 0, s, a); break;
-        case 16: hipLaunchKernelGGL(k_zasm<16>, dim3(grid, ncols), dim3(256), 0, s, a); break;
-        case 32: hipLaunchKernelGGL(k_zasm<32>, dim3(grid, ncols), dim3(256), 0, s, a); break;
-        case 48: hipLaunchKernelGGL(k_zasm<48>, dim3(grid, ncols), dim3(256), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_zasm<64>, dim3(grid, ncols), dim3(256), 0, s, a); break;
+#define KM_SWITCH(kmax, CALL)            \
+    switch (kmax) {                      \
+        case 0: CALL(0); break;          \
+        case 8: CALL(8); break;          \
+        case 16: CALL(16); break;        \
+        case 24: CALL(24); break;        \
+        case 32: CALL(32); break;        \
+        case 40: CALL(40); break;        \
+        case 48: CALL(48); break;        \
+        default: CALL(64); break;        \
     }
+void launch_zasm(const ZasmArgs &a, int kmax, int grid, hipStream_t s, int ncols) {
+#define ZASM(KM) hipLaunchKernelGGL(k_zasm<KM>, dim3(grid, ncols), dim3(256), 0, s, a)
+    KM_SWITCH(kmax, ZASM)
+#undef ZASM
 }
 
+// nodes per pass of the direction update: two where a thread has more than
+// one, up to 24 columns (227 registers; two blocks a compute unit)
+template <int KM>
+constexpr int pupd_nodes() { return KM <= 24 ? 2 : 1; }
+
 void launch_pupd(const PupdArgs &a, int kmax, int grid, hipStream_t s) {
-    switch (kmax) {
-        case 0: hipLaunchKernelGGL(k_pupd<0>, dim3(grid), dim3(256), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(k_pupd<8>, dim3(grid), dim3(256), 0, s, a); break;
-        case 16: hipLaunchKernelGGL(k_pupd<16>, dim3(grid), dim3(256), 0, s, a); break;
-        case 32: hipLaunchKernelGGL(k_pupd<32>, dim3(grid), dim3(256), 0, s, a); break;
-        case 48: hipLaunchKernelGGL(k_pupd<48>, dim3(grid), dim3(256), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_pupd<64>, dim3(grid), dim3(256), 0, s, a); break;
-    }
+    const bool two = a.n > (int64_t)grid * 256;
+#define PUPD(KM)                                                                                      \
+    if (two) hipLaunchKernelGGL((k_pupd<KM, pupd_nodes<KM>()>), dim3(grid), dim3(256), 0, s, a);       \
+    else hipLaunchKernelGGL((k_pupd<KM, 1>), dim3(grid), dim3(256), 0, s, a)
+    KM_SWITCH(kmax, PUPD)
+#undef PUPD
 }
 
 void launch_resid(const ResidArgs &a, int kmax, int grid, hipStream_t s) {
-    switch (kmax) {
-        case 0: hipLaunchKernelGGL(k_resid<0>, dim3(grid), dim3(256), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(k_resid<8>, dim3(grid), dim3(256), 0, s, a); break;
-        case 16: hipLaunchKernelGGL(k_resid<16>, dim3(grid), dim3(256), 0, s, a); break;
-        case 32: hipLaunchKernelGGL(k_resid<32>, dim3(grid), dim3(256), 0, s, a); break;
-        case 48: hipLaunchKernelGGL(k_resid<48>, dim3(grid), dim3(256), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_resid<64>, dim3(grid), dim3(256), 0, s, a); break;
-    }
+#define RESID(KM) hipLaunchKernelGGL(k_resid<KM>, dim3(grid), dim3(256), 0, s, a)
+    KM_SWITCH(kmax, RESID)
+#undef RESID
 }
 
 void launch_defl_init(const DeflArgs &a, int kmax, int grid, hipStream_t s) {
-    switch (kmax) {
-        case 0: hipLaunchKernelGGL(k_defl_init<0>, dim3(grid), dim3(256), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(k_defl_init<8>, dim3(grid), dim3(256), 0, s, a); break;
-        case 16: hipLaunchKernelGGL(k_defl_init<16>, dim3(grid), dim3(256), 0, s, a); break;
-        case 32: hipLaunchKernelGGL(k_defl_init<32>, dim3(grid), dim3(256), 0, s, a); break;
-        case 48: hipLaunchKernelGGL(k_defl_init<48>, dim3(grid), dim3(256), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_defl_init<64>, dim3(grid), dim3(256), 0, s, a); break;
-    }
+#define DEFL(KM) hipLaunchKernelGGL(k_defl_init<KM>, dim3(grid), dim3(256), 0, s, a)
+    KM_SWITCH(kmax, DEFL)
+#undef DEFL
 }
 
 void launch_reorth(const ReorthArgs &a, int kmax, int grid, hipStream_t s) {
-    switch (kmax) {
-        case 0: break;
-        case 8:
-            hipLaunchKernelGGL(k_wtr<8>, dim3(grid), dim3(256), 0, s, a);
-            hipLaunchKernelGGL(k_reorth<8>, dim3(grid), dim3(256), 0, s, a);
-            break;
-        case 16:
-            hipLaunchKernelGGL(k_wtr<16>, dim3(grid), dim3(256), 0, s, a);
-            hipLaunchKernelGGL(k_reorth<16>, dim3(grid), dim3(256), 0, s, a);
-            break;
-        case 32:
-            hipLaunchKernelGGL(k_wtr<32>, dim3(grid), dim3(256), 0, s, a);
-            hipLaunchKernelGGL(k_reorth<32>, dim3(grid), dim3(256), 0, s, a);
-            break;
-        case 48:
-            hipLaunchKernelGGL(k_wtr<48>, dim3(grid), dim3(256), 0, s, a);
-            hipLaunchKernelGGL(k_reorth<48>, dim3(grid), dim3(256), 0, s, a);
-            break;
-        default:
-            hipLaunchKernelGGL(k_wtr<64>, dim3(grid), dim3(256), 0, s, a);
-            hipLaunchKernelGGL(k_reorth<64>, dim3(grid), dim3(256), 0, s, a);
-            break;
-    }
+    if (kmax == 0) return;
+#define REORTH(KM)                                                                              \
+    hipLaunchKernelGGL(k_wtr<(KM > 0 ? KM : 8)>, dim3(grid), dim3(256), 0, s, a);                \
+    hipLaunchKernelGGL(k_reorth<(KM > 0 ? KM : 8)>, dim3(grid), dim3(256), 0, s, a)
+    KM_SWITCH(kmax, REORTH)
+#undef REORTH
 }
 
 void launch_reduce(const ReduceArgs &a, hipStream_t s) {
