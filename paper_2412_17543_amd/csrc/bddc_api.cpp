@@ -1645,8 +1645,10 @@ int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
 // product's shape: it is timed on the TUNE_SHORT fastest configurations of
 // that one only.  (Every split used to build and upload all lists: 176 ms of a
 // 64^3 setup, 68 ms at 32^3.  A training step with its setup: 277 -> 139 ms and
-// 95 -> 41 ms; 16^3 sequence of 10: 5.08 -> 4.92 ms, Schur call 25.9 -> 24.7 us.)
-constexpr int TUNE_GATHER = 16384, TUNE_SHORT = 8;
+// 95 -> 41 ms, then 136 -> 123 and 39.6 -> 37.8 with two tiles in flight tried on
+// the TUNE_TWO fastest only; 16^3 sequence of 10: 5.08 -> 4.92 ms, Schur call
+// 25.9 -> 24.7 us.)
+constexpr int TUNE_GATHER = 16384, TUNE_SHORT = 8, TUNE_TWO = 4;
 
 int tune_operators(bddc_ctx *c, int mask = 7) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1712,13 +1714,19 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
                 seen[ps].push_back(std::move(key));
                 for (int nw : {4, 8}) {
                     if (nw == 8 && !c->allow8) continue;
-                    for (int u : {2, 4}) {
-                        float ms = 0.f;
-                        if ((rc = time_cfg(SymvCfg{nw, u}, 3, gather, ms))) break;
-                        cand.push_back(Cand{ms, bpc, div, ps, SymvCfg{nw, u}});
-                    }
-                    if (rc) break;
+                    float ms = 0.f;
+                    if ((rc = time_cfg(SymvCfg{nw, 4}, 3, gather, ms))) break;
+                    cand.push_back(Cand{ms, bpc, div, ps, SymvCfg{nw, 4}});
                 }
+            }
+            // two tiles in flight instead of four on the fastest of these only
+            // (rarely the fastest, never on a split that is slow with four)
+            std::stable_sort(cand.begin(), cand.end(), [](const Cand &x, const Cand &y) { return x.ms < y.ms; });
+            for (size_t k = 0, nk = std::min<size_t>(TUNE_TWO, cand.size()); k < nk && rc == 0; ++k) {
+                Cand t = cand[k];
+                t.cfg.unroll = 2;
+                if ((rc = split(t.bpc, t.div, t.ps, gather)) || (rc = time_cfg(t.cfg, 3, gather, t.ms))) break;
+                cand.push_back(t);
             }
         }
         if (rc || cand.empty()) break;
