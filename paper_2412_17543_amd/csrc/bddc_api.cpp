@@ -1120,6 +1120,7 @@ int apply_basis(bddc_ctx *c, const std::vector<double> &Y, int m, int ncol, cons
     g.k1 = k1; g.k2 = l;
     g.V1[0] = c->d_W + o0; g.V2[0] = c->d_P + (size_t)j0 * c->ld; g.out[0] = c->d_W + o0;
     g.V1[1] = c->d_AW + o0; g.V2[1] = c->d_AP + (size_t)j0 * c->ld; g.out[1] = c->d_AW + o0;
+    g.sign[0] = g.sign[1] = 1.0;
     launch_recycle_gemm(g, c->stream);
     ncol += nc0;                    // the Gram product, Cholesky and commit cover all columns
     const int nb = c->gram_nb;
@@ -2544,10 +2545,13 @@ void block_gram(bddc_ctx *c, BlockWork &b, const double *X, int kx, const double
                          c->stream);
 }
 
-// out = [V1, V2] Y (Y: (k1 + k2) x ncol row-major, host, coefficient slot
-// `slot`); out may be V1 (each wave reads its rows before writing them).
-int block_gemm(bddc_ctx *c, BlockWork &b, const double *V1, int k1, const double *V2, int k2,
-               const std::vector<double> &Y, int ncol, double *out, int slot) {
+// out = base + sign [V1, V2] Y (Y: (k1 + k2) x ncol row-major, host, coefficient
+// slot `slot`; base nullable); out may be base or V1 (each wave reads its rows
+// before writing them).  With `out2` the same launch forms
+// out2 = out2 - sign V1b Y too (k2 = 0): the updates of X and R.
+int block_gemm(bddc_ctx *c, BlockWork &b, const double *base, double sign, const double *V1, int k1, const double *V2,
+               int k2, const std::vector<double> &Y, int ncol, double *out, int slot, double *out2 = nullptr,
+               const double *V1b = nullptr) {
     if (ncol <= 0) return 0;
     double *hy = b.h + 4 * BlockWork::GSZ + (size_t)slot * BlockWork::CSZ;
     double *dy = b.coef + (size_t)slot * BlockWork::CSZ;
@@ -2556,8 +2560,11 @@ int block_gemm(bddc_ctx *c, BlockWork &b, const double *V1, int k1, const double
     GemmArgs g{};
     g.n = c->n_gamma; g.ld = c->ld;
     g.V1[0] = V1; g.k1 = k1; g.V2[0] = V2 ? V2 : V1; g.k2 = k2;
-    g.Y = dy; g.ncol = ncol; g.ldy = ncol; g.out[0] = out;
-    launch_recycle_gemm(g, c->stream, 1);
+    g.Y = dy; g.ncol = ncol; g.ldy = ncol; g.base[0] = base; g.sign[0] = sign; g.out[0] = out;
+    if (out2) {
+        g.V1[1] = g.V2[1] = V1b; g.base[1] = out2; g.sign[1] = -sign; g.out[1] = out2;
+    }
+    launch_recycle_gemm(g, c->stream, out2 ? 2 : 1);
     return 0;
 }
 
@@ -2649,17 +2656,6 @@ bool spd_solve(std::vector<double> G, int k, const double *Bm, int m, std::vecto
     return true;
 }
 
-// [I; C] as a (k + r) x k coefficient matrix (identity on the first block)
-std::vector<double> stack_identity(int k, const std::vector<double> &C, int r, double sign) {
-    std::vector<double> Y((size_t)(k + r) * k, 0.0);
-    for (int i = 0; i < k; ++i) Y[(size_t)i * k + i] = 1.0;
-    for (int q = 0; q < r; ++q)
-        for (int j = 0; j < k; ++j) Y[(size_t)(k + q) * k + j] = sign * C[(size_t)q * k + j];
-    return Y;
-}
-
-
-
 int block_solve(bddc_ctx *c, BlockWork &b, int s, double rtol, int *iters_out) {
     const int m = c->k;                               // deflation columns (the current basis)
     const int ld = c->ld;
@@ -2675,9 +2671,8 @@ int block_solve(bddc_ctx *c, BlockWork &b, int s, double rtol, int *iters_out) {
     for (int j = 0; j < s; ++j) bb[j] = b.h[(size_t)j * s + j];
     if (m > 0) {
         if (!spd_solve(WAW, m, b.h + BlockWork::GSZ, s, T)) return fail(BDDC_EBREAKDOWN, "W^T A W not positive definite");
-        if ((rc = block_gemm(c, b, c->d_W, m, nullptr, 0, T, s, b.X, 0))) return rc;
-        std::vector<double> Y = stack_identity(s, T, m, -1.0);
-        if ((rc = block_gemm(c, b, b.R, s, c->d_AW, m, Y, s, b.R, 1))) return rc;
+        // (X = 0 + W T, R = R - A W T)
+        if ((rc = block_gemm(c, b, b.X, 1.0, c->d_W, m, nullptr, 0, T, s, b.X, 0, b.R, c->d_AW))) return rc;
     }
     int r = 0, it = 0;                                // columns of P
     const int stop_r0 = c->opts.stop_rule == 1;
@@ -2700,14 +2695,16 @@ int block_solve(bddc_ctx *c, BlockWork &b, int s, double rtol, int *iters_out) {
         if (done) break;
         if (it >= c->opts.max_it) { *iters_out = it; return fail(BDDC_ENOTCONV, "max_it reached (block adjoint)"); }
         // Y = Z - W (W^T A W)^{-1} (A W)^T Z - P (P^T Q)^{-1} Q^T Z
+        std::vector<double> C;
         if (m > 0) {
             if (!spd_solve(WAW, m, b.h + BlockWork::GSZ, s, T)) return fail(BDDC_EBREAKDOWN, "W^T A W not positive definite");
-            if ((rc = block_gemm(c, b, b.Z, s, c->d_W, m, stack_identity(s, T, m, -1.0), s, b.Z, 0))) return rc;
+            C = T;
         }
         if (r > 0) {
             if (!spd_solve(Gpq, r, b.h + 2 * BlockWork::GSZ, s, T)) return fail(BDDC_EBREAKDOWN, "P^T A P not positive definite");
-            if ((rc = block_gemm(c, b, b.Z, s, b.P, r, stack_identity(s, T, r, -1.0), s, b.Z, 1))) return rc;
+            C.insert(C.end(), T.begin(), T.end());
         }
+        if (m + r > 0 && (rc = block_gemm(c, b, b.Z, -1.0, c->d_W, m, b.P, r, C, s, b.Z, 1))) return rc;
         // P = orth(Y): eigenvectors of Y^T Y above 1e-12 of the largest eigenvalue
         block_gram(c, b, b.Z, s, b.Z, s, 3);
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -2726,7 +2723,7 @@ int block_solve(bddc_ctx *c, BlockWork &b, int s, double rtol, int *iters_out) {
             for (int i = 0; i < s; ++i)
                 for (int q = 0; q < r; ++q) Cm[(size_t)i * r + q] = V[(size_t)i * s + keep[q]] / std::sqrt(lam[keep[q]]);
         }
-        if ((rc = block_gemm(c, b, b.Z, s, nullptr, 0, Cm, r, b.P, 2))) return rc;
+        if ((rc = block_gemm(c, b, nullptr, 1.0, b.Z, s, nullptr, 0, Cm, r, b.P, 2))) return rc;
         // Q = A P; alpha = (P^T Q)^{-1} P^T R
         block_A(c, b, b.P, r, b.Q);
         block_gram(c, b, b.P, r, b.Q, r, 0);
@@ -2735,9 +2732,8 @@ int block_solve(bddc_ctx *c, BlockWork &b, int s, double rtol, int *iters_out) {
         Gpq.assign(b.h, b.h + (size_t)r * r);
         std::vector<double> alpha;
         if (!spd_solve(Gpq, r, b.h + BlockWork::GSZ, s, alpha)) return fail(BDDC_EBREAKDOWN, "P^T A P not positive definite");
-        if ((rc = block_gemm(c, b, b.X, s, b.P, r, stack_identity(s, alpha, r, 1.0), s, b.X, 3)) ||
-            (rc = block_gemm(c, b, b.R, s, b.Q, r, stack_identity(s, alpha, r, -1.0), s, b.R, 4)))
-            return rc;
+        // X += P alpha, R -= Q alpha
+        if ((rc = block_gemm(c, b, b.X, 1.0, b.P, r, nullptr, 0, alpha, s, b.X, 3, b.R, b.Q))) return rc;
         ++it;
     }
     *iters_out = it;

@@ -295,13 +295,16 @@ struct RecOutArgs {                 // u = (x_I, x_G), 0 elsewhere
     int64_t ldy, ldx, ldu;
 };
 
-// Two products of the same shape (blockIdx.y picks one): out[y] = [V1[y], V2[y]] Y.
+// Two products of the same shape (blockIdx.y picks one):
+// out[y] = base[y] + sign[y] [V1[y], V2[y]] Y (base null: none).
 struct GemmArgs {
     int n;
     int64_t ld;
     const double *V1[2]; int k1;
     const double *V2[2]; int k2;
     const double *Y; int ncol, ldy;
+    const double *base[2];
+    double sign[2];
     double *out[2];
 };
 

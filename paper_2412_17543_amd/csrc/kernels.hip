@@ -501,8 +501,8 @@ __global__ void __launch_bounds__(256) k_node_src(int n_int, const int32_t *node
 // layout: A[i][k] and B[k][j] in lane i (j) + 16 k; result (i, j) in lane
 // j + 16 (i % 4), register i / 4).
 //
-// k_recycle_gemm: out[:, c] = sum_q V[:, q] Y[q][c] with V = [V1, V2]
-// column-major (leading dimension ld); blockIdx.y selects [W, P] or
+// k_recycle_gemm: out[:, c] = base[:, c] + sign sum_q V[:, q] Y[q][c] with V =
+// [V1, V2] column-major (leading dimension ld); blockIdx.y selects [W, P] or
 // [AW, AP].  Each wave takes 16 rows and forms out^T = Y^T V^T for them, 16
 // columns per tile (NT tiles): the B operand is 16 consecutive rows of one
 // column of V (one coalesced load per lane and step of 4 columns), the A
@@ -520,8 +520,15 @@ __global__ void __launch_bounds__(256) k_recycle_gemm(GemmArgs a) {
     const bool rok = row < a.n;
     const int m = a.k1 + a.k2;
     dvec4 acc[NT];
+    const double *base = a.base[y];
+    const double sign = a.sign[y];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = dvec4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = 16 * t + lk + 4 * r;
+            acc[t][r] = base && rok && c < a.ncol ? base[(int64_t)c * a.ld + row] : 0.0;
+        }
     // B operands GQ steps (4 GQ columns of V) at a time, all requested before
     // the first is used
     constexpr int GQ = 8;
@@ -538,7 +545,7 @@ __global__ void __launch_bounds__(256) k_recycle_gemm(GemmArgs a) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int c = 16 * t + li;
-                const double av = (q < m && c < a.ncol) ? a.Y[(int64_t)q * a.ldy + c] : 0.0;
+                const double av = (q < m && c < a.ncol) ? sign * a.Y[(int64_t)q * a.ldy + c] : 0.0;
                 acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b[u], acc[t], 0, 0, 0);
             }
         }
