@@ -74,6 +74,15 @@ struct Pending {
 
 }  // namespace
 
+// A symmetric matrix as its upper triangle in 64 x 64 blocks, with the parts
+// of one product (SymBlkArgs).
+struct SymBlk {
+    int n = 0, nb = 0;
+    double *B = nullptr, *part = nullptr;
+    int32_t *bI = nullptr;
+    int64_t parts() const { return (int64_t)64 * nb * symblk_ld(nb); }
+};
+
 struct bddc_ctx {
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;
@@ -140,16 +149,15 @@ struct bddc_ctx {
     int32_t *d_c3o = nullptr, *d_n3p = nullptr;
     size_t smem_l2d = 0;
     bool coarse_dense = false;      // u_C from one dense product (two levels, or explicit form)
-    // dense coarse operator, row-major nC x nC with rows of ldm (even)
-    // entries: -K_C^{-1} (two levels) or the explicit level-2 BDDC operator
-    double *d_Mc = nullptr, *d_rC = nullptr;
+    // dense coarse operator: -K_C^{-1} (two levels) or the explicit level-2
+    // BDDC operator, row-major with rows of ldm (even) entries; above
+    // FUSED_MAX_NC rows its upper triangle in blocks (sign folded in)
+    double *d_Mc = nullptr;
     int64_t ldm = 0;
+    SymBlk mc;
     int64_t *d_K2_off = nullptr, *d_N2_off = nullptr, *d_P2_off = nullptr;
-    // level-3 inverse also as its upper triangle in 64 x 64 blocks (large levels)
-    int nb3 = 0;
-    double *d_K3s = nullptr, *d_K3part = nullptr;
-    int32_t *d_K3bI = nullptr;
-    double *d_K2 = nullptr, *d_N2 = nullptr, *d_Phi2 = nullptr, *d_K3inv = nullptr, *d_r3 = nullptr, *d_vI2 = nullptr,
+    SymBlk k3;                      // level-3 inverse above FUSED_MAX_NC rows
+    double *d_K2 = nullptr, *d_N2 = nullptr, *d_Phi2 = nullptr, *d_K3inv = nullptr, *d_vI2 = nullptr,
            *d_t2 = nullptr, *d_rB2 = nullptr, *d_u2 = nullptr, *d_c3loc = nullptr, *d_u3 = nullptr;
     // deflation / recycling
     int R = 0, k = 0, save_cap = 0, kmax = 0;
@@ -306,9 +314,10 @@ double coarse_bytes(const bddc_ctx *c) {
     double cp = 0.0;   // coarse partials gathered into r_C: index + value
     for (int i = 0; i < c->n_sub; ++i) cp += c->h_nc[i] * 12.0;
     const double vec = c->nC * (4.0 + 8.0 + 8.0);
-    if (c->coarse_dense) return (double)c->nC * c->ldm * 8.0 + cp + vec + c->nC * 8.0;
+    auto tri = [](double n) { return n * (n + 1) / 2 * 8.0; };
+    if (c->coarse_dense) return (c->mc.B ? tri(c->nC) : (double)c->nC * c->ldm * 8.0) + cp + vec + c->nC * 8.0;
     const double n3 = c->n3;
-    double b = cp + vec + (c->d_K3s ? n3 * (n3 + 1) / 2 * 8.0 : n3 * c->ld3 * 8.0);
+    double b = cp + vec + (c->k3.B ? tri(n3) : n3 * c->ld3 * 8.0);
     for (const SubregionHost &r : c->st.sr) {
         const double nL = (double)r.L.size(), nI = r.nI, nB = r.nB, n3 = (double)r.c3.size();
         b += (nL * nI + nB * nB + nB * n3 + nB * n3 + nI * nB) * 8.0 + nL * (4.0 + 8.0);
@@ -553,26 +562,56 @@ L2Args l2_args(const bddc_ctx *c, const Gather &rc) {
     return l;
 }
 
+SymBlkArgs symblk_args(const bddc_ctx *c, const SymBlk &o, Gather rc, double *part, int ncols) {
+    SymBlkArgs a{};
+    a.ctl = c->d_ctl; a.n = o.n; a.nb = o.nb; a.B = o.B; a.bI = o.bI; a.rc = rc;
+    a.part = part; a.ncols = ncols; a.cs_part = o.parts();
+    return a;
+}
+
+// Level 3: u3 = K3^{-1} r3, r3 the sum of the subregion contributions c3 (one
+// column per cs_c3, cs_u3 entries), with the inverse's upper triangle in blocks
+// or the dense inverse (stored negated, rows padded to ld3).
+void run_level3(const bddc_ctx *c, const double *c3, int64_t cs_c3, double *u3, int64_t cs_u3, double *part, int ncols,
+                hipStream_t st) {
+    const Gather rc{c->d_asm3_ptr, c->d_asm3_idx, c3};
+    if (c->k3.B) {
+        SymBlkArgs a = symblk_args(c, c->k3, rc, part, ncols);
+        a.cs_rc = cs_c3; a.u = u3; a.cs_u = cs_u3;
+        launch_symblk(a, st);
+        launch_symblk_sum(a, st);
+        return;
+    }
+    CoarseDenseArgs a{};
+    a.ctl = c->d_ctl; a.n = c->n3; a.rc = rc; a.M = c->d_K3inv; a.ldm = c->ld3; a.sign = -1.0; a.u = u3;
+    a.cs_rc = cs_c3; a.cs_u = cs_u3;
+    launch_coarse_dense(a, st, ncols);
+}
+
+// u_C of a dense coarse operator from the coarse partials cp: u_C itself, or
+// its parts for the prolongation to add (above FUSED_MAX_NC rows).
+void run_dense_coarse(const bddc_ctx *c, const double *cp, int64_t cs_cp, double *uC, int64_t cs_uC, double *part,
+                      int ncols, hipStream_t st) {
+    const Gather rc{c->d_casm_ptr, c->d_casm_idx, cp};
+    if (c->mc.B) {
+        SymBlkArgs a = symblk_args(c, c->mc, rc, part, ncols);
+        a.cs_rc = cs_cp;
+        launch_symblk(a, st);
+        return;
+    }
+    CoarseDenseArgs a{};
+    a.ctl = c->d_ctl; a.n = c->nC; a.rc = rc; a.M = c->d_Mc; a.ldm = c->ldm;
+    a.sign = c->three ? 1.0 : -1.0; a.u = uC; a.cs_rc = cs_cp; a.cs_u = cs_uC;
+    launch_coarse_dense(a, st, ncols);
+}
+
 // Level-2 BDDC applied to the level-1 coarse residual (Section 3.2,
 // multilevel paragraph): subregion pre-solves, level-2 interface residual
 // and local solves, level-3 coarse solve, level-2 correction into u_C.
 void run_l2_chain(const bddc_ctx *c, const L2Args &l, hipStream_t st) {
     launch_l2_a(l, c->nsr, c->max_nL, st);
     launch_l2_b(l, c->nsr, c->max_nL, st);
-    // level 3: r3 = sum of the subregion contributions, u3 = K3^{-1} r3 with
-    // the inverse's upper triangle in blocks, or the dense inverse (stored
-    // negated, rows padded to ld3)
-    CoarseDenseArgs l3{};
-    l3.ctl = c->d_ctl; l3.n = c->n3; l3.rc = Gather{c->d_asm3_ptr, c->d_asm3_idx, c->d_c3loc}; l3.r = c->d_r3;
-    l3.M = c->d_K3inv; l3.ldm = c->ld3; l3.sign = -1.0; l3.u = c->d_u3;
-    if (c->d_K3s) {
-        SymBlkArgs sb{};
-        sb.ctl = c->d_ctl; sb.n = c->n3; sb.nb = c->nb3; sb.B = c->d_K3s; sb.bI = c->d_K3bI; sb.r = c->d_r3;
-        sb.part = c->d_K3part; sb.u = c->d_u3;
-        launch_coarse_symblk(l3, sb, st);
-    } else {
-        launch_coarse_dense(l3, st);
-    }
+    run_level3(c, c->d_c3loc, 0, c->d_u3, 0, c->k3.part, 1, st);
     launch_l2_d(l, c->nsr, c->smem_l2d, st);
 }
 
@@ -626,17 +665,10 @@ void run_precond(bddc_ctx *c, const double *r, double *z, int test, bool gated, 
 void run_coarse(bddc_ctx *c, hipStream_t st) {
     if (c->nC == 0) return;
     TScope ts(c, TK_COARSE);
-    const Gather rc{c->d_casm_ptr, c->d_casm_idx, c->d_crest};
-    if (c->coarse_dense) {
-        CoarseDenseArgs ca{};
-        ca.ctl = c->d_ctl; ca.n = c->nC; ca.rc = rc; ca.r = c->d_rC;
-        ca.M = c->d_Mc; ca.ldm = c->ldm;
-        ca.sign = c->three ? 1.0 : -1.0;
-        ca.u = c->d_uC;
-        launch_coarse_dense(ca, st);
-    } else {
-        run_l2_chain(c, l2_args(c, rc), st);
-    }
+    if (c->coarse_dense)
+        run_dense_coarse(c, c->d_crest, 0, c->d_uC, 0, c->mc.part, 1, st);
+    else
+        run_l2_chain(c, l2_args(c, Gather{c->d_casm_ptr, c->d_casm_idx, c->d_crest}), st);
 }
 
 // Arguments of the prolongation w_i = u_i + D Phi_i u_C of a single vector.
@@ -646,7 +678,8 @@ ProlArgs prolong_args(const bddc_ctx *c, bool gated) {
     pa.nB = c->d_nB; pa.b_off = c->d_b_off; pa.nc = c->d_nc; pa.c_off = c->d_c_off; pa.cidx = c->d_cidx;
     pa.nchunk = c->opN.d_nchunk; pa.pb = c->opN.d_pb; pa.upart = c->opN.d_ypart;
     pa.phir = c->d_phir; pa.phr_off = c->d_phr_off;
-    pa.uC = c->nC > 0 ? c->d_uC : nullptr;
+    pa.uC = c->nC > 0 && !c->mc.B ? c->d_uC : nullptr;
+    pa.upC = c->mc.part; pa.nbC = c->mc.nb;
     pa.wloc = c->d_wloc;
     pa.ch_sub = c->d_pch_sub; pa.ch_row = c->d_pch_row;
     return pa;
@@ -1766,14 +1799,36 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
     return rc;
 }
 
+// The upper triangle of sign * M (n x n, rows of ld entries, symmetric) in
+// 64 x 64 blocks, and the parts of one product.
+int set_symblk(bddc_ctx *c, SymBlk &o, const double *M, int64_t ld, int n, double sign) {
+    const int nb = (n + 63) / 64;
+    const int64_t nbt = (int64_t)nb * (nb + 1) / 2;
+    std::vector<int32_t> bI;
+    bI.reserve(nbt);
+    for (int I = 0; I < nb; ++I)
+        for (int J = I; J < nb; ++J) bI.push_back(I);
+    o.n = n;
+    o.nb = nb;
+    int rc;
+    if ((rc = dupload(c, &o.bI, bI)) || (rc = dalloc(c, &o.B, (size_t)nbt * 4096)) || (rc = dalloc(c, &o.part, (size_t)o.parts())))
+        return rc;
+    launch_pack_symblk(M, ld, n, nb, o.bI, sign, o.B, c->stream);
+    return 0;
+}
+
 // The dense coarse operator from an nC x nC device matrix (column-major when
-// `transpose`, else row-major), its rows padded to an even length, and the
-// r_C buffer of the dense product.
+// `transpose`, else row-major; either way symmetric): up to FUSED_MAX_NC rows
+// as they are, padded to an even length (a block of the prolongation, or of
+// k_coarse_dense, holds r_C whole), above in blocks
+// (one application with its prolongation: 1,932 rows 18.0 -> 13.0 us, 3,595 rows
+// 38 -> 30).
 int set_dense_coarse(bddc_ctx *c, const double *d_src, bool transpose) {
     const int n = c->nC;
+    if (n > FUSED_MAX_NC) return set_symblk(c, c->mc, d_src, n, n, c->three ? 1.0 : -1.0);
     c->ldm = (n + 1) & ~1;
     int rc;
-    if ((rc = dalloc(c, &c->d_Mc, (size_t)n * c->ldm)) || (rc = dalloc(c, &c->d_rC, (size_t)std::max(1, n)))) return rc;
+    if ((rc = dalloc(c, &c->d_Mc, (size_t)n * c->ldm))) return rc;
     launch_pad_rows(d_src, n, transpose, c->d_Mc, c->ldm, c->stream);
     return 0;
 }
@@ -1799,13 +1854,13 @@ int build_explicit_coarse(bddc_ctx *c) {
     const int64_t n3 = std::max(1, c->n3);
     i2 = std::max<int64_t>(1, i2); b2 = std::max<int64_t>(1, b2); c3 = std::max<int64_t>(1, c3);
     int32_t *dp;
-    double *de, *dcol, *vI2, *t2, *rB2, *u2, *c3loc, *u3, *r3;
+    double *de, *dcol, *vI2, *t2, *rB2, *u2, *c3loc, *u3, *p3;
     int rc;
     if ((rc = dupload(c, &dp, ptr)) || (rc = dalloc(c, &de, 2 * (size_t)n)) || (rc = dalloc(c, &dcol, (size_t)n * n)) ||
         (rc = dalloc(c, &vI2, (size_t)i2 * nb)) || (rc = dalloc(c, &t2, (size_t)b2 * nb)) ||
         (rc = dalloc(c, &rB2, (size_t)b2 * nb)) || (rc = dalloc(c, &u2, (size_t)b2 * nb)) ||
         (rc = dalloc(c, &c3loc, (size_t)c3 * nb)) || (rc = dalloc(c, &u3, (size_t)n3 * nb)) ||
-        (rc = dalloc(c, &r3, (size_t)n3 * nb)))
+        (rc = dalloc(c, &p3, (size_t)std::max<int64_t>(1, c->k3.parts() * nb))))
         return rc;
     launch_fill(2 * (int64_t)n, 0.0, de, s);
     launch_fill(1, 1.0, de + n, s);
@@ -1813,23 +1868,19 @@ int build_explicit_coarse(bddc_ctx *c) {
     L2Args l = l2_args(c, Gather{dp, dp, de});
     l.vI2 = vI2; l.t2 = t2; l.rB2 = rB2; l.u2 = u2; l.c3loc = c3loc; l.u3 = u3;
     l.cs_rc = -1; l.cs_vI2 = i2; l.cs_t2 = l.cs_rB2 = l.cs_u2 = b2; l.cs_c3loc = c3; l.cs_u3 = n3; l.cs_uC = n;
-    CoarseDenseArgs l3{};
-    l3.ctl = c->d_ctl; l3.n = c->n3; l3.rc = Gather{c->d_asm3_ptr, c->d_asm3_idx, c3loc}; l3.r = r3;
-    l3.M = c->d_K3inv; l3.ldm = c->ld3; l3.sign = -1.0; l3.u = u3;
-    l3.cs_rc = c3; l3.cs_r = n3; l3.cs_u = n3;
     for (int q0 = 0; q0 < n; q0 += nb) {
         const int nq = std::min(nb, n - q0);
         l.rc.part = de + n - q0;
         l.uC = dcol + (int64_t)q0 * n;
         launch_l2_a(l, c->nsr, c->max_nL, s, nq);
         launch_l2_b(l, c->nsr, c->max_nL, s, nq);
-        launch_coarse_dense(l3, s, nq);
+        run_level3(c, c3loc, c3, u3, n3, p3, nq, s);
         launch_l2_d(l, c->nsr, c->smem_l2d, s, nq);
     }
     if ((rc = set_dense_coarse(c, dcol, true))) return rc;
     HIPCHK(hipStreamSynchronize(s));
     for (void *q : {(void *)dp, (void *)de, (void *)dcol, (void *)vI2, (void *)t2, (void *)rB2, (void *)u2, (void *)c3loc,
-                    (void *)u3, (void *)r3})
+                    (void *)u3, (void *)p3})
         dfree(c, q);
     return 0;
 }
@@ -2278,8 +2329,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             build_csr((int64_t)n * ld, pr, ptr, idx);
             int32_t *dp, *di;
             if ((rc = dupload(c, &dp, ptr)) || (rc = dupload(c, &di, idx)) ||
-                (rc = dalloc(c, &c->d_K3inv, (size_t)std::max<int64_t>(1, (int64_t)n * ld))) ||
-                (rc = dalloc(c, &c->d_r3, (size_t)std::max(1, n))))
+                (rc = dalloc(c, &c->d_K3inv, (size_t)std::max<int64_t>(1, (int64_t)n * ld))))
                 return rc;
             launch_gather_sum((int64_t)n * ld, dp, di, d_K3loc, c->d_K3inv, s);
             if (n > 0 && c->nullc) {
@@ -2293,23 +2343,13 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             } else if (n > 0 && (rc = run_sweeps(c, {SweepDesc{c->d_K3inv, n, ld, n, n}}))) {
                 return rc;
             }
-            // large levels: the upper triangle in 64 x 64 blocks for the
-            // single-vector product (half the bytes per application)
-            if (n >= 512) {
-                const int nb = (n + 63) / 64;
-                const int64_t nbt = (int64_t)nb * (nb + 1) / 2;
-                std::vector<int32_t> bI;
-                bI.reserve(nbt);
-                for (int I = 0; I < nb; ++I)
-                    for (int J = I; J < nb; ++J) bI.push_back(I);
-                c->nb3 = nb;
-                if ((rc = dupload(c, &c->d_K3bI, bI)) || (rc = dalloc(c, &c->d_K3s, (size_t)nbt * 4096)) ||
-                    (rc = dalloc(c, &c->d_K3part, (size_t)nbt * 128)))
-                    return rc;
-                launch_pack_symblk(c->d_K3inv, ld, n, nb, c->d_K3bI, -1.0, c->d_K3s, s);
-            }
+            if (n > FUSED_MAX_NC && (rc = set_symblk(c, c->k3, c->d_K3inv, ld, n, -1.0))) return rc;
             HIPCHK(hipStreamSynchronize(s));
             dfree(c, dp); dfree(c, di);
+            if (c->k3.B) {
+                dfree(c, c->d_K3inv);
+                c->d_K3inv = nullptr;
+            }
         }
         dfree(c, d_cptr2); dfree(c, d_ccol2); dfree(c, d_cval2); dfree(c, d_w2); dfree(c, d_M2); dfree(c, d_X2);
         dfree(c, d_K3loc);
@@ -2462,8 +2502,8 @@ struct BlockWork {
     double *xsave = nullptr;         // the forward sequence's previous solution
     double *h = nullptr;             // pinned: 4 Gram results, then 6 coefficient slots
     // per-column buffers of the coarse levels and the prolongation
-    double *rC = nullptr, *uC = nullptr, *wloc = nullptr, *vI2 = nullptr, *t2 = nullptr, *rB2 = nullptr,
-           *u2 = nullptr, *c3loc = nullptr, *u3 = nullptr, *r3 = nullptr;
+    double *pC = nullptr, *uC = nullptr, *wloc = nullptr, *vI2 = nullptr, *t2 = nullptr, *rB2 = nullptr,
+           *u2 = nullptr, *c3loc = nullptr, *u3 = nullptr, *p3 = nullptr;
     int64_t i2len = 1, b2len = 1, c3len = 1, n3len = 1, nclen = 1;
     int64_t ylen = 0, clen = 0;
     int max_nt = 0;                  // most tile rows of a Schur or Neumann operator
@@ -2502,9 +2542,9 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
         {&b.B, nv}, {&b.X, nv}, {&b.R, nv}, {&b.Z, nv}, {&b.P, nv}, {&b.Q, nv}, {&b.yS, ny}, {&b.yN, ny}, {&b.wloc, ny},
         {&b.cN, (size_t)b.clen * BMAX}, {&b.gp, (size_t)c->gram_nb * BlockWork::GSZ},
         {&b.gout, (size_t)4 * BlockWork::GSZ}, {&b.coef, (size_t)6 * BlockWork::CSZ},
-        {&b.rC, (size_t)b.nclen * BMAX}, {&b.uC, (size_t)b.nclen * BMAX}, {&b.vI2, (size_t)b.i2len * BMAX},
+        {&b.pC, (size_t)c->mc.parts() * BMAX}, {&b.uC, (size_t)b.nclen * BMAX}, {&b.vI2, (size_t)b.i2len * BMAX},
         {&b.t2, (size_t)b.b2len * BMAX}, {&b.rB2, (size_t)b.b2len * BMAX}, {&b.u2, (size_t)b.b2len * BMAX},
-        {&b.c3loc, (size_t)b.c3len * BMAX}, {&b.u3, (size_t)b.n3len * BMAX}, {&b.r3, (size_t)b.n3len * BMAX},
+        {&b.c3loc, (size_t)b.c3len * BMAX}, {&b.u3, (size_t)b.n3len * BMAX}, {&b.p3, (size_t)c->k3.parts() * BMAX},
         {&b.xsave, (size_t)c->n_gamma}};
     auto up = [](size_t doubles) { return (doubles * sizeof(double) + 255) & ~size_t(255); };
     const size_t si = (nsub * sizeof(BlockItem) + 255) & ~size_t(255), so = (nsub * sizeof(int32_t) + 255) & ~size_t(255);
@@ -2581,25 +2621,16 @@ void block_A(bddc_ctx *c, BlockWork &b, const double *X, int ncols, double *out)
 // Neumann product (one grid row per column).
 void block_coarse(bddc_ctx *c, BlockWork &b, int ncols, hipStream_t st) {
     TScope ts(c, TK_COARSE);
-    const Gather rc{c->d_casm_ptr, c->d_casm_idx, b.cN};
     if (c->coarse_dense) {
-        CoarseDenseArgs ca{};
-        ca.ctl = c->d_ctl; ca.n = c->nC; ca.rc = rc; ca.r = b.rC; ca.M = c->d_Mc; ca.ldm = c->ldm;
-        ca.sign = c->three ? 1.0 : -1.0; ca.u = b.uC;
-        ca.cs_rc = b.clen; ca.cs_r = b.nclen; ca.cs_u = b.nclen;
-        launch_coarse_dense(ca, st, ncols);
+        run_dense_coarse(c, b.cN, b.clen, b.uC, b.nclen, b.pC, ncols, st);
     } else {
-        L2Args l = l2_args(c, rc);
+        L2Args l = l2_args(c, Gather{c->d_casm_ptr, c->d_casm_idx, b.cN});
         l.vI2 = b.vI2; l.t2 = b.t2; l.rB2 = b.rB2; l.u2 = b.u2; l.c3loc = b.c3loc; l.u3 = b.u3; l.uC = b.uC;
         l.cs_rc = b.clen; l.cs_vI2 = b.i2len; l.cs_t2 = b.b2len; l.cs_rB2 = b.b2len; l.cs_u2 = b.b2len;
         l.cs_c3loc = b.c3len; l.cs_u3 = b.n3len; l.cs_uC = b.nclen;
         launch_l2_a(l, c->nsr, c->max_nL, st, ncols);
         launch_l2_b(l, c->nsr, c->max_nL, st, ncols);
-        CoarseDenseArgs l3{};
-        l3.ctl = c->d_ctl; l3.n = c->n3; l3.rc = Gather{c->d_asm3_ptr, c->d_asm3_idx, b.c3loc}; l3.r = b.r3;
-        l3.M = c->d_K3inv; l3.ldm = c->ld3; l3.sign = -1.0; l3.u = b.u3;
-        l3.cs_rc = b.c3len; l3.cs_r = b.n3len; l3.cs_u = b.n3len;
-        launch_coarse_dense(l3, st, ncols);
+        run_level3(c, b.c3loc, b.c3len, b.u3, b.n3len, b.p3, ncols, st);
         launch_l2_d(l, c->nsr, c->smem_l2d, st, ncols);
     }
 }
@@ -2626,10 +2657,11 @@ void block_M(bddc_ctx *c, BlockWork &b, const double *R, int ncols, double *Z) {
     pa.nB = c->d_nB; pa.b_off = c->d_b_off; pa.nc = c->d_nc; pa.c_off = c->d_c_off; pa.cidx = c->d_cidx;
     pa.nchunk = b.ones; pa.pb = c->d_b_off; pa.upart = b.yN;
     pa.phir = c->d_phirx[prec_slot(64)]; pa.phr_off = c->d_phr_off;
-    pa.uC = c->nC > 0 ? b.uC : nullptr;
+    pa.uC = c->nC > 0 && !c->mc.B ? b.uC : nullptr;
+    pa.upC = c->mc.B ? b.pC : nullptr; pa.nbC = c->mc.nb;
     pa.wloc = b.wloc;
     pa.ch_sub = c->d_pch_sub; pa.ch_row = c->d_pch_row;
-    pa.cs_u = b.ylen; pa.cs_uC = b.nclen; pa.cs_w = b.ylen;
+    pa.cs_u = b.ylen; pa.cs_uC = c->mc.B ? c->mc.parts() : b.nclen; pa.cs_w = b.ylen;
     launch_prolong(pa, 64, c->n_pch, c->max_nc, c->stream, ncols);
     ZasmArgs za{};
     za.n = c->n_gamma;

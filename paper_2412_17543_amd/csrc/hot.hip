@@ -729,16 +729,43 @@ __device__ __forceinline__ double ld_rc_as<uint16_t>(__amdgpu_buffer_rsrc_t r, i
     return (double)dev::bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, i * 2, 0, 0));
 }
 
-// FUSED (dense coarse operators of up to FUSED_MAX_NC rows, one column): the
+// Sums of up to NE rows' parts at once, 32 lanes a row (every lane of the wave
+// active; rows < 0: no access, zero), in the same order for every reader.
+template <int NE>
+__device__ __forceinline__ void symblk_rows(__amdgpu_buffer_rsrc_t pr, int nb, const int (&row)[NE], double (&s)[NE]) {
+    const int l = threadIdx.x & 31, nbp = symblk_ld(nb), np = 64 * nb * nbp;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) s[e] = 0.0;
+    for (int k0 = 0; k0 < nb; k0 += 64) {
+        double v[NE][2];
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int k = k0 + 32 * u + l;
+                v[e][u] = ld_rc(pr, row[e] >= 0 && k < nb ? row[e] * nbp + k : np);
+            }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) s[e] += v[e][0] + v[e][1];
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e) s[e] = dev::row16_sum(dev::add_xor16(s[e]));
+}
+
+enum { UC_VEC, UC_SOLVE, UC_PARTS };
+
+// u_C is read (UC_VEC), added from the parts of the product in blocks
+// (UC_PARTS), or solved for.
+// UC_SOLVE (dense coarse operators of up to FUSED_MAX_NC rows, one column): the
 // block computes the entries of u_C that its subdomain needs from the coarse
 // partials, a wave per entry with the operands of four entries requested
-// before r_C is gathered, in the summation order of k_coarse_rhs and
-// k_coarse_dense, whose two launches (about 6 us, whatever the size) it
-// replaces.  One preconditioner application: 18 coarse DOFs (16^3) 19.8 -> 16.1
-// us, 82 24.1 -> 20.0, 216 (32^3) 28.0 -> 23.8, 444 37.8 -> 33.9.  Above, every
-// block's rows of M (nc_i nC entries) cost what the launches do: with room for
-// 2,048 columns 790 DOFs take 45.8 us either way, 1,932 take 45.9 against 31.7.
-template <typename T, bool FUSED>
+// before r_C is gathered, in the summation order of
+// k_coarse_dense, whose launch it replaces.  One preconditioner application
+// against that launch and one for r_C before it: 18 coarse DOFs (16^3) 19.8 ->
+// 16.1 us, 82 24.1 -> 20.0, 216 (32^3) 28.0 -> 23.8, 444 37.8 -> 33.9.  Above,
+// every block's rows of M (nc_i nC entries) cost what the launches do: with room
+// for 2,048 columns 790 DOFs take 45.8 us either way, 1,932 45.9 against 31.7.
+template <typename T, int UC>
 __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
     extern __shared__ double uCl[];
     constexpr int PF = 16, CF = 4;      // basis entries / partials of a row requested early
@@ -746,13 +773,14 @@ __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
     {
         const int64_t col = blockIdx.y;  // one column per grid row (block products)
         a.upart += col * a.cs_u;
-        if (a.uC) a.uC += col * a.cs_uC;
+        if (UC == UC_PARTS) a.upC += col * a.cs_uC;
+        else if (a.uC) a.uC += col * a.cs_uC;
         a.wloc += col * a.cs_w;
     }
     // 512 rows of one subdomain per block (large subdomains take several)
     const int i = a.ch_sub[blockIdx.x], r0 = a.ch_row[blockIdx.x];
     const int n = a.nB[i], C = a.nchunk[i];
-    const int nci = a.uC ? a.nc[i] : 0, ld = phi_ld(n);
+    const int nci = UC != UC_VEC || a.uC ? a.nc[i] : 0, ld = phi_ld(n);
     const int32_t *ci = a.cidx + a.c_off[i];
     const T *ph = reinterpret_cast<const T *>(a.phir) + a.phr_off[i];   // column-major, rows of ld
     const double *up = a.upart + a.pb[i];
@@ -776,7 +804,7 @@ __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
         pr0[q] = ld_rc_as<T>(pr, q * ld + k0);
         pr1[q] = ld_rc_as<T>(pr, q * ld + k1);
     }
-    if constexpr (FUSED) {
+    if constexpr (UC == UC_SOLVE) {
         constexpr int EG = 4;
         __shared__ double rs[FUSED_MAX_NC];
         const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, ldm = (int)a.ldm;
@@ -815,35 +843,61 @@ __global__ void __launch_bounds__(256) k_prolong(ProlArgs a) {
         for (int j = 0; j < EG; ++j)
 #pragma unroll
             for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(m[j][u]));
+    } else if constexpr (UC == UC_PARTS) {
+        // the parts of four entries a round, 32 lanes each
+        const __amdgpu_buffer_rsrc_t sr = vec_rsrc(a.upC, (int64_t)64 * a.nbC * symblk_ld(a.nbC));
+        const int g = threadIdx.x >> 5;
+        for (int qb = 0; qb < nci; qb += 32) {
+            int rw[4];
+            double s[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rw[j] = qb + g + 8 * j < nci ? ci[qb + g + 8 * j] : -1;
+            symblk_rows(sr, a.nbC, rw, s);
+            if ((threadIdx.x & 31) == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (qb + g + 8 * j < nci) uCl[qb + g + 8 * j] = s[j];
+            }
+        }
     } else {
         for (int q = threadIdx.x; q < nci; q += blockDim.x) uCl[q] = a.uC[ci[q]];
     }
     __syncthreads();
-    // w = sum of the partials, then the basis terms, in column order
-    auto row = [&](int k, const double (&u)[CF], const double (&r)[PF]) {
-        double w = 0.0;
+    // w = sum of the partials, then the basis terms, in column order; both rows
+    // advance together, so that a subdomain cut into many segments or with
+    // many coarse DOFs waits once for both (holed 64^3: 19.5 -> 16.1 us)
+    double w0 = 0.0, w1 = 0.0;
 #pragma unroll
-        for (int cc = 0; cc < CF; ++cc)
-            if (cc < C) w += u[cc];
-        // (a subdomain cut into many segments, four partials a round: holed
-        // 64^3 22.9 -> 16.7 us a launch)
-        for (int cc = CF; cc < C; cc += CF) {
-            double v[CF];
+    for (int cc = 0; cc < CF; ++cc)
+        if (cc < C) { w0 += u0[cc]; w1 += u1[cc]; }
+    for (int cc = CF; cc < C; cc += CF) {
+        double v0[CF], v1[CF];
 #pragma unroll
-            for (int m = 0; m < CF; ++m) v[m] = ld_rc(ur, (cc + m) * n + k);
-#pragma unroll
-            for (int m = 0; m < CF; ++m)
-                if (cc + m < C) w += v[m];
+        for (int m = 0; m < CF; ++m) {
+            v0[m] = ld_rc(ur, (cc + m) * n + k0);
+            v1[m] = ld_rc(ur, (cc + m) * n + k1);
         }
 #pragma unroll
-        for (int q = 0; q < PF; ++q)
-            if (q < nci) w += r[q] * uCl[q];
-#pragma unroll 8
-        for (int q = PF; q < nci; ++q) w += to_d(ph[(int64_t)q * ld + k]) * uCl[q];
-        wl[k] = w;
-    };
-    if (k0 < n) row(k0, u0, pr0);
-    if (k1 < n) row(k1, u1, pr1);
+        for (int m = 0; m < CF; ++m)
+            if (cc + m < C) { w0 += v0[m]; w1 += v1[m]; }
+    }
+#pragma unroll
+    for (int q = 0; q < PF; ++q)
+        if (q < nci) { w0 += pr0[q] * uCl[q]; w1 += pr1[q] * uCl[q]; }
+    constexpr int QF = 16;
+    for (int qb = PF; qb < nci; qb += QF) {
+        double v0[QF], v1[QF];
+#pragma unroll
+        for (int m = 0; m < QF; ++m) {
+            v0[m] = ld_rc_as<T>(pr, (qb + m) * ld + k0);
+            v1[m] = ld_rc_as<T>(pr, (qb + m) * ld + k1);
+        }
+#pragma unroll
+        for (int m = 0; m < QF; ++m)
+            if (qb + m < nci) { w0 += v0[m] * uCl[qb + m]; w1 += v1[m] * uCl[qb + m]; }
+    }
+    if (k0 < n) wl[k0] = w0;
+    if (k1 < n) wl[k1] = w1;
 }
 
 // ---------------------------------------------------------------------------
@@ -1133,166 +1187,109 @@ __global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) {
 // of Section 3.2, subdomains acting as the elements of subregions.  Every
 // matrix here is symmetric and row-major; products read it column by column.
 // ---------------------------------------------------------------------------
-// Two levels: r_C = sum_i R_Ci^T c_i, u_C = K_C^{-1} r_C with the dense
-// inverse (stored negated by the sweep); block b computes rows [64b, 64b+64).
-// r_C assembled once from the coarse partials (fixed order).
-__device__ __forceinline__ void coarse_cols(CoarseDenseArgs &a) {
-    const int64_t col = blockIdx.y;     // one column per grid row (block products)
-    a.rc.part += col * a.cs_rc;
-    a.r += col * a.cs_r;
-    a.u += col * a.cs_u;
-}
-
-__global__ void __launch_bounds__(256) k_coarse_rhs(CoarseDenseArgs a) {
+// Dense product u = sign * M r of up to FUSED_MAX_NC rows (row-major M, rows
+// padded with zeros to the even length ldm): a wave per row, four rows a
+// block.  Latency alone: the row (512 columns in four 16-byte loads a lane,
+// zero past the row through the range check) is requested before the block
+// gathers r into LDS.  (A launch of its own for r: 4.6 us before 4.6 us at 460
+// rows; with the gather in every block 4.7 us.)
+constexpr int CD_ROWS = 4;
+__global__ void __launch_bounds__(CD_ROWS * 64) k_coarse_dense(CoarseDenseArgs a) {
+    __shared__ double rs[FUSED_MAX_NC];
     if (a.ctl->done) return;
-    coarse_cols(a);
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < a.n) a.r[q] = gather_sum(a.rc, q);
-}
-
-// Dense coarse product u_C = sign * M r_C (row-major M, rows padded with
-// zeros to the even length ldm): each wave takes one row of the block's
-// ROWS, lanes striding over the columns in 16-byte pieces, four pieces per
-// round (8 rows per block above 4096 columns, where the staged r_C limits the
-// blocks per compute unit, else 4).  The first CD_PRE rounds of the row do not depend on r_C and are
-// requested before r_C is staged in LDS; the staging issues all of a
-// thread's loads before waiting for any.  Loads past the row read as zero
-// through the buffer range check, and the staged copy is zero past n.
-constexpr int CD_PRE = 4;           // rounds of 512 columns requested up front
-__host__ __device__ inline int coarse_dense_staged(int ldm) {
-    return ((max(ldm, 512 * CD_PRE) + 511) / 512) * 512;
-}
-template <int ROWS>
-__global__ void __launch_bounds__(ROWS * 64) k_coarse_dense(CoarseDenseArgs a) {
-    extern __shared__ double rs[];
-    if (a.ctl->done) return;
-    coarse_cols(a);
+    a.rc.part += blockIdx.y * a.cs_rc;  // one column per grid row (block products)
+    a.u += blockIdx.y * a.cs_u;
     const int n = a.n, ldm = (int)a.ldm;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int row = blockIdx.x * ROWS + w;
+    const int row = blockIdx.x * CD_ROWS + w;
     const bool live = row < n;
     const __amdgpu_buffer_rsrc_t mr = tile_rsrc(a.M + (int64_t)(live ? row : 0) * ldm, live ? ldm * 8 : 0);
-    uvec4 pre[4 * CD_PRE];
+    uvec4 m[4];
 #pragma unroll
-    for (int u = 0; u < 4 * CD_PRE; ++u) pre[u] = __builtin_amdgcn_raw_buffer_load_b128(mr, (2 * l + 128 * u) * 8, 0, 0);
-    const int nr = coarse_dense_staged(ldm);
-    const __amdgpu_buffer_rsrc_t rr = vec_rsrc(a.r, n);
-    constexpr int NT = ROWS * 64;
-    for (int q0 = 0; q0 < nr; q0 += 8 * NT) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = ld_rc(rr, q0 + u * NT + (int)threadIdx.x);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int q = q0 + u * NT + (int)threadIdx.x;
-            if (q < nr) rs[q] = v[u];
-        }
-    }
+    for (int u = 0; u < 4; ++u) m[u] = __builtin_amdgcn_raw_buffer_load_b128(mr, (2 * l + 128 * u) * 8, 0, 0);
+    for (int q = threadIdx.x; q < FUSED_MAX_NC; q += CD_ROWS * 64) rs[q] = q < n ? gather_sum(a.rc, q) : 0.0;
     __syncthreads();
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    double s[4];
 #pragma unroll
-    for (int i = 0; i < CD_PRE; ++i) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int col = 2 * l + 512 * i + 128 * u;
-            const uvec4 v = pre[4 * i + u];
-            s[u] += __hiloint2double(v.y, v.x) * rs[col] + __hiloint2double(v.w, v.z) * rs[col + 1];
-        }
-    }
-    for (int c0 = 512 * CD_PRE; c0 < ldm; c0 += 512) {
-        uvec4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(mr, (2 * l + c0 + 128 * u) * 8, 0, 0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int col = 2 * l + c0 + 128 * u;
-            s[u] += __hiloint2double(v[u].y, v[u].x) * rs[col] + __hiloint2double(v[u].w, v[u].z) * rs[col + 1];
-        }
+    for (int u = 0; u < 4; ++u) {
+        const int col = 2 * l + 128 * u;
+        s[u] = __hiloint2double(m[u].y, m[u].x) * rs[col] + __hiloint2double(m[u].w, m[u].z) * rs[col + 1];
     }
     const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
     if (live && l == 0) a.u[row] = a.sign * t;
 }
 
-// Level-3 coarse product with the upper triangle of the (symmetric) inverse
-// in 64 x 64 blocks: half the bytes of the full matrix.  One block of
-// threads per matrix block (I, J); thread t takes row i = t / 4, columns
-// 16 (t % 4) .. + 15 (a wave reads 16 whole rows, 8 KB in one piece).  The
-// row part B x_J is summed over the quad of the row; for J > I the column
-// part B^T x_I over the 16 rows of the wave (row rotations within 16 lanes,
-// then the row-swap permutes) and the 4 waves in order.
+// Larger symmetric coarse operators: the upper triangle in 64 x 64 blocks,
+// half the bytes of the full matrix.  One block of threads per matrix block
+// (I, J); thread 16 i + j holds the 4 x 4 patch (i, j), stored in the order the
+// threads read it and requested before r is gathered on the panels I and J.
+// Its four row sums are added over the 16 lanes of the row of patches, for
+// J > I its four column sums over the 4 lanes of the wave in that column, then
+// over the waves in order.  (Sixteen entries of one row a thread: sixteen
+// column sums over 64 lanes, take 16.7 us a launch at 3,595 rows and 7.3 at
+// 1,932; the patches 13.6 and 6.6, of which the gather and the start of a launch
+// are about 4.  The full matrix by rows, with a launch for r before it: 20.7 and
+// 11.6 us.)
+// A row's parts are stored side by side, for readers of single rows.
 __device__ __forceinline__ int symblk_start(int I, int nb) { return I * nb - I * (I - 1) / 2; }
 
 __global__ void __launch_bounds__(256) k_symblk(SymBlkArgs a) {
     __shared__ double colw[4][64];
-    __shared__ double xsh[128];     // x_J, then x_I
+    __shared__ double xsh[128];     // r_J, then r_I
     if (a.ctl->done) return;
-    const int b = blockIdx.x;
-    const int t = threadIdx.x, i = t >> 2, q = t & 3, w = t >> 6, l = t & 63;
-    const double2 *rp = reinterpret_cast<const double2 *>(a.B + (int64_t)b * 4096 + i * 64 + 16 * q);
-    double2 v[8];
+    const int b = blockIdx.x / a.ncols, col = blockIdx.x - b * a.ncols;
+    const int t = threadIdx.x, i = t >> 4, j = t & 15, w = t >> 6;
+    const double2 *bp = reinterpret_cast<const double2 *>(a.B + (int64_t)b * 4096) + t;
+    double2 v[4][2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = rp[k];
-    const int I = a.bI[b], J = I + (b - symblk_start(I, a.nb));
-    // x_J and x_I staged once (range-checked loads: zero past n, no branch)
-    const __amdgpu_buffer_rsrc_t rr = vec_rsrc(a.r, a.n);
-    if (t < 128) xsh[t] = ld_rc(rr, t < 64 ? 64 * J + t : 64 * I + t - 64);
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) v[r][h] = bp[(2 * r + h) * 256];
+    const int I = a.bI[b], J = I + (b - symblk_start(I, a.nb)), nbp = symblk_ld(a.nb);
+    double *part = a.part + col * a.cs_part;
+    a.rc.part += col * a.cs_rc;
+    if (t < 128) {
+        const int g = t < 64 ? 64 * J + t : 64 * I + t - 64;
+        xsh[t] = g < a.n ? gather_sum(a.rc, g) : 0.0;
+    }
     __syncthreads();
-    double xj[16];
+    double xj[4], xi[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) xj[c] = xsh[16 * q + c];
-    const double xi = xsh[64 + i];
-    double s = 0.0;
+    for (int c = 0; c < 4; ++c) {
+        xj[c] = xsh[4 * j + c];
+        xi[c] = xsh[64 + 4 * i + c];
+    }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += v[k].x * xj[2 * k] + v[k].y * xj[2 * k + 1];
-    s += dpp<DPP_XOR1>(s);
-    s += dpp<DPP_XOR2>(s);
-    if (q == 0) a.part[(int64_t)b * 128 + i] = s;
+    for (int r = 0; r < 4; ++r) {
+        const double s = dev::row16_sum((v[r][0].x * xj[0] + v[r][0].y * xj[1]) + (v[r][1].x * xj[2] + v[r][1].y * xj[3]));
+        if (j == r) part[(int64_t)(64 * I + 4 * i + r) * nbp + J] = s;
+    }
     if (J == I) return;             // (block-uniform) a diagonal block holds both triangles
-    double cs[16];
+    double cs[4];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) { cs[2 * k] = v[k].x * xi; cs[2 * k + 1] = v[k].y * xi; }
+    for (int c = 0; c < 4; ++c) {
+        double u = 0.0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        double u = cs[k] + dpp<DPP_ROR4>(cs[k]);
-        u += dpp<DPP_ROR8>(u);
-        cs[k] = col_sum4(u);        // the wave's 16 rows of column 16 q + k
+        for (int r = 0; r < 4; ++r) u += (c & 1 ? v[r][c >> 1].y : v[r][c >> 1].x) * xi[r];
+        cs[c] = col_sum4(u);
     }
-    if (l < 4) {
+    if ((t & 63) < 16) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) colw[w][16 * q + k] = cs[k];
+        for (int c = 0; c < 4; ++c) colw[w][4 * j + c] = cs[c];
     }
     __syncthreads();
-    if (t < 64) a.part[(int64_t)b * 128 + 64 + t] = ((colw[0][t] + colw[1][t]) + colw[2][t]) + colw[3][t];
+    if (t < 64) part[(int64_t)(64 * J + t) * nbp + I] = ((colw[0][t] + colw[1][t]) + colw[2][t]) + colw[3][t];
 }
 
-// u on the rows of panel P: the column sums of blocks (I, P), I < P, then the
-// row sums of blocks (P, J), J >= P, split over 4 waves and added in order.
 __global__ void __launch_bounds__(256) k_symblk_sum(SymBlkArgs a) {
-    __shared__ double red[4][64];
     if (a.ctl->done) return;
-    const int P = blockIdx.x, t = threadIdx.x, i = t & 63, sq = t >> 6, nb = a.nb;
-    // 8 terms of the thread requested at a time (past the last term: an index
-    // past the buffer, which reads as zero), added in increasing order
-    const int64_t np = (int64_t)nb * (nb + 1) / 2 * 128;
-    const __amdgpu_buffer_rsrc_t pr = vec_rsrc(a.part, np);
-    double acc = 0.0;
-    for (int k0 = sq; k0 < nb; k0 += 32) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + 4 * u;
-            const int64_t e = k >= nb ? np
-                            : k < P ? (int64_t)(symblk_start(k, nb) + P - k) * 128 + 64 + i
-                                    : (int64_t)(symblk_start(P, nb) + k - P) * 128 + i;
-            v[u] = ld_rc(pr, e);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-    red[sq][i] = acc;
-    __syncthreads();
-    const int g = 64 * P + t;
-    if (t < 64 && g < a.n) a.u[g] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
+    const __amdgpu_buffer_rsrc_t pr =
+        vec_rsrc(a.part + blockIdx.y * a.cs_part, (int64_t)64 * a.nb * symblk_ld(a.nb));
+    const int r = blockIdx.x * 8 + (threadIdx.x >> 5);
+    const int row[1] = {r < a.n ? r : -1};
+    double s[1];
+    symblk_rows(pr, a.nb, row, s);
+    if ((threadIdx.x & 31) == 0 && r < a.n) a.u[blockIdx.y * a.cs_u + r] = s[0];
 }
 
 __device__ __forceinline__ void l2_cols(L2Args &a) {
@@ -1467,13 +1464,13 @@ void launch_update(const UpdArgs &a, int grid, hipStream_t s) {
 void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s, int ncols) {
     const size_t smem = (size_t)std::max(1, max_nc) * 8;
     const dim3 grid(nblocks, ncols);
-    if (a.fused) {
-        if (prec == 64) hipLaunchKernelGGL((k_prolong<double, true>), grid, dim3(256), smem, s, a);
-        else if (prec == 32) hipLaunchKernelGGL((k_prolong<float, true>), grid, dim3(256), smem, s, a);
-        else hipLaunchKernelGGL((k_prolong<uint16_t, true>), grid, dim3(256), smem, s, a);
-    } else if (prec == 64) hipLaunchKernelGGL((k_prolong<double, false>), grid, dim3(256), smem, s, a);
-    else if (prec == 32) hipLaunchKernelGGL((k_prolong<float, false>), grid, dim3(256), smem, s, a);
-    else hipLaunchKernelGGL((k_prolong<uint16_t, false>), grid, dim3(256), smem, s, a);
+    const int uc = a.fused ? UC_SOLVE : a.upC ? UC_PARTS : UC_VEC;
+    auto go = [&](auto v64, auto v32, auto v16) {
+        hipLaunchKernelGGL(prec == 64 ? v64 : prec == 32 ? v32 : v16, grid, dim3(256), smem, s, a);
+    };
+    if (uc == UC_SOLVE) go(k_prolong<double, UC_SOLVE>, k_prolong<float, UC_SOLVE>, k_prolong<uint16_t, UC_SOLVE>);
+    else if (uc == UC_PARTS) go(k_prolong<double, UC_PARTS>, k_prolong<float, UC_PARTS>, k_prolong<uint16_t, UC_PARTS>);
+    else go(k_prolong<double, UC_VEC>, k_prolong<float, UC_VEC>, k_prolong<uint16_t, UC_VEC>);
 }
 
 // Registers and loads are laid out for KM columns: buckets of 8 up to 48 (a
@@ -1538,18 +1535,15 @@ void launch_reduce(const ReduceArgs &a, hipStream_t s) {
 }
 
 void launch_coarse_dense(const CoarseDenseArgs &a, hipStream_t s, int ncols) {
-    if (a.n <= 0) return;
-    hipLaunchKernelGGL(k_coarse_rhs, dim3((a.n + 255) / 256, ncols), dim3(256), 0, s, a);
-    const size_t smem = (size_t)coarse_dense_staged((int)a.ldm) * 8;
-    if (a.n > 4096) hipLaunchKernelGGL(k_coarse_dense<8>, dim3((a.n + 7) / 8, ncols), dim3(512), smem, s, a);
-    else hipLaunchKernelGGL(k_coarse_dense<4>, dim3((a.n + 3) / 4, ncols), dim3(256), smem, s, a);
+    if (a.n > 0) hipLaunchKernelGGL(k_coarse_dense, dim3((a.n + CD_ROWS - 1) / CD_ROWS, ncols), dim3(CD_ROWS * 64), 0, s, a);
 }
 
-void launch_coarse_symblk(const CoarseDenseArgs &g, const SymBlkArgs &a, hipStream_t s) {
-    if (a.n <= 0) return;
-    hipLaunchKernelGGL(k_coarse_rhs, dim3((g.n + 255) / 256), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(k_symblk, dim3(a.nb * (a.nb + 1) / 2), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_symblk_sum, dim3(a.nb), dim3(256), 0, s, a);
+void launch_symblk(const SymBlkArgs &a, hipStream_t s) {
+    if (a.n > 0) hipLaunchKernelGGL(k_symblk, dim3(a.nb * (a.nb + 1) / 2 * a.ncols), dim3(256), 0, s, a);
+}
+
+void launch_symblk_sum(const SymBlkArgs &a, hipStream_t s) {
+    if (a.n > 0) hipLaunchKernelGGL(k_symblk_sum, dim3((a.n + 7) / 8, a.ncols), dim3(256), 0, s, a);
 }
 
 #define L2_LAUNCH(K, SMEM)                                                                              \

@@ -122,10 +122,11 @@ struct ProlArgs {                   // w_i = u_i + D Phi_i u_C (eq. averaging_su
     const double *upart;
     const void *phir;               // D Phi_i, column-major (rows of phi_ld(n) entries), local precision
     const int64_t *phr_off;
-    const double *uC;               // level-1 coarse solution (nullable: no coarse space)
+    const double *uC;               // level-1 coarse solution (nullable)
+    const double *upC; int nbC;     // or (nullable) its partials: nbC panels, part of SymBlkArgs
     double *wloc;
     const int32_t *ch_sub, *ch_row; // block b: subdomain ch_sub[b], rows ch_row[b] .. +511
-    int64_t cs_u, cs_uC, cs_w;      // several columns (blockIdx.y): strides of upart, uC, wloc
+    int64_t cs_u, cs_uC, cs_w;      // several columns (blockIdx.y): strides of upart, uC or upC, wloc
     // small dense coarse spaces (`fused`): every block forms the entries of u_C
     // that it needs itself, u_C = sign M r_C, r_C from the coarse partials
     int fused, nC;
@@ -203,35 +204,37 @@ struct ReduceArgs {                 // out[c] = sum_b part[c * n + b]
 };
 
 // ============================================================ coarse levels
-// u_C = sign * M r_C with a dense row-major n x n matrix M (r_C assembled by
-// a first kernel, the product by a second): two levels,
-// M = -K_C^{-1} (sign -1); three levels in explicit form, M = the level-2
-// BDDC operator assembled at setup (sign +1); level 3 of the three-level
-// chain, M = -K_3^{-1} (sign -1).
+// u = sign * M r with a dense row-major n x n matrix M, n <= FUSED_MAX_NC, r
+// gathered from the coarse partials: two levels, M = -K_C^{-1} (sign -1);
+// three levels in explicit form, M = the level-2 BDDC operator assembled at
+// setup (sign +1); level 3 of the three-level chain, M = -K_3^{-1} (sign -1).
 struct CoarseDenseArgs {
     Ctl *ctl;
     int n;
-    Gather rc;                      // r_C from the coarse partials
-    double *r;                      // assembled r_C (n)
+    Gather rc;                      // r from the coarse partials
     const double *M; int64_t ldm;   // rows padded to an even length (16-byte aligned)
     double sign;
     double *u;
-    int64_t cs_rc, cs_r, cs_u;      // several columns (blockIdx.y): strides of rc.part, r, u
+    int64_t cs_rc, cs_u;            // several columns (blockIdx.y): strides of rc.part, u
 };
 
-// Symmetric product u = K r with the upper triangle of K in 64 x 64 blocks
-// (I, J >= I), each row-major and zero past n; block (I, J) has index
-// I nb - I (I - 1) / 2 + J - I and bI[b] = I.  Per block: 64 row sums, then
-// (J > I) 64 column sums, in part[128 b ...]; a second pass adds them.
+// Larger ones: symmetric product u = K r with the upper triangle of K in 64 x
+// 64 blocks (I, J >= I), each in 4 x 4 patches and zero past n; block (I, J) has index
+// I nb - I (I - 1) / 2 + J - I and bI[b] = I.  part[row nbp + k] is the part
+// of a row that its block with panel k gives; a row's nb parts are added by
+// its readers, or by a second pass.
 struct SymBlkArgs {
     Ctl *ctl;
     int n, nb;                      // order, 64-row panels
     const double *B;
     const int32_t *bI;
-    const double *r;
+    Gather rc;                      // r from the coarse partials
     double *part;
     double *u;
+    int ncols;
+    int64_t cs_rc, cs_part, cs_u;   // several columns: strides of rc.part, part, u
 };
+__host__ __device__ inline int symblk_ld(int nb) { return (nb + 1) & ~1; }
 
 struct L2Args {
     Ctl *ctl;
@@ -432,8 +435,9 @@ void launch_defl_init(const DeflArgs &a, int kmax, int grid, hipStream_t s);
 void launch_reduce(const ReduceArgs &a, hipStream_t s);
 void launch_reorth(const ReorthArgs &a, int kmax, int grid, hipStream_t s);
 void launch_coarse_dense(const CoarseDenseArgs &a, hipStream_t s, int ncols = 1);
-// u = K r for the block layout of SymBlkArgs (r first gathered like the dense form's)
-void launch_coarse_symblk(const CoarseDenseArgs &g, const SymBlkArgs &a, hipStream_t s);
+// the parts of u = K r, and their sum into u
+void launch_symblk(const SymBlkArgs &a, hipStream_t s);
+void launch_symblk_sum(const SymBlkArgs &a, hipStream_t s);
 void launch_pack_symblk(const double *M, int64_t ldm, int n, int nb, const int32_t *bI, double sign, double *B,
                         hipStream_t s);
 void launch_l2_a(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols = 1);

@@ -251,12 +251,14 @@ __global__ void __launch_bounds__(256) k_pack(const PackDesc *descs, T *dst, T *
 
 
 // setup: the upper triangle of a symmetric n x n row-major matrix (sign
-// folded in) as 64 x 64 row-major blocks (I, J >= I), zero past n
+// folded in) as 64 x 64 blocks (I, J >= I), zero past n, each in 4 x 4 patches:
+// pair h of patch row r of thread t's patch at 2 ((2 r + h) 256 + t)
 __global__ void __launch_bounds__(256) k_pack_symblk(const double *M, int64_t ldm, int n, int nb, const int32_t *bI,
                                                      double sign, double *B) {
     const int b = blockIdx.x, I = bI[b], J = I + (b - (I * nb - I * (I - 1) / 2));
     for (int e = threadIdx.x; e < 4096; e += blockDim.x) {
-        const int gi = 64 * I + (e >> 6), gj = 64 * J + (e & 63);
+        const int t = (e >> 1) & 255, rh = e >> 9;
+        const int gi = 64 * I + 4 * (t >> 4) + (rh >> 1), gj = 64 * J + 4 * (t & 15) + 2 * (rh & 1) + (e & 1);
         B[(int64_t)b * 4096 + e] = (gi < n && gj < n) ? sign * M[(int64_t)gi * ldm + gj] : 0.0;
     }
 }

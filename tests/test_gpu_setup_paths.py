@@ -102,3 +102,34 @@ def test_coarse_solve_inside_the_prolongation(nx, part, cons, prec):
     z = g.apply_precond(r)
     g.enable_timing(True)
     assert torch.equal(z, g.apply_precond(r))
+
+
+@pytest.mark.parametrize("nx,cells,group,cons,form", [
+    (24, 6, None, ("corners", "faces"), "auto"),             # two levels, 665 DOFs: 11 panels, 25 rows in the last
+    (24, 6, 3, ("corners", "faces"), "explicit"),            # the same number in explicit form
+    (27, 9, 3, ("corners",), "explicit"),                    # 512 DOFs: the most held as rows
+    (20, 10, 5, ("corners", "faces"), "explicit"),           # 3,429 DOFs: 54 panels
+    (24, 12, 2, ("corners", "edges", "faces"), "chain"),     # level 3 in panels (1,115 DOFs)
+])
+def test_coarse_operators_in_panels(nx, cells, group, cons, form):
+    """Coarse operators on both sides of the size from which they are held in
+    panels: M^{-1} r against the oracle (both are sums of at most a few thousand
+    products of size ~1, through coarse matrices of condition up to ~1e4: 1e-11
+    of the largest entry), and a block adjoint against the single ones (both
+    solved to 1e-12: 1e-9)."""
+    torch = _torch()
+    from oracle.sequence import OracleSolver
+    from paper_2412_17543_amd.solver import Solver
+    part, coef = _box(nx, cells), workload.lognormal_coef(nx ** 3, 0.5)
+    sr = None if group is None else workload.cube_subregions(cells, group)
+    g = Solver(nx, part, coef, sub_to_subregion=sr, constraints=cons, coarse_form=form, autotune=False)
+    print("[gpu] %d^3, %d^3 subdomains, %s: %d coarse DOFs" % (nx, cells, form, g.info()["n_coarse"]), flush=True)
+    o = OracleSolver(nx, part, coef, sub_to_subregion=sr, constraints=cons)
+    r = np.random.default_rng(nx).standard_normal(g.n_gamma)
+    z, zo = g.apply_precond(torch.tensor(r, device="cuda")).cpu().numpy(), o.M.apply(r)
+    assert np.abs(z - zo).max() <= 1e-11 * np.abs(zo).max()
+    u = torch.tensor(workload.rhs_sequence(nx, 3), device="cuda")
+    one, gf1 = g.adjoint_grad(u, u, 1e-12)
+    blk, gfb, its = g.adjoint_grad_block(u, u, 1e-12)
+    assert (one - blk).abs().max().item() <= 1e-9 * one.abs().max().item()
+    assert (gf1 - gfb).abs().max().item() <= 1e-9 * gf1.abs().max().item()
