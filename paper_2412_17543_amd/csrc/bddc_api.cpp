@@ -2496,7 +2496,6 @@ constexpr int BMAX = 32;            // columns of one block solve
 struct BlockWork {
     char *mem = nullptr;            // holds every device buffer below
     BlockItem *items = nullptr;     // one per subdomain (the Schur and Neumann tiles share the layout)
-    int32_t *ones = nullptr;
     double *B = nullptr, *X = nullptr, *R = nullptr, *Z = nullptr, *P = nullptr, *Q = nullptr;
     double *yS = nullptr, *yN = nullptr, *cN = nullptr, *gp = nullptr, *gout = nullptr, *coef = nullptr;
     double *xsave = nullptr;         // the forward sequence's previous solution
@@ -2547,21 +2546,18 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
         {&b.c3loc, (size_t)b.c3len * BMAX}, {&b.u3, (size_t)b.n3len * BMAX}, {&b.p3, (size_t)c->k3.parts() * BMAX},
         {&b.xsave, (size_t)c->n_gamma}};
     auto up = [](size_t doubles) { return (doubles * sizeof(double) + 255) & ~size_t(255); };
-    const size_t si = (nsub * sizeof(BlockItem) + 255) & ~size_t(255), so = (nsub * sizeof(int32_t) + 255) & ~size_t(255);
-    size_t total = si + so;
+    const size_t si = (nsub * sizeof(BlockItem) + 255) & ~size_t(255);
+    size_t total = si;
     for (const auto &q : parts) total += up(q.second);
     if (int rc = dalloc(c, &b.mem, total)) return rc;
     char *at = b.mem;
     b.items = reinterpret_cast<BlockItem *>(at);
-    b.ones = reinterpret_cast<int32_t *>(at + si);
-    at += si + so;
+    at += si;
     for (const auto &q : parts) {
         *q.first = reinterpret_cast<double *>(at);
         at += up(q.second);
     }
-    const std::vector<int32_t> ones(nsub, 1);
     HIPCHK(hipMemcpyAsync(b.items, is.data(), nsub * sizeof(BlockItem), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(b.ones, ones.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     if (hipHostMalloc((void **)&b.h, sizeof(double) * (4 * BlockWork::GSZ + 6 * BlockWork::CSZ)) != hipSuccess)
         return fail(BDDC_ENOMEM, "hipHostMalloc failed (block adjoint)");
     // partial slots that no kernel writes (none with one chunk per subdomain) stay zero
@@ -2655,14 +2651,14 @@ void block_M(bddc_ctx *c, BlockWork &b, const double *R, int ncols, double *Z) {
     ProlArgs pa{};
     pa.ctl = c->d_ctl; pa.gated = 0;
     pa.nB = c->d_nB; pa.b_off = c->d_b_off; pa.nc = c->d_nc; pa.c_off = c->d_c_off; pa.cidx = c->d_cidx;
-    pa.nchunk = b.ones; pa.pb = c->d_b_off; pa.upart = b.yN;
+    pa.pb = c->d_b_off; pa.upart = b.yN;
     pa.phir = c->d_phirx[prec_slot(64)]; pa.phr_off = c->d_phr_off;
     pa.uC = c->nC > 0 && !c->mc.B ? b.uC : nullptr;
     pa.upC = c->mc.B ? b.pC : nullptr; pa.nbC = c->mc.nb;
     pa.wloc = b.wloc;
     pa.ch_sub = c->d_pch_sub; pa.ch_row = c->d_pch_row;
     pa.cs_u = b.ylen; pa.cs_uC = c->mc.B ? c->mc.parts() : b.nclen; pa.cs_w = b.ylen;
-    launch_prolong(pa, 64, c->n_pch, c->max_nc, c->stream, ncols);
+    launch_prolong_cols(pa, c->n_pch, ncols, c->stream);
     ZasmArgs za{};
     za.n = c->n_gamma;
     za.w = Gather{c->d_asm_ptr, c->d_asm_idx, b.wloc};

@@ -126,7 +126,7 @@ struct ProlArgs {                   // w_i = u_i + D Phi_i u_C (eq. averaging_su
     const double *upC; int nbC;     // or (nullable) its partials: nbC panels, part of SymBlkArgs
     double *wloc;
     const int32_t *ch_sub, *ch_row; // block b: subdomain ch_sub[b], rows ch_row[b] .. +511
-    int64_t cs_u, cs_uC, cs_w;      // several columns (blockIdx.y): strides of upart, uC or upC, wloc
+    int64_t cs_u, cs_uC, cs_w;      // several columns: strides of upart, uC or upC, wloc
     // small dense coarse spaces (`fused`): every block forms the entries of u_C
     // that it needs itself, u_C = sign M r_C, r_C from the coarse partials
     int fused, nC;
@@ -427,7 +427,9 @@ size_t symv_smem(int prec, int nw, int max_nt);
 int set_symv_smem_limit(size_t bytes);
 void launch_symv(const SymvArgs &a, SymvOp op, int prec, SymvCfg cfg, size_t smem, hipStream_t s);
 void launch_update(const UpdArgs &a, int grid, hipStream_t s);
-void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s, int ncols = 1);
+void launch_prolong(const ProlArgs &a, int prec, int nblocks, int max_nc, hipStream_t s);
+// ncols columns, float64 bases, one partial product per subdomain
+void launch_prolong_cols(const ProlArgs &a, int nblocks, int ncols, hipStream_t s);
 void launch_zasm(const ZasmArgs &a, int kmax, int grid, hipStream_t s, int ncols = 1);
 void launch_pupd(const PupdArgs &a, int kmax, int grid, hipStream_t s);
 void launch_resid(const ResidArgs &a, int kmax, int grid, hipStream_t s);

@@ -133,3 +133,28 @@ def test_coarse_operators_in_panels(nx, cells, group, cons, form):
     blk, gfb, its = g.adjoint_grad_block(u, u, 1e-12)
     assert (one - blk).abs().max().item() <= 1e-9 * one.abs().max().item()
     assert (gf1 - gfb).abs().max().item() <= 1e-9 * gf1.abs().max().item()
+
+
+@pytest.mark.parametrize("form,ncols", [("auto", 8), ("auto", 9), ("chain", 1), ("chain", 17), ("chain", 32)])
+def test_block_prolongation(form, ncols):
+    """Block adjoints of full and partly filled column groups, on a partition
+    whose middle subdomain has over 128 coarse DOFs (a cube of 4^3 cells among
+    152 single ones), two levels (coarse parts added by the prolongation) and a
+    chain of three: each equals the column-by-column gradient, both solved to
+    1e-12 (1e-9 of the largest entry)."""
+    torch = _torch()
+    from paper_2412_17543_amd.solver import Solver
+    nx, cells = 12, 6
+    cell = _box(nx, cells).astype(np.int64)
+    xyz = np.stack([cell % cells, (cell // cells) % cells, cell // cells ** 2])
+    cell[((xyz >= 1) & (xyz <= 4)).all(axis=0)] = -1
+    ids, part = np.unique(cell, return_inverse=True)
+    part = part.reshape(-1).astype(np.int32)
+    sr = (ids >= 108).astype(np.int32) if form == "chain" else None
+    g = Solver(nx, part, workload.lognormal_coef(nx ** 3, 0.5), sub_to_subregion=sr, coarse_form=form, autotune=False)
+    print("[gpu] %s, %d columns: %d coarse DOFs" % (form, ncols, g.info()["n_coarse"]), flush=True)
+    u = torch.tensor(workload.rhs_sequence(nx, ncols), device="cuda")
+    one, gf1 = g.adjoint_grad(u, u, 1e-12)
+    blk, gfb, its = g.adjoint_grad_block(u, u, 1e-12)
+    assert (one - blk).abs().max().item() <= 1e-9 * one.abs().max().item()
+    assert (gf1 - gfb).abs().max().item() <= 1e-9 * gf1.abs().max().item()
