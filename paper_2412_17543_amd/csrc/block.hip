@@ -25,8 +25,9 @@
 // (about 70 cycles each: 0.21 ms for the 0.46 M tiles of 96^3 and two chunks;
 // the tiles' bytes take 0.15 ms).  Two blocks a compute unit (at most 80 KB of
 // LDS, 128 registers) cover each other's row ends.  Measured at 96^3, 20 columns:
-// 0.83 -> 0.42 ms a product, against 4 waves, X and Y in 126 KB of LDS and both
-// parts read back through it (block adjoint 65.0 -> 47.1 ms).
+// 0.83 -> 0.42 ms a product in two chunks, against 4 waves, X and Y in 126 KB of
+// LDS and both parts read back through it (block adjoint 65.0 -> 47.1 ms); 0.32
+// with the last four columns beside the first 16 (X4).
 // v_mfma_f64_16x16x4f64 takes A[i][k] and B[k][j] in lane i (j) + 16 k and
 // returns (i, j) in lane j + 16 (i % 4), register i / 4.
 #include <hip/hip_runtime.h>
@@ -66,12 +67,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void *p, int64_
 }
 
 // Two blocks per compute unit (4 waves per SIMD) up to NJ = 4.
-template <int NJ>
+// X4: 16 + 4 columns in one block, for 17 to 20 columns.  The tile, its transpose
+// and its row end then serve all of them, and the four go through
+// v_mfma_f64_4x4x4f64 (four blocks of 4 rows; A as above, B[k][j] in lane
+// j + 16 k of every block's lanes, (i, j) of block m returned in lane
+// 4 m + j + 16 i): 9 ns a step and SIMD against 28, where a second chunk would
+// take 28 for 16 columns of which 12 are none.  96^3, 20 columns: 0.42 -> 0.32 ms
+// a product, block adjoint 34.5 -> 30.2 ms.
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+template <int NJ, bool X4>
 __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs a, int nsub) {
     extern __shared__ __align__(16) double sm[];
     // the column chunks of one subdomain are 8 blocks apart: the same XCD takes
     // them at the same time, so the second reads the tiles from its L2
-    const int nch = (a.ncols + 15) / 16;
+    constexpr int W = X4 ? 20 : 16;                    // columns of a block
+    const int nch = X4 ? 1 : (a.ncols + 15) / 16;
     int sub, chunk;
     {
         const int b = blockIdx.x, grp = b / (8 * nch), q = b - grp * 8 * nch, m = min(8, nsub - 8 * grp);
@@ -85,6 +98,7 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
     const int64_t total = full_tiles(n);
     double *xs = sm;                                   // X in operand order: [tile][s][lane]
     double *ts = xs + (size_t)npad * 16;               // per wave one 16 x 16 tile
+    double *x4 = ts + NW * 256;                        // the last four columns: [tile][s][k][column]
     const int tid = threadIdx.x, L = tid & 63, li = L & 15, lk = L >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t *gb = a.gB + it.xoff;
@@ -102,12 +116,12 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) request(jj, 0, 0);
     // X_i: 8 entries per thread at a time, all index loads before the gathers
-    for (int e0 = tid; e0 < 16 * npad; e0 += NW * 64 * 8) {
+    for (int e0 = tid; e0 < W * npad; e0 += NW * 64 * 8) {
         int gi[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int e = e0 + NW * 64 * u, cc = e / npad, k = e - cc * npad;
-            gi[u] = (e < 16 * npad && k < n && c0 + cc < a.ncols) ? gb[k] : -1;
+            gi[u] = (e < W * npad && k < n && c0 + cc < a.ncols) ? gb[k] : -1;
         }
         double v[8];
 #pragma unroll
@@ -118,7 +132,11 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int e = e0 + NW * 64 * u, cc = e / npad, k = e - cc * npad;
-            if (e < 16 * npad) xs[(k >> 4) * 256 + (k & 3) * 64 + cc + 16 * ((k & 15) >> 2)] = v[u];
+            if (X4 && cc >= 16) {
+                if (e < W * npad) x4[(k >> 4) * 64 + (k & 3) * 16 + 4 * ((k & 15) >> 2) + cc - 16] = v[u];
+            } else if (e < W * npad) {
+                xs[(k >> 4) * 256 + (k & 3) * 64 + cc + 16 * ((k & 15) >> 2)] = v[u];
+            }
         }
     }
     __syncthreads();
@@ -137,6 +155,8 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
         for (int s = 0; s < 4; ++s) u[s] = tw[rb ^ s];
     };
     const dvec4 zero = {0.0, 0.0, 0.0, 0.0};
+    const int x4l = 4 * lk + (li & 3);                 // the lane's entry of a step's four columns
+    const int r4 = 4 * (li >> 2) + lk;                 // row of the lane's result
     // Coarse restriction c_i = (D Phi_i)^T X_i from the staged X, 16 coarse DOFs
     // at a time: wave w takes the 16-row tiles w, w + 8, ..., U of them
     // requested together (four consecutive entries of a DOF's row a lane, the
@@ -147,6 +167,7 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
         const __amdgpu_buffer_rsrc_t pr = raw_rsrc(a.phir + a.phr_off[sub], pend);
         for (int q0 = 0; q0 < nci; q0 += 16) {
             dvec4 acc = zero;
+            double acc4 = 0.0;
             for (int t0 = w; t0 < tt; t0 += NW * U) {
                 uvec4 pa[U], pb[U];
 #pragma unroll
@@ -163,8 +184,10 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
                         const double v[4] = {__hiloint2double(pa[u].y, pa[u].x), __hiloint2double(pa[u].w, pa[u].z),
                                              __hiloint2double(pb[u].y, pb[u].x), __hiloint2double(pb[u].w, pb[u].z)};
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
+                        for (int s = 0; s < 4; ++s) {
                             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[s], xs[t * 256 + s * 64 + L], acc, 0, 0, 0);
+                            if constexpr (X4) acc4 = mfma4(v[s], x4[t * 64 + s * 16 + x4l], acc4);
+                        }
                     }
                 }
                 // (a tile past the last: its zero read is not left outstanding)
@@ -182,13 +205,26 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
                 if (q < nci && col < a.ncols) a.cpart[(int64_t)col * a.cs + a.c_off[sub] + q] = v;
             }
             lds_barrier();
+            if constexpr (X4) {
+                tw[L] = acc4;
+                lds_barrier();
+                if (tid < 64) {
+                    double v = ts[tid];
+#pragma unroll
+                    for (int q = 1; q < NW; ++q) v += ts[q * 256 + tid];
+                    const int q = q0 + r4, col = c0 + 16 + (li & 3);
+                    if (q < nci && col < a.ncols) a.cpart[(int64_t)col * a.cs + a.c_off[sub] + q] = v;
+                }
+                lds_barrier();
+            }
         }
     }
     dvec4 yacc[NJ], racc = zero;
+    double yacc4[NJ], racc4 = 0.0;
 #pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) yacc[jj] = zero;
+    for (int jj = 0; jj < NJ; ++jj) { yacc[jj] = zero; yacc4[jj] = 0.0; }
     // the waves' row parts, in wave order, in the registers of wave `owner`
-    auto row_sum = [&](int owner, dvec4 &y) {
+    auto row_sum = [&](int owner, dvec4 &y, double &y4) {
         wave_sync();
 #pragma unroll
         for (int r = 0; r < 4; ++r) tw[r * 64 + L] = racc[r];
@@ -204,6 +240,18 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
         }
         lds_barrier();
         racc = zero;
+        if constexpr (X4) {
+            tw[L] = racc4;
+            lds_barrier();
+            if (w == owner) {
+                double v = ts[L];
+#pragma unroll
+                for (int q = 1; q < NW; ++q) v += ts[q * 256 + L];
+                y4 += v;
+            }
+            lds_barrier();
+            racc4 = 0.0;
+        }
     };
     int S = 0;
 #pragma unroll
@@ -211,9 +259,12 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
         for (int wi = 0; wi < NW; ++wi) {
             const int I = ib * NW + wi;
             if (I >= nt) break;
-            double xi[4];
+            double xi[4], xi4[4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) xi[s] = xs[I * 256 + s * 64 + L];
+            for (int s = 0; s < 4; ++s) {
+                xi[s] = xs[I * 256 + s * 64 + L];
+                xi4[s] = X4 ? x4[I * 64 + s * 16 + x4l] : 0.0;
+            }
             const int Sn = S + nt - I - 1;
 #pragma unroll
             for (int jj = ib; jj < NJ; ++jj) {
@@ -226,19 +277,23 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
                     transpose(t, u);
                     if (J > I) {
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
+                        for (int s = 0; s < 4; ++s) {
                             yacc[jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[s], xi[s], yacc[jj], 0, 0, 0);
+                            if constexpr (X4) yacc4[jj] = mfma4(t[s], xi4[s], yacc4[jj]);
+                        }
                     }
                 }
                 // on every path, so that the number of loads in flight is known
                 request(jj, I + 1, Sn);
                 if (live) {
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
+                    for (int s = 0; s < 4; ++s) {
                         racc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s], xs[J * 256 + s * 64 + L], racc, 0, 0, 0);
+                        if constexpr (X4) racc4 = mfma4(u[s], x4[J * 64 + s * 16 + x4l], racc4);
+                    }
                 }
             }
-            row_sum(wi, yacc[ib]);
+            row_sum(wi, yacc[ib], yacc4[ib]);
             S = Sn;
         }
     }
@@ -253,13 +308,17 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
     // wave nt % 8).
     const int rem = uses_strip(n) ? n % 16 : 0;
     dvec4 yrag = zero;
+    double yrag4 = 0.0;
     if (rem > 0) {
         const int n0 = 16 * nt;
         const double *sp = a.tiles + (it.tile + total) * 256;
         constexpr int G = 2;        // chunks whose entries are requested together
-        double xr[4];
+        double xr[4], xr4[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) xr[s] = xs[nt * 256 + s * 64 + L];
+        for (int s = 0; s < 4; ++s) {
+            xr[s] = xs[nt * 256 + s * 64 + L];
+            xr4[s] = X4 ? x4[nt * 64 + s * 16 + x4l] : 0.0;
+        }
 #pragma unroll
         for (int j0 = 0; j0 <= NJ; j0 += G) {
             double v[G][4], u[4];
@@ -280,32 +339,37 @@ __global__ void __launch_bounds__(NW * 64, NJ <= 4 ? 4 : 2) k_symm(BlockSymvArgs
                     transpose(v[g], u);
                     if (jj < NJ) {
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
+                        for (int s = 0; s < 4; ++s) {
                             yacc[jj < NJ ? jj : 0] =
                                 __builtin_amdgcn_mfma_f64_16x16x4f64(v[g][s], xr[s], yacc[jj < NJ ? jj : 0], 0, 0, 0);
+                            if constexpr (X4) yacc4[jj < NJ ? jj : 0] = mfma4(v[g][s], xr4[s], yacc4[jj < NJ ? jj : 0]);
+                        }
                     }
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
+                    for (int s = 0; s < 4; ++s) {
                         racc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s], xs[q * 256 + s * 64 + L], racc, 0, 0, 0);
+                        if constexpr (X4) racc4 = mfma4(u[s], x4[q * 64 + s * 16 + x4l], racc4);
+                    }
                 }
             }
         }
-        row_sum(0, yrag);
+        row_sum(0, yrag, yrag4);
     }
     // Y through LDS ([column][row], odd stride, over X and the tiles' slots),
     // so that it is written in whole lines
     __syncthreads();
     const int ldy = npad + 1;
-    auto put = [&](int J, const dvec4 &y) {
+    auto put = [&](int J, const dvec4 &y, double y4) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) sm[li * ldy + 16 * J + 4 * r + lk] = y[r];
+        if constexpr (X4) sm[(16 + (li & 3)) * ldy + 16 * J + r4] = y4;
     };
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj)
-        if (jj * NW + w < nt) put(jj * NW + w, yacc[jj]);
-    if (rem > 0 && w == 0) put(nt, yrag);
+        if (jj * NW + w < nt) put(jj * NW + w, yacc[jj], yacc4[jj]);
+    if (rem > 0 && w == 0) put(nt, yrag, yrag4);
     __syncthreads();
-    for (int e = tid; e < 16 * n; e += NW * 64) {
+    for (int e = tid; e < W * n; e += NW * 64) {
         const int cc = e / n, k = e - cc * n, col = c0 + cc;
         if (col < a.ncols) a.ypart[(int64_t)col * a.ylen + it.xoff + k] = sm[cc * ldy + k];
     }
@@ -328,10 +392,14 @@ __global__ void __launch_bounds__(256) k_gather_block(int n, const int32_t *ptr,
 
 }  // namespace
 
-static size_t symm_smem(int max_n) { return sizeof(double) * ((size_t)16 * 16 * ((max_n + 15) / 16) + NW * 256); }
+static size_t symm_smem(int max_n, int cols = 16) {
+    return sizeof(double) * ((size_t)cols * 16 * ((max_n + 15) / 16) + NW * 256);
+}
+constexpr size_t SYMM_HALF = 80 * 1024;     // two blocks a compute unit
 
 int set_symm_smem_limit() {
-    const void *f[3] = {(const void *)k_symm<3>, (const void *)k_symm<4>, (const void *)k_symm<5>};
+    const void *f[4] = {(const void *)k_symm<3, false>, (const void *)k_symm<4, false>, (const void *)k_symm<5, false>,
+                        (const void *)k_symm<3, true>};
     for (const void *p : f)
         if (hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)symm_smem(SYMM_MAX_N)) != hipSuccess)
             return 1;
@@ -342,10 +410,14 @@ int set_symm_smem_limit() {
 void launch_symm(const BlockSymvArgs &a, int nsub, int max_n, int max_nt, hipStream_t s) {
     if (nsub <= 0 || a.ncols <= 0) return;
     const dim3 grid(nsub * ((a.ncols + 15) / 16)), block(NW * 64);
-    const size_t smem = symm_smem(max_n);
-    if (max_nt <= 3 * NW) hipLaunchKernelGGL(k_symm<3>, grid, block, smem, s, a, nsub);
-    else if (max_nt <= 4 * NW) hipLaunchKernelGGL(k_symm<4>, grid, block, smem, s, a, nsub);
-    else hipLaunchKernelGGL(k_symm<5>, grid, block, smem, s, a, nsub);
+    const size_t smem = symm_smem(max_n), smem4 = symm_smem(max_n, 20);
+    // 17 to 20 columns, while two blocks still fit a compute unit (subdomains
+    // of up to 8^3 elements); above them two chunks
+    if (a.ncols > 16 && a.ncols <= 20 && max_nt <= 3 * NW && smem4 <= SYMM_HALF)
+        hipLaunchKernelGGL((k_symm<3, true>), dim3(nsub), block, smem4, s, a, nsub);
+    else if (max_nt <= 3 * NW) hipLaunchKernelGGL((k_symm<3, false>), grid, block, smem, s, a, nsub);
+    else if (max_nt <= 4 * NW) hipLaunchKernelGGL((k_symm<4, false>), grid, block, smem, s, a, nsub);
+    else hipLaunchKernelGGL((k_symm<5, false>), grid, block, smem, s, a, nsub);
 }
 
 void launch_gather_block(int n, const int32_t *ptr, const int32_t *idx, const double *part, int64_t plen, double *out,

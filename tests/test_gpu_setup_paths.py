@@ -158,3 +158,23 @@ def test_block_prolongation(form, ncols):
     blk, gfb, its = g.adjoint_grad_block(u, u, 1e-12)
     assert (one - blk).abs().max().item() <= 1e-9 * one.abs().max().item()
     assert (gf1 - gfb).abs().max().item() <= 1e-9 * gf1.abs().max().item()
+
+
+@pytest.mark.parametrize("nx,ncols,cons", [
+    (24, 17, ("corners", "faces")),             # 386 interface nodes: 24 tile rows and a strip; 16 + 4 columns a block
+    (24, 20, ("corners", "faces", "edges")),    # the same, 26 coarse DOFs (two groups of 16)
+    (24, 21, ("corners", "faces")),             # two chunks of columns
+    (27, 20, ("corners", "faces")),             # 488 interface nodes: above the LDS of two blocks
+])
+def test_block_products_with_four_more_columns(nx, ncols, cons):
+    """Block adjoints around 16 columns equal the column-by-column ones, both
+    solved to 1e-12 (1e-9 of the largest entry)."""
+    torch = _torch()
+    from paper_2412_17543_amd.solver import Solver
+    g = Solver(nx, _box(nx, 3), workload.lognormal_coef(nx ** 3, 0.5), constraints=cons, autotune=False)
+    print("[gpu] %d^3, %d columns: %d coarse DOFs" % (nx, ncols, g.info()["n_coarse"]), flush=True)
+    u = torch.tensor(workload.rhs_sequence(nx, ncols), device="cuda")
+    one, gf1 = g.adjoint_grad(u, u, 1e-12)
+    blk, gfb, its = g.adjoint_grad_block(u, u, 1e-12)
+    assert (one - blk).abs().max().item() <= 1e-9 * one.abs().max().item()
+    assert (gf1 - gfb).abs().max().item() <= 1e-9 * gf1.abs().max().item()
