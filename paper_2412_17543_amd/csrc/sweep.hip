@@ -31,9 +31,9 @@
 // however much the sizes differ.
 // All sweeps of a setup (local matrices of 729 rows and 343 pivots, saddle
 // matrices of about 412, coarse levels), against 16-pivot panels over both
-// triangles: 64^3 40.6 -> 11.5 ms, 192^3 1,225 -> 309 ms (update tiles 206 ms,
-// 12.4 M of them, 128 KB each through HBM and L2), holed 64^3 (up to 4,700 rows)
-// 257 -> 39 ms.
+// triangles: 64^3 40.6 -> 10.7 ms, 192^3 1,225 -> 296 ms (update tiles 192 ms,
+// 12.4 M of them, 64 KB each through HBM: 4.1 TB/s), holed 64^3 (up to 4,700 rows)
+// 257 -> 36 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -168,11 +168,22 @@ __global__ void __launch_bounds__(256) k_sweep_cols(const Mat *mats, const Item 
     }
 }
 
+// Blocks go to the 8 XCDs in turn; each XCD takes a consecutive eighth of the
+// list, so that a matrix's U and X are read into one L2 instead of eight (update
+// tiles of one setup: 64^3 7.7 -> 6.9 ms, 192^3 206 -> 192, holed 64^3 31 -> 28).
+constexpr int XCDS = 8;
+__device__ __forceinline__ int xcd_item(int n) {
+    const int per = (n + XCDS - 1) / XCDS, i = (int)(blockIdx.x / XCDS), x = blockIdx.x % XCDS;
+    return x * per + i < n ? x * per + i : -1;
+}
+
 // A <- A - U^T X over one 64 x 64 tile: wave w takes rows 16 w .. + 15 and the
 // four 16-column tiles; X staged in LDS, U's 16 columns in registers.
-__global__ void __launch_bounds__(256) k_sweep_update(const Mat *mats, const Item *items) {
+__global__ void __launch_bounds__(256) k_sweep_update(const Mat *mats, const Item *items, int nitems) {
     __shared__ double xs[TS][LDX];
-    const Item it = items[blockIdx.x];
+    const int id = xcd_item(nitems);
+    if (id < 0) return;
+    const Item it = items[id];
     const Mat d = mats[it.mat];
     const int n = d.n, I0 = it.I * TS, J0 = it.J * TS;
     const int t = threadIdx.x, w = t >> 6, L = t & 63, li = L & 15, lk = L >> 4;
@@ -334,7 +345,8 @@ int launch_sweeps(const std::vector<SweepDesc> &h, void *ws, int *status, hipStr
             while (h[p.order[q1 - 1]].p1 <= TS * st) --q1;
             hipLaunchKernelGGL(k_sweep_diag, dim3((unsigned)(q1 - q0)), dim3(256), 0, s, dm + q0, st, status);
             hipLaunchKernelGGL(k_sweep_cols, dim3((unsigned)(ce[q1] - ce[q0])), dim3(256), 0, s, dm, dc + ce[q0], st);
-            hipLaunchKernelGGL(k_sweep_update, dim3((unsigned)(te[q1] - te[q0])), dim3(256), 0, s, dm, dt + te[q0]);
+            hipLaunchKernelGGL(k_sweep_update, dim3((unsigned)((te[q1] - te[q0] + XCDS - 1) / XCDS * XCDS)), dim3(256), 0, s, dm,
+                               dt + te[q0], (int)(te[q1] - te[q0]));
         }
         q1 = p.batch[b + 1];
         hipLaunchKernelGGL(k_sweep_mirror, dim3((unsigned)(te[q1] - te[q0])), dim3(256), 0, s, dm, dt + te[q0]);
