@@ -241,8 +241,8 @@ int bddc_adjoint_grad(bddc_ctx *ctx, const double *dLdu_seq, int32_t n_rhs, cons
  * Arguments as bddc_adjoint_grad; iters: host int32, block iterations
  * (nullable).  Needs n_rhs <= 32, the float64 Neumann operators (local_prec
  * 64 or local_prec_set bit 1), a problem with Dirichlet nodes, and every
- * subdomain interface small enough for the block product's LDS (about 540
- * nodes); otherwise EINVAL.  Errors: ENOTCONV (outputs hold the last
+ * subdomain interface of at most 528 nodes (the block product's LDS and
+ * registers); otherwise EINVAL.  Errors: ENOTCONV (outputs hold the last
  * iterate), EBREAKDOWN, ENOMEM, EHIP.
  */
 int bddc_adjoint_grad_block(bddc_ctx *ctx, const double *dLdu_seq, int32_t n_rhs, const double *u_seq, double rtol,
