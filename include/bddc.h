@@ -111,7 +111,8 @@ typedef struct {
     int32_t product_cfg[8];  /* optional fixed configuration of the two batched
                                 products, Schur then Neumann: blocks per compute
                                 unit, work split (1: blocks inside one subdomain,
-                                0: equal ranges of the tile sequence), waves per
+                                0: equal ranges of the tile sequence; v = 2, 3, ...:
+                                inside one subdomain, 1/v of the blocks), waves per
                                 block (4 or 8), tiles in flight per wave (2 or 4).
                                 A product whose first entry is 0 is autotuned (or
                                 takes the default without autotuning).         */
@@ -345,9 +346,11 @@ int bddc_stats(const bddc_ctx *ctx, double *out, int32_t n);
  * bddc_tuning -- configuration of the two batched operator products (host
  * float64[14]): for the Schur operators then the Neumann operators, kernel
  * blocks, blocks per compute unit requested, work split (1: every block
- * inside one subdomain, 0: equal ranges of the whole tile sequence), waves
+ * inside one subdomain, 0: equal ranges of the whole tile sequence, v > 1:
+ * inside one subdomain with 1/v of the requested blocks), waves
  * per block, tiles in flight per wave, fastest tuning launch in
- * microseconds (0 without autotuning), tiles.
+ * microseconds (0 without autotuning), tiles.  The second to fifth entries
+ * as product_cfg give the same work list again.
  */
 int bddc_tuning(const bddc_ctx *ctx, double *out);
 

@@ -41,7 +41,8 @@ struct OpHost {
     int prec = 64;
     SymvCfg cfg{4, 2};
     int bpc = 6;                    // product blocks per compute unit
-    bool per_sub = true;            // blocks inside single subdomains (else balanced ranges)
+    int split = 1;                  // work split: 0 balanced ranges, v > 0 blocks inside single subdomains,
+                                    // 1/v of the blocks per compute unit asked for
     float tuned_us = 0.f;           // fastest tuning launch
     size_t smem = 0;
     int64_t n_tiles = 0;
@@ -379,9 +380,16 @@ void flush_timing(bddc_ctx *c) {
 }
 
 // ------------------------------------------------------------- work lists
-// Split the work of a batched product over `nblocks` blocks and lay out the
-// partial buffers (one partial vector per segment).  Work is counted in the
-// operators' 256-entry slots (tiles, then the strip of the ragged tail rows).
+// Product blocks for `per_cu` blocks per compute unit, at most one per 16
+// tiles.
+int product_blocks(const bddc_ctx *c, int64_t total_tiles, int per_cu) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * per_cu, (total_tiles + 15) / 16));
+}
+
+// Split the work of a batched product over the nblocks that op.bpc and op.split
+// ask for and lay out the partial buffers (one partial vector per segment).
+// Work is counted in the operators' 256-entry slots (tiles, then the strip of
+// the ragged tail rows).
 // Balanced: the concatenated slot sequence of all subdomains is cut into nblocks equal
 // ranges, each range into segments inside single subdomains (a block may
 // span subdomains).  Per subdomain: every subdomain is cut into about
@@ -389,8 +397,10 @@ void flush_timing(bddc_ctx *c) {
 // spans subdomains; the block count follows the rounding).
 // `lists`: also the gather lists of the products' consumers (not needed to
 // time the product alone).
-int build_worklist(bddc_ctx *c, OpHost &op, int nblocks, bool per_sub, bool lists = true) {
+int build_worklist(bddc_ctx *c, OpHost &op, bool lists = true) {
     const int nsub = c->n_sub;
+    const bool per_sub = op.split != 0;
+    int nblocks = std::max(1, product_blocks(c, op.n_tiles, op.bpc) / std::max(1, op.split));
     struct Seg { int k; int64_t t0, t1; int32_t c; };
     std::vector<Seg> seg;                // segments, block after block
     std::vector<size_t> first(1, 0);     // block b: segments [first[b], first[b + 1])
@@ -1529,12 +1539,6 @@ int sweep_semidefinite(bddc_ctx *c, double *A, int n, int64_t ld, const std::vec
     return 0;
 }
 
-// Product blocks for `per_cu` blocks per compute unit, at most one per 16
-// tiles.
-int product_blocks(const bddc_ctx *c, int64_t total_tiles, int per_cu) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)c->n_cu * per_cu, (total_tiles + 15) / 16));
-}
-
 int setup_operators(bddc_ctx *c) {
     const int nsub = c->n_sub;
     OpHost *ops[2] = {&c->opS, &c->opN};
@@ -1552,7 +1556,7 @@ int setup_operators(bddc_ctx *c) {
         op.bytes = product_bytes(c, op.prec, isN && c->nC > 0);
         op.cfg = SymvCfg{4, 2};
         op.smem = symv_smem(op.prec, op.cfg.nw, c->max_nt);
-        int rc = build_worklist(c, op, product_blocks(c, op.n_tiles, op.bpc), op.per_sub);
+        int rc = build_worklist(c, op);
         if (rc) return rc;
     }
     // (LDS accumulators are float64 for a float64 Neumann batch, else float32)
@@ -1664,7 +1668,7 @@ int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
                                 symv_smem((c->prec_built & 1) ? 64 : 32, nwmax, c->max_nt));
     if (set_symv_smem_limit(lim)) return fail(BDDC_EHIP, "hipFuncSetAttribute (dynamic LDS) failed");
     HIPCHK(hipMemsetAsync(c->d_tmpN, 0, (size_t)c->n_nodes * sizeof(double), c->stream));
-    return build_worklist(c, op, product_blocks(c, op.n_tiles, op.bpc), op.per_sub);
+    return build_worklist(c, op);
 }
 
 // Tile-level autotuning of the batched products on the operators just built:
@@ -1691,7 +1695,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
     int rc = 0;
     const int bpcs[7] = {1, 2, 3, 4, 5, 6, 8};
     OpHost *ops[3] = {&c->opS, &c->opN, &c->opI};
-    struct Cand { float ms; int bpc, div; bool ps; SymvCfg cfg; };   // div: 1/div of the blocks of bpc
+    struct Cand { float ms; int bpc, split; SymvCfg cfg; };
     std::vector<Cand> schur;             // the Schur product's candidates, fastest first
     for (int w = 0; w < 3 && rc == 0; ++w) {
         OpHost &op = *ops[w];
@@ -1723,34 +1727,35 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             ms /= reps;
             return 0;
         };
-        auto split = [&](int bpc, int div, bool ps, bool lists) {
-            return build_worklist(c, op, std::max(1, product_blocks(c, op.n_tiles, bpc) / div), ps, lists);
+        auto split = [&](int bpc, int sp, bool lists) {
+            op.bpc = bpc;
+            op.split = sp;
+            return build_worklist(c, op, lists);
         };
         std::vector<Cand> cand;
         if (w == 2 && !schur.empty()) {
             for (size_t k = 0; k < schur.size() && k < (size_t)TUNE_SHORT && rc == 0; ++k) {
                 Cand t = schur[k];
-                if ((rc = split(t.bpc, t.div, t.ps, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
+                if ((rc = split(t.bpc, t.split, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
                 cand.push_back(t);
             }
         } else {
             std::vector<std::vector<int32_t>> seen[2];   // splits timed: segments per subdomain
             // (where the partials' sum counts, a half and a quarter of the fewest
-            // blocks too)
-            const int nt = gather ? 9 : 7;
-            for (int trial = 0; trial < 2 * nt && rc == 0; ++trial) {
-                const bool ps = trial >= nt;
-                const int q = trial % nt, bpc = q < 7 ? bpcs[q] : 1, div = q < 7 ? 1 : 1 << (q - 6);
-                if ((rc = split(bpc, div, ps, gather))) break;
+            // blocks inside subdomains too)
+            for (int trial = 0; trial < (gather ? 16 : 14) && rc == 0; ++trial) {
+                const int bpc = trial < 14 ? bpcs[trial % 7] : 1, sp = trial < 14 ? trial / 7 : 2 << (trial - 14);
+                if ((rc = split(bpc, sp, gather))) break;
                 std::vector<int32_t> key = op.nchunk;
                 key.push_back(op.dev.n_blocks);          // (a balanced split is its block count)
-                if (std::find(seen[ps].begin(), seen[ps].end(), key) != seen[ps].end()) continue;
-                seen[ps].push_back(std::move(key));
+                auto &list = seen[sp ? 1 : 0];
+                if (std::find(list.begin(), list.end(), key) != list.end()) continue;
+                list.push_back(std::move(key));
                 for (int nw : {4, 8}) {
                     if (nw == 8 && !c->allow8) continue;
                     float ms = 0.f;
                     if ((rc = time_cfg(SymvCfg{nw, 4}, 3, gather, ms))) break;
-                    cand.push_back(Cand{ms, bpc, div, ps, SymvCfg{nw, 4}});
+                    cand.push_back(Cand{ms, bpc, sp, SymvCfg{nw, 4}});
                 }
             }
             // two tiles in flight instead of four on the fastest of these only
@@ -1759,7 +1764,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             for (size_t k = 0, nk = std::min<size_t>(TUNE_TWO, cand.size()); k < nk && rc == 0; ++k) {
                 Cand t = cand[k];
                 t.cfg.unroll = 2;
-                if ((rc = split(t.bpc, t.div, t.ps, gather)) || (rc = time_cfg(t.cfg, 3, gather, t.ms))) break;
+                if ((rc = split(t.bpc, t.split, gather)) || (rc = time_cfg(t.cfg, 3, gather, t.ms))) break;
                 cand.push_back(t);
             }
         }
@@ -1773,7 +1778,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
         for (int round = 0; round < 2 && rc == 0; ++round)
             for (size_t k = 0; k < nk && rc == 0; ++k) {
                 float ms = 0.f;
-                if ((rc = split(cand[k].bpc, cand[k].div, cand[k].ps, gather)) || (rc = time_cfg(cand[k].cfg, 6, gather, ms))) break;
+                if ((rc = split(cand[k].bpc, cand[k].split, gather)) || (rc = time_cfg(cand[k].cfg, 6, gather, ms))) break;
                 tot[k] += ms;
             }
         if (rc) break;
@@ -1782,11 +1787,9 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             if (tot[k] < tot[kb]) kb = k;
         const Cand &best = cand[kb];
         op.cfg = best.cfg;
-        op.bpc = best.bpc;
-        op.per_sub = best.ps;
         op.smem = symv_smem(op.prec, best.cfg.nw, mnt);
         float us = tot[kb] / 2 * 1e3f;
-        if ((rc = split(best.bpc, best.div, best.ps, true))) break;
+        if ((rc = split(best.bpc, best.split, true))) break;
         if (gather) {                                    // (reported: the product alone)
             float ms = 0.f;
             if ((rc = time_cfg(best.cfg, 6, false, ms))) break;
@@ -2454,11 +2457,11 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
                 return fail(BDDC_EINVAL, "product_cfg: waves must be 4 or 8 (8 when it fits), tiles in flight 2 or 4");
             OpHost &op = *ops[w];
             op.bpc = pc[0];
-            op.per_sub = pc[1] != 0;
+            op.split = pc[1] < 0 ? 1 : pc[1];
             op.cfg = SymvCfg{pc[2], pc[3]};
             op.smem = symv_smem(op.prec, op.cfg.nw, c->max_nt);
             op.tuned_us = 0.f;
-            if ((rc = build_worklist(c, op, product_blocks(c, op.n_tiles, op.bpc), op.per_sub))) return rc;
+            if ((rc = build_worklist(c, op))) return rc;
         }
     }
     if ((rc = dalloc(c, &c->d_dotS, (size_t)std::max(1, c->opS.dev.n_blocks)))) return rc;
@@ -3271,16 +3274,16 @@ int bddc_set_launch(bddc_ctx *c, int32_t use_graph, const int32_t *product_cfg) 
                 if ((pc[2] != 4 && pc[2] != 8) || (pc[3] != 2 && pc[3] != 4) || (pc[2] == 8 && !c->allow8))
                     return fail(BDDC_EINVAL, "product_cfg: waves must be 4 or 8 (8 when it fits), tiles in flight 2 or 4");
                 op.bpc = pc[0];
-                op.per_sub = pc[1] != 0;
+                op.split = pc[1] < 0 ? 1 : pc[1];
                 op.cfg = SymvCfg{pc[2], pc[3]};
             } else {   // negative: the untuned default
                 op.bpc = 6;
-                op.per_sub = true;
+                op.split = 1;
                 op.cfg = SymvCfg{4, 2};
             }
             op.smem = symv_smem(op.prec, op.cfg.nw, c->max_nt);
             op.tuned_us = 0.f;
-            if (int rc = build_worklist(c, op, product_blocks(c, op.n_tiles, op.bpc), op.per_sub)) return rc;
+            if (int rc = build_worklist(c, op)) return rc;
         }
         if (c->opS.dev.n_blocks > 0) {
             dfree(c, c->d_dotS);
@@ -3366,7 +3369,7 @@ int bddc_tuning(const bddc_ctx *c, double *out) {
         double *o = out + 7 * w;
         o[0] = ops[w]->dev.n_blocks;
         o[1] = ops[w]->bpc;
-        o[2] = ops[w]->per_sub ? 1.0 : 0.0;
+        o[2] = ops[w]->split;
         o[3] = ops[w]->cfg.nw;
         o[4] = ops[w]->cfg.unroll;
         o[5] = ops[w]->tuned_us;

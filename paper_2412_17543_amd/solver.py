@@ -186,7 +186,10 @@ class Solver:
     TUNING_KEYS = ("blocks", "blocks_per_cu", "per_subdomain", "waves", "unroll", "best_us", "tiles")
 
     def tuning(self) -> dict:
-        """Configuration chosen for the Schur and Neumann products."""
+        """Configuration chosen for the Schur and Neumann products.  The second
+        to fifth values are a `product_cfg` that gives it again
+        (per_subdomain: 0 equal ranges, v > 0 inside subdomains with 1/v of the
+        blocks)."""
         a = (ctypes.c_double * 14)()
         check(self.lib.bddc_tuning(self.ctx, a))
         v = list(a)
