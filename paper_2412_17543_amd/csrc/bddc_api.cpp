@@ -1679,10 +1679,17 @@ int setup_interior(bddc_ctx *c, const std::vector<int64_t> &k_off) {
 // it gains the product (16^3: 48 segments give the update kernel up to 48
 // partials a node), the sum of the partials is timed with the product; from
 // TUNE_GATHER nodes on it follows the product's own time and the lists are
-// built once, for the configuration kept.  The interior product has the Schur
-// product's shape: it is timed on the TUNE_SHORT fastest configurations of
-// that one only.  (Every split used to build and upload all lists: 176 ms of a
-// 64^3 setup, 68 ms at 32^3.  A training step with its setup: 277 -> 139 ms and
+// built once, for the configuration kept.  Above TUNE_GATHER the interior product,
+// of the Schur product's shape, is timed on the TUNE_SHORT fastest configurations
+// of that one only (90^3, 192^3, holed 64^3: within 0.5 % of the fastest of all,
+// 64^3 52.5 against 51.9 us); below, the Schur product's order follows the sums of
+// its partials, which the interior product does not have, and it is timed on its
+// own splits inside subdomains (20^3 in 2^3 subdomains: 11.1 us by the Schur
+// product's order, 8.6 by its own, 26^3 in 3^3 11.5 and 9.1, 32^3 in 4^3 11.0 and
+// 9.7, 16^3 in 2^3 5.7 and 4.9; equal ranges are the fastest on none of the
+// sizes looked at, from 15^3 to 37^3).
+// (Every split used to build and upload all lists: 176 ms of a 64^3 setup,
+// 68 ms at 32^3.  A training step with its setup: 277 -> 139 ms and
 // 95 -> 41 ms, then 136 -> 123 and 39.6 -> 37.8 with two tiles in flight tried on
 // the TUNE_TWO fastest only; 16^3 sequence of 10: 5.08 -> 4.92 ms, Schur call
 // 25.9 -> 24.7 us.)
@@ -1733,7 +1740,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             return build_worklist(c, op, lists);
         };
         std::vector<Cand> cand;
-        if (w == 2 && !schur.empty()) {
+        if (w == 2 && !schur.empty() && c->n_gamma > TUNE_GATHER) {
             for (size_t k = 0; k < schur.size() && k < (size_t)TUNE_SHORT && rc == 0; ++k) {
                 Cand t = schur[k];
                 if ((rc = split(t.bpc, t.split, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
@@ -1745,6 +1752,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             // blocks inside subdomains too)
             for (int trial = 0; trial < (gather ? 16 : 14) && rc == 0; ++trial) {
                 const int bpc = trial < 14 ? bpcs[trial % 7] : 1, sp = trial < 14 ? trial / 7 : 2 << (trial - 14);
+                if (sp == 0 && op.interior && !schur.empty()) continue;   // (small interfaces, see above)
                 if ((rc = split(bpc, sp, gather))) break;
                 std::vector<int32_t> key = op.nchunk;
                 key.push_back(op.dev.n_blocks);          // (a balanced split is its block count)
@@ -1759,7 +1767,8 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
                 }
             }
             // two tiles in flight instead of four on the fastest of these only
-            // (rarely the fastest, never on a split that is slow with four)
+            // (often the fastest on small interfaces, but not on a split that is
+            // slow with four: trying all finds nothing faster)
             std::stable_sort(cand.begin(), cand.end(), [](const Cand &x, const Cand &y) { return x.ms < y.ms; });
             for (size_t k = 0, nk = std::min<size_t>(TUNE_TWO, cand.size()); k < nk && rc == 0; ++k) {
                 Cand t = cand[k];

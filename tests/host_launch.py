@@ -88,7 +88,24 @@ def check_pinned(schur, neumann):
     LIB.bddc_destroy(b)
 
 
-CHECKS = {"pinned": check_pinned}
+def check_interior(schur, interior):
+    """Small interfaces: the interior product gets the split that is best for
+    it, whatever is best for the Schur product and its sums."""
+    got = []
+    for best_schur in (schur, interior):
+        best(OpSchur=best_schur, OpInterior=interior)
+        c = setup(16, 2)
+        n_nodes, n_gamma = sizes(c)
+        F, b = np.zeros(n_nodes), np.zeros(n_gamma)
+        DEV.host_device_forget()
+        _lib.check(LIB.bddc_condense(c, F.ctypes.data, b.ctypes.data))
+        got.append(grid("OpInterior"))
+        LIB.bddc_destroy(c)
+    print("interior blocks", got, flush=True)
+    assert got[0] == got[1] and abs(got[0] - interior) <= interior // 8
+
+
+CHECKS = {"pinned": check_pinned, "interior": check_interior}
 
 if __name__ == "__main__":
     CHECKS[sys.argv[2]](*[int(v) for v in sys.argv[3:]])

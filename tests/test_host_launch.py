@@ -39,3 +39,8 @@ def _run(device, *args):
 ])
 def test_tuned_configuration_can_be_pinned(device, schur, neumann):
     _run(device, "pinned", schur, neumann)
+
+
+@pytest.mark.parametrize("schur,interior", [(8, 232), (24, 232)])
+def test_interior_product_tuned_on_its_own_splits(device, schur, interior):
+    _run(device, "interior", schur, interior)
