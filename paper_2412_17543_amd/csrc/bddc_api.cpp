@@ -3274,14 +3274,16 @@ int bddc_set_launch(bddc_ctx *c, int32_t use_graph, const int32_t *product_cfg) 
     if (use_graph < 0 || use_graph > 2) return fail(BDDC_EINVAL, "use_graph must be 0, 1 or 2");
     HIPCHK(hipStreamSynchronize(c->stream));
     if (product_cfg) {
+        // (refused as a whole: the dot partials below are sized to the Schur product's blocks)
+        for (const int32_t *pc = product_cfg; pc < product_cfg + 8; pc += 4)
+            if (pc[0] > 0 && ((pc[2] != 4 && pc[2] != 8) || (pc[3] != 2 && pc[3] != 4) || (pc[2] == 8 && !c->allow8)))
+                return fail(BDDC_EINVAL, "product_cfg: waves must be 4 or 8 (8 when it fits), tiles in flight 2 or 4");
         OpHost *ops[2] = {&c->opS, &c->opN};
         for (int w = 0; w < 2; ++w) {
             const int32_t *pc = product_cfg + 4 * w;
             OpHost &op = *ops[w];
             if (pc[0] == 0) continue;   // keep this product's configuration
             if (pc[0] > 0) {
-                if ((pc[2] != 4 && pc[2] != 8) || (pc[3] != 2 && pc[3] != 4) || (pc[2] == 8 && !c->allow8))
-                    return fail(BDDC_EINVAL, "product_cfg: waves must be 4 or 8 (8 when it fits), tiles in flight 2 or 4");
                 op.bpc = pc[0];
                 op.split = pc[1] < 0 ? 1 : pc[1];
                 op.cfg = SymvCfg{pc[2], pc[3]};

@@ -105,7 +105,19 @@ def check_interior(schur, interior):
     assert got[0] == got[1] and abs(got[0] - interior) <= interior // 8
 
 
-CHECKS = {"pinned": check_pinned, "interior": check_interior}
+def check_refused(*cfg):
+    """A refused launch configuration changes nothing, whichever product it is
+    refused for (the products' buffers are sized together)."""
+    good, ref = [4, 1, 8, 4], [1, 4, 4, 4]
+    for bad in (list(cfg) + good, good + list(cfg)):
+        c = setup(16, 2, autotune=0, product_cfg=ref * 2)
+        was = tuning(c), apply(c)
+        assert LIB.bddc_set_launch(c, 2, (ctypes.c_int32 * 8)(*bad)) == -1
+        assert (tuning(c), apply(c)) == was, bad
+        LIB.bddc_destroy(c)
+
+
+CHECKS = {"pinned": check_pinned, "interior": check_interior, "refused": check_refused}
 
 if __name__ == "__main__":
     CHECKS[sys.argv[2]](*[int(v) for v in sys.argv[3:]])

@@ -44,3 +44,8 @@ def test_tuned_configuration_can_be_pinned(device, schur, neumann):
 @pytest.mark.parametrize("schur,interior", [(8, 232), (24, 232)])
 def test_interior_product_tuned_on_its_own_splits(device, schur, interior):
     _run(device, "interior", schur, interior)
+
+
+@pytest.mark.parametrize("cfg", [(2, 1, 5, 2), (2, 1, 4, 3)])       # waves, tiles in flight
+def test_refused_launch_configuration_changes_nothing(device, cfg):
+    _run(device, "refused", *cfg)
