@@ -50,9 +50,8 @@ struct OpHost {
     bool interior = false;          // interior operators (sizes nI, no gather lists)
     std::vector<int32_t> nchunk;    // per subdomain
     int32_t *d_items = nullptr, *d_nchunk = nullptr, *d_pb = nullptr;
-    size_t items_cap = 0, yidx_cap = 0;   // allocated lengths (the tuner rebuilds the lists many times)
     double *d_ypart = nullptr;
-    int64_t ypart_len = 0;          // allocated length of the partial buffer
+    size_t items_cap = 0, yidx_cap = 0, ypart_cap = 0;   // allocated lengths (the lists are rebuilt many times)
     int64_t ylen = 0;               // partial entries the current work list writes
     // flat gather list: interface node -> y partials
     int32_t *d_yptr = nullptr, *d_yidx = nullptr;
@@ -136,6 +135,7 @@ struct bddc_ctx {
     int vgrid = 1;
     double *d_b = nullptr, *d_x = nullptr, *d_r = nullptr, *d_z = nullptr, *d_p = nullptr, *d_tmp = nullptr;
     double *d_wloc = nullptr;
+    size_t dotS_cap = 0;
     double *d_rr = nullptr, *d_bbp = nullptr, *d_zp = nullptr, *d_wp = nullptr, *d_dotS = nullptr, *d_gp = nullptr;
     // coarse
     bool three = false;
@@ -231,6 +231,21 @@ int dalloc(bddc_ctx *c, T **p, size_t count) {
     c->dev_bytes += count * sizeof(T);
     c->dev_peak = std::max(c->dev_peak, c->dev_bytes);
     *p = (T *)q;
+    return 0;
+}
+
+void dfree(bddc_ctx *c, void *p);
+
+// Makes a buffer of *cap elements hold at least `count` (its contents are not
+// kept); where there is no memory for it the buffer stays as it was.
+template <typename T>
+int dgrow(bddc_ctx *c, T **p, size_t *cap, size_t count) {
+    if (*p && count <= *cap) return 0;
+    T *q;
+    if (int rc = dalloc(c, &q, count)) return rc;
+    dfree(c, *p);
+    *p = q;
+    *cap = count;
     return 0;
 }
 
@@ -485,32 +500,28 @@ int build_worklist(bddc_ctx *c, OpHost &op, bool lists = true) {
             }
         }
     }
+    // gather lists of the Schur partials (the Neumann partials are summed by
+    // subdomain, interior entries have one owner: no lists)
+    const bool gather = &op == &c->opS && lists;
+    // all memory first, so that a list that finds none leaves the old one whole
     int rc;
     const size_t raw = items.size() * (sizeof(SymvItem) / 4);
-    if (raw > op.items_cap) {
-        dfree(c, op.d_items);
-        if ((rc = dalloc(c, &op.d_items, raw))) return rc;
-        op.items_cap = raw;
-    }
-    if (!op.d_nchunk && ((rc = dalloc(c, &op.d_nchunk, nsub)) || (rc = dalloc(c, &op.d_pb, nsub)))) return rc;
+    if ((rc = dgrow(c, &op.d_items, &op.items_cap, raw)) || (rc = dgrow(c, &op.d_ypart, &op.ypart_cap, (size_t)ylen)) ||
+        (!op.d_nchunk && (rc = dalloc(c, &op.d_nchunk, nsub))) || (!op.d_pb && (rc = dalloc(c, &op.d_pb, nsub))) ||
+        (gather && ((!op.d_yptr && (rc = dalloc(c, &op.d_yptr, c->n_gamma + 1))) ||
+                    (rc = dgrow(c, &op.d_yidx, &op.yidx_cap, (size_t)ylen)))))
+        return rc;
     HIPCHK(hipMemcpyAsync(op.d_items, items.data(), raw * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(op.d_nchunk, nch.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(op.d_pb, pb.data(), nsub * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-    if (ylen > op.ypart_len) {
-        dfree(c, op.d_ypart);
-        if ((rc = dalloc(c, &op.d_ypart, (size_t)ylen))) return rc;
-        op.ypart_len = ylen;
-    }
     op.nchunk = nch;
     op.ylen = ylen;
     op.dev.items = reinterpret_cast<const SymvItem *>(op.d_items);
     op.dev.n_blocks = total > 0 ? nblocks : 0;
     op.dev.nchunk = op.d_nchunk;
     op.dev.pb = op.d_pb;
-    // (the Neumann partials are summed by subdomain, interior entries have one
-    // owner: no lists)
-    if (&op != &c->opS || !lists) return 0;
-    // flat gather lists, owners in assembly order, items in increasing order
+    if (!gather) return 0;
+    // owners in assembly order, items in increasing order
     std::vector<int32_t> ptr(c->n_gamma + 1, 0), idx((size_t)ylen);
     size_t w = 0;
     for (int g = 0; g < c->n_gamma; ++g) {
@@ -521,15 +532,29 @@ int build_worklist(bddc_ctx *c, OpHost &op, bool lists = true) {
         }
         ptr[g + 1] = (int32_t)w;
     }
-    if (!op.d_yptr && (rc = dalloc(c, &op.d_yptr, ptr.size()))) return rc;
-    if (w > op.yidx_cap) {
-        dfree(c, op.d_yidx);
-        if ((rc = dalloc(c, &op.d_yidx, w))) return rc;
-        op.yidx_cap = w;
-    }
     HIPCHK(hipMemcpyAsync(op.d_yptr, ptr.data(), ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(op.d_yidx, idx.data(), w * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
     return 0;
+}
+
+// build_worklist for another block count and split; on failure the work list
+// and what is reported of it stay.
+int resplit(bddc_ctx *c, OpHost &op, int bpc, int split, bool lists = true) {
+    const int bpc0 = op.bpc, split0 = op.split;
+    op.bpc = bpc;
+    op.split = split;
+    const int rc = build_worklist(c, op, lists);
+    if (rc) { op.bpc = bpc0; op.split = split0; }
+    return rc;
+}
+
+// The captured iteration holds its kernels and buffers: a new one is captured
+// when needed.
+void drop_graph(bddc_ctx *c) {
+    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
+    if (c->graph) (void)hipGraphDestroy(c->graph);
+    c->gexec = nullptr;
+    c->graph = nullptr;
 }
 
 // ------------------------------------------------------------- sub-steps
@@ -1734,16 +1759,11 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             ms /= reps;
             return 0;
         };
-        auto split = [&](int bpc, int sp, bool lists) {
-            op.bpc = bpc;
-            op.split = sp;
-            return build_worklist(c, op, lists);
-        };
         std::vector<Cand> cand;
         if (w == 2 && !schur.empty() && c->n_gamma > TUNE_GATHER) {
             for (size_t k = 0; k < schur.size() && k < (size_t)TUNE_SHORT && rc == 0; ++k) {
                 Cand t = schur[k];
-                if ((rc = split(t.bpc, t.split, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
+                if ((rc = resplit(c, op, t.bpc, t.split, false)) || (rc = time_cfg(t.cfg, 3, false, t.ms))) break;
                 cand.push_back(t);
             }
         } else {
@@ -1753,7 +1773,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             for (int trial = 0; trial < (gather ? 16 : 14) && rc == 0; ++trial) {
                 const int bpc = trial < 14 ? bpcs[trial % 7] : 1, sp = trial < 14 ? trial / 7 : 2 << (trial - 14);
                 if (sp == 0 && op.interior && !schur.empty()) continue;   // (small interfaces, see above)
-                if ((rc = split(bpc, sp, gather))) break;
+                if ((rc = resplit(c, op, bpc, sp, gather))) break;
                 std::vector<int32_t> key = op.nchunk;
                 key.push_back(op.dev.n_blocks);          // (a balanced split is its block count)
                 auto &list = seen[sp ? 1 : 0];
@@ -1773,7 +1793,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             for (size_t k = 0, nk = std::min<size_t>(TUNE_TWO, cand.size()); k < nk && rc == 0; ++k) {
                 Cand t = cand[k];
                 t.cfg.unroll = 2;
-                if ((rc = split(t.bpc, t.split, gather)) || (rc = time_cfg(t.cfg, 3, gather, t.ms))) break;
+                if ((rc = resplit(c, op, t.bpc, t.split, gather)) || (rc = time_cfg(t.cfg, 3, gather, t.ms))) break;
                 cand.push_back(t);
             }
         }
@@ -1787,7 +1807,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
         for (int round = 0; round < 2 && rc == 0; ++round)
             for (size_t k = 0; k < nk && rc == 0; ++k) {
                 float ms = 0.f;
-                if ((rc = split(cand[k].bpc, cand[k].split, gather)) || (rc = time_cfg(cand[k].cfg, 6, gather, ms))) break;
+                if ((rc = resplit(c, op, cand[k].bpc, cand[k].split, gather)) || (rc = time_cfg(cand[k].cfg, 6, gather, ms))) break;
                 tot[k] += ms;
             }
         if (rc) break;
@@ -1798,7 +1818,7 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
         op.cfg = best.cfg;
         op.smem = symv_smem(op.prec, best.cfg.nw, mnt);
         float us = tot[kb] / 2 * 1e3f;
-        if ((rc = split(best.bpc, best.split, true))) break;
+        if ((rc = resplit(c, op, best.bpc, best.split))) break;
         if (gather) {                                    // (reported: the product alone)
             float ms = 0.f;
             if ((rc = time_cfg(best.cfg, 6, false, ms))) break;
@@ -2473,7 +2493,7 @@ int setup_impl(bddc_ctx *c, const bddc_mesh *mesh, const bddc_partition *part, c
             if ((rc = build_worklist(c, op))) return rc;
         }
     }
-    if ((rc = dalloc(c, &c->d_dotS, (size_t)std::max(1, c->opS.dev.n_blocks)))) return rc;
+    if ((rc = dgrow(c, &c->d_dotS, &c->dotS_cap, (size_t)std::max(1, c->opS.dev.n_blocks)))) return rc;
     HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     for (auto &e : c->gev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&c->sync_ev, hipEventDisableTiming));
@@ -3243,6 +3263,7 @@ int bddc_set_local_prec(bddc_ctx *c, int32_t prec) {
         return fail(BDDC_EINVAL, "local precision " + std::to_string(prec) + " was not built at setup (local_prec_set)");
     if (prec == c->prec) return 0;
     HIPCHK(hipStreamSynchronize(c->stream));
+    drop_graph(c);                 // (it launches the other precision's kernel)
     c->prec = prec;
     c->d_N = c->d_Nx[q];
     c->d_phir = c->d_phirx[q];
@@ -3257,14 +3278,6 @@ int bddc_set_local_prec(bddc_ctx *c, int32_t prec) {
         int rc = tune_operators(c, 2);
         if (rc) return rc;
     }
-    if (c->gexec) {   // the captured iteration launches the other precision's kernel
-        (void)hipGraphExecDestroy(c->gexec);
-        c->gexec = nullptr;
-    }
-    if (c->graph) {
-        (void)hipGraphDestroy(c->graph);
-        c->graph = nullptr;
-    }
     HIPCHK(hipStreamSynchronize(c->stream));
     return 0;
 }
@@ -3278,38 +3291,39 @@ int bddc_set_launch(bddc_ctx *c, int32_t use_graph, const int32_t *product_cfg) 
         for (const int32_t *pc = product_cfg; pc < product_cfg + 8; pc += 4)
             if (pc[0] > 0 && ((pc[2] != 4 && pc[2] != 8) || (pc[3] != 2 && pc[3] != 4) || (pc[2] == 8 && !c->allow8)))
                 return fail(BDDC_EINVAL, "product_cfg: waves must be 4 or 8 (8 when it fits), tiles in flight 2 or 4");
+        drop_graph(c);
         OpHost *ops[2] = {&c->opS, &c->opN};
+        struct Was { int bpc, split; SymvCfg cfg; size_t smem; float us; } was[2];
+        int rc = 0;
         for (int w = 0; w < 2; ++w) {
+            OpHost &op = *ops[w];
+            was[w] = Was{op.bpc, op.split, op.cfg, op.smem, op.tuned_us};
+        }
+        for (int w = 0; w < 2 && !rc; ++w) {
             const int32_t *pc = product_cfg + 4 * w;
             OpHost &op = *ops[w];
             if (pc[0] == 0) continue;   // keep this product's configuration
-            if (pc[0] > 0) {
-                op.bpc = pc[0];
-                op.split = pc[1] < 0 ? 1 : pc[1];
-                op.cfg = SymvCfg{pc[2], pc[3]};
-            } else {   // negative: the untuned default
-                op.bpc = 6;
-                op.split = 1;
-                op.cfg = SymvCfg{4, 2};
-            }
+            const bool pin = pc[0] > 0; // (negative: the untuned default)
+            if ((rc = pin ? resplit(c, op, pc[0], pc[1] < 0 ? 1 : pc[1]) : resplit(c, op, 6, 1))) break;
+            op.cfg = pin ? SymvCfg{pc[2], pc[3]} : SymvCfg{4, 2};
             op.smem = symv_smem(op.prec, op.cfg.nw, c->max_nt);
             op.tuned_us = 0.f;
-            if (int rc = build_worklist(c, op)) return rc;
+            if (w == 0) rc = dgrow(c, &c->d_dotS, &c->dotS_cap, (size_t)op.dev.n_blocks);
         }
-        if (c->opS.dev.n_blocks > 0) {
-            dfree(c, c->d_dotS);
-            if (int rc = dalloc(c, &c->d_dotS, (size_t)c->opS.dev.n_blocks)) return rc;
+        if (rc) {   // both as they were: nothing grows, so no memory is asked for
+            const std::string why = g_err;
+            for (int w = 0; w < 2; ++w) {
+                OpHost &op = *ops[w];
+                if (product_cfg[4 * w] == 0) continue;
+                (void)resplit(c, op, was[w].bpc, was[w].split);
+                op.cfg = was[w].cfg; op.smem = was[w].smem; op.tuned_us = was[w].us;
+            }
+            HIPCHK(hipStreamSynchronize(c->stream));
+            return fail(rc, why);
         }
     }
     c->opts.use_graph = use_graph;
-    if (c->gexec) {   // the captured iteration holds the old kernels and buffers
-        (void)hipGraphExecDestroy(c->gexec);
-        c->gexec = nullptr;
-    }
-    if (c->graph) {
-        (void)hipGraphDestroy(c->graph);
-        c->graph = nullptr;
-    }
+    drop_graph(c);
     HIPCHK(hipStreamSynchronize(c->stream));
     return 0;
 }
@@ -3400,8 +3414,7 @@ void bddc_destroy(bddc_ctx *c) {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
+    drop_graph(c);
     for (auto &e : c->gev)
         if (e) (void)hipEventDestroy(e);
     if (c->sync_ev) (void)hipEventDestroy(c->sync_ev);

@@ -117,7 +117,40 @@ def check_refused(*cfg):
         LIB.bddc_destroy(c)
 
 
-CHECKS = {"pinned": check_pinned, "interior": check_interior, "refused": check_refused}
+def check_failed(*cfg):
+    """A launch configuration that finds no memory, at whichever allocation,
+    leaves the one before in place; the same call later takes it."""
+    for fn in ("host_device_live", "host_device_bad"):
+        getattr(DEV, fn).restype = ctypes.c_long
+    cfg8 = (ctypes.c_int32 * 8)(*(cfg + cfg))
+    want = setup(16, 2, autotune=0, product_cfg=cfg + cfg)
+    ref = tuning(want), apply(want)
+    failures = 0
+    while True:
+        c = setup(16, 2, autotune=0, product_cfg=[1, 4, 4, 4] * 2)
+        was = tuning(c), apply(c)
+        DEV.host_device_fail_in(ctypes.c_long(failures))
+        rc = LIB.bddc_set_launch(c, 2, cfg8)
+        DEV.host_device_fail_in(ctypes.c_long(-1))
+        if rc == 0:
+            break
+        failures += 1
+        assert rc == -2, rc
+        now = tuning(c), apply(c)
+        _lib.check(LIB.bddc_set_launch(c, 2, (ctypes.c_int32 * 8)(*([1, 4, 4, 4] * 2))))
+        assert (tuning(c), apply(c)) == was
+        _lib.check(LIB.bddc_set_launch(c, 2, cfg8))
+        assert (tuning(c), apply(c)) == ref
+        assert now == was, (now, was)
+        LIB.bddc_destroy(c)
+    print("allocations", failures, flush=True)
+    assert failures >= 1 and DEV.host_device_bad() == 0
+    LIB.bddc_destroy(c)
+    LIB.bddc_destroy(want)
+    assert DEV.host_device_live() == 0
+
+
+CHECKS = {"pinned": check_pinned, "interior": check_interior, "refused": check_refused, "failed": check_failed}
 
 if __name__ == "__main__":
     CHECKS[sys.argv[2]](*[int(v) for v in sys.argv[3:]])

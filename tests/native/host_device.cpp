@@ -18,10 +18,11 @@ std::map<std::string, long> g_best, g_grid;    // kernel name part: cheapest gri
 std::set<void *> g_live;
 double g_clock = 0.0;
 long g_fail_in = -1;                            // device allocations until one fails (-1: none)
+long g_bad = 0;                                 // memory freed twice, copies to or from nowhere
 struct Event { double t = 0.0; };
 constexpr int OK = 0, INVALID = 1, NO_MEMORY = 2;
 int copy(void *d, const void *s, size_t n) {
-    if (n && (!d || !s)) return INVALID;
+    if (n && (!d || !s)) { ++g_bad; return INVALID; }
     if (n) std::memmove(d, s, n);
     return OK;
 }
@@ -39,6 +40,7 @@ long host_device_last_grid(const char *part) {
 }
 void host_device_forget() { g_grid.clear(); }
 long host_device_live() { return (long)g_live.size(); }
+long host_device_bad() { return g_bad; }
 
 // ---- module registration and launches
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
@@ -77,7 +79,7 @@ int hipMalloc(void **p, size_t n) {
     return OK;
 }
 int hipFree(void *p) {
-    if (p && !g_live.erase(p)) return INVALID;      // freed twice, or not ours
+    if (p && !g_live.erase(p)) { ++g_bad; return INVALID; }
     std::free(p);
     return OK;
 }

@@ -49,3 +49,8 @@ def test_interior_product_tuned_on_its_own_splits(device, schur, interior):
 @pytest.mark.parametrize("cfg", [(2, 1, 5, 2), (2, 1, 4, 3)])       # waves, tiles in flight
 def test_refused_launch_configuration_changes_nothing(device, cfg):
     _run(device, "refused", *cfg)
+
+
+@pytest.mark.parametrize("cfg", [(8, 0, 8, 4), (2, 1, 4, 2)])
+def test_failed_launch_configuration_changes_nothing(device, cfg):
+    _run(device, "failed", *cfg)
