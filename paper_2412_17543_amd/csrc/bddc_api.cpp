@@ -1772,6 +1772,9 @@ int tune_operators(bddc_ctx *c, int mask = 7) {
             // blocks inside subdomains too)
             for (int trial = 0; trial < (gather ? 16 : 14) && rc == 0; ++trial) {
                 const int bpc = trial < 14 ? bpcs[trial % 7] : 1, sp = trial < 14 ? trial / 7 : 2 << (trial - 14);
+                // (the same count of blocks again: the same list, not built)
+                if (trial % 7 && trial < 14 && product_blocks(c, op.n_tiles, bpc) == product_blocks(c, op.n_tiles, bpcs[trial % 7 - 1]))
+                    continue;
                 if (sp == 0 && op.interior && !schur.empty()) continue;   // (small interfaces, see above)
                 if ((rc = resplit(c, op, bpc, sp, gather))) break;
                 std::vector<int32_t> key = op.nchunk;
