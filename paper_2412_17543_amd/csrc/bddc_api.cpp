@@ -2595,9 +2595,6 @@ int alloc_block(bddc_ctx *c, BlockWork &b) {
     HIPCHK(hipMemcpyAsync(b.items, is.data(), nsub * sizeof(BlockItem), hipMemcpyHostToDevice, c->stream));
     if (hipHostMalloc((void **)&b.h, sizeof(double) * (4 * BlockWork::GSZ + 6 * BlockWork::CSZ)) != hipSuccess)
         return fail(BDDC_ENOMEM, "hipHostMalloc failed (block adjoint)");
-    // partial slots that no kernel writes (none with one chunk per subdomain) stay zero
-    launch_fill((int64_t)b.ylen * BMAX, 0.0, b.yN, c->stream);
-    launch_fill((int64_t)b.clen * BMAX, 0.0, b.cN, c->stream);
     for (int n : c->h_nB) b.max_nt = std::max(b.max_nt, tile_rows(n));
     return 0;
 }
