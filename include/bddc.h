@@ -332,7 +332,9 @@ int bddc_interface_nodes(const bddc_ctx *ctx, int64_t *out);
  * enabled (bddc_enable_timing: 0 off, 1 every class, otherwise a bit mask of
  * the classes to time, bit k = class k).  While timing is enabled the
  * iteration is launched kernel by kernel (no graph) so that every launch can
- * be bracketed by events.  out (host float64[3*n]) receives,
+ * be bracketed by events, and a dense coarse problem of up to 512 DOFs is
+ * solved by a kernel of its own (class 2), where it is otherwise solved inside
+ * the prolongation (class 3; same results).  out (host float64[3*n]) receives,
  * for kernel class k: total milliseconds, launch count, algorithmic bytes per
  * launch (packed upper triangle of the symmetric operators + coarse bases +
  * gathered input, its index and the output).
@@ -403,6 +405,9 @@ int bddc_set_launch(bddc_ctx *ctx, int32_t use_graph, const int32_t *product_cfg
  *          (eqs. averaging_subdomain_solves, coarse_problem, localCorr)
  *   [8,9]  the coarse levels alone (from the restriction's partials)
  *   [10,11] prolongation and assembly alone
+ * [6,7] is the application as a solve runs it: with a dense coarse problem of up
+ * to 512 DOFs the prolongation solves it, and [8,9] and [10,11] are separate
+ * kernels that such a solve does not launch.
  * Algorithmic bytes are those the method must move (operators in their
  * stored precision, packed; gathered vectors and index lists once).
  * Errors: EINVAL, EHIP.

@@ -19,8 +19,12 @@
 // by bit) and LDS carries one write and one read of a tile, X (staged in
 // operand order) and 8 partial tiles a row.  Each column's next tile, one row
 // down, is requested as soon as the current one is used: NJ tiles in flight a
-// wave, in fixed registers.  A short ragged tail stored as a strip after the
-// tiles (uses_strip) follows as one more tile row.
+// wave, in registers (but NJ = 4, of the 128 registers that two blocks leave a
+// lane, passes one column's tile through scratch in the first 8 tile rows; NJ = 3
+// keeps an index or two there, NJ = 5 has registers enough).  One variant serves
+// all subdomains of a launch, the one that the largest needs.  A short ragged
+// tail stored as a strip after the tiles (uses_strip) follows as one more tile
+// row.
 // What bounds it: the matrix cores, 8 v_mfma_f64_16x16x4f64 a tile and chunk
 // (about 70 cycles each: 0.21 ms for the 0.46 M tiles of 96^3 and two chunks;
 // the tiles' bytes take 0.15 ms).  Two blocks a compute unit (at most 80 KB of
@@ -73,7 +77,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void *p, int64_
 // j + 16 k of every block's lanes, (i, j) of block m returned in lane
 // 4 m + j + 16 i): 9 ns a step and SIMD against 28, where a second chunk would
 // take 28 for 16 columns of which 12 are none.  96^3, 20 columns: 0.42 -> 0.32 ms
-// a product, block adjoint 34.5 -> 30.2 ms.
+// a product, block adjoint 34.5 -> 30.2 ms.  It covers 17 to 20 columns only: a
+// product takes 0.25 ms for 1 to 16, 0.32 to 20, then 0.44 (21) to 0.45 (32) in two
+// chunks.
 __device__ __forceinline__ double mfma4(double a, double b, double c) {
     return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }

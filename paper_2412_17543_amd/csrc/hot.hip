@@ -1559,7 +1559,9 @@ void launch_prolong_cols(const ProlArgs &a, int nblocks, int ncols, hipStream_t 
 
 // Registers and loads are laid out for KM columns: buckets of 8 up to 48 (a
 // basis of 20 in a bucket of 32 issues 12 loads a node for nothing, one of 40
-// in a bucket of 48 8: 192^3 direction update 133 -> 122 us, assembly 147 -> 140).
+// in a bucket of 48 8).  192^3, both builds in turn on one card, with the sums
+// over lanes and the joint loads above: direction update 132 -> 122 us, assembly
+// 136 -> 129.
 int kmax_bucket(int k) { return k <= 48 ? (k + 7) / 8 * 8 : 64; }
 
 #define KM_SWITCH(kmax, CALL)            \

@@ -447,7 +447,7 @@ void launch_l2_b(const L2Args &a, int nsr, int max_nL, hipStream_t s, int ncols 
 size_t l2_d_smem(int max_nL);
 int set_l2_smem_limit(size_t bytes);
 void launch_l2_d(const L2Args &a, int nsr, size_t smem, hipStream_t s, int ncols = 1);
-// deflation-column bucket of the templated reductions (0, 8, 16, 32, 64)
+// deflation-column bucket of the templated reductions (0, 8, ..., 48, 64)
 int kmax_bucket(int k);
 
 }  // namespace bddc

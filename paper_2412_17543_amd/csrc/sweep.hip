@@ -16,9 +16,9 @@
 // What bounds it: every panel reads and writes the whole trailing matrix (the
 // swept rows too), so the bytes are n^2 x panels.  64 pivots a panel instead
 // of 16 and the upper triangle of 64 x 64 tiles only (the lower one is
-// mirrored once at the end) move an eighth of the bytes; a 64-pivot update is
-// 16 flop/byte, near where the matrix cores and HBM meet (70 TFLOP/s, 4.9
-// TB/s copied).  Per panel s (pivots 64 s .. 64 s + b - 1, every pivot checked
+// mirrored once at the end) move an eighth of the bytes.  A 64-pivot update does
+// 524,288 flop on a tile of 64 KB read and written, 8 flop/byte: HBM bounds it,
+// the matrix cores and a copy meet at about 14 (70 TFLOP/s, 4.9 TB/s copied).  Per panel s (pivots 64 s .. 64 s + b - 1, every pivot checked
 // for its expected sign):
 //   k_sweep_diag   (one block per matrix) sweeps the b x b block in registers;
 //   k_sweep_cols   (one block per 64 columns) U = A(P, :), X = A_PP^{-1} U
