@@ -67,8 +67,8 @@ def test_block_product_refuses_larger_interfaces():
 @pytest.mark.parametrize("nx,cells,cons,inside", [
     (8, 2, ("corners", "faces"), True),                 # 18 coarse DOFs
     (24, "c3s", ("corners", "edges"), True),            # an odd count, uneven subdomains
-    (20, 5, ("corners", "faces"), True),                # 364
-    (20, 5, ("corners", "faces", "edges"), False),      # 664: by blocks of the operator, outside
+    (20, 5, ("corners", "faces"), True),                # 444
+    (20, 5, ("corners", "faces", "edges"), False),      # 684: by blocks of the operator, outside
 ])
 def test_coarse_solve_on_both_sides_of_the_limit(nx, cells, cons, inside):
     """M^{-1} r against the oracle (sums of at most a few thousand products of
